@@ -67,19 +67,38 @@ struct Tiling {
 // The fp32 path, which is held to a tighter tolerance, takes shorter runs.
 int64_t max_fp32_run(int dt) { return dt == LA_BF16 ? 16384 : 4096; }
 
-Tiling choose_tiling(int64_t N, int d, int dt) {
-  // at least 2048 (d = 128) or 512 tokens per partial: the 16,384-token
-  // grid shape (64 heads, d = 64) gave 0.151 / 0.146 / 0.159 ms for its
-  // cache-flushed forward at 1024 / 512 / 256
-  const int64_t tw_min = d >= 128 ? 2048 : 512;
-  // at most 128 partials at d = 128 and 64 below while that keeps each
-  // FP32 run within max_fp32_run: longer ranges per wave paid off at d = 64
-  // (summary of 32 heads x 262,144 tokens 0.38 -> 0.33 ms), while 8 heads
-  // at d = 128 need the 128 to give each SIMD a wave.  Beyond that the
-  // partial count grows with N (about (d^2 + d) * 4 bytes of workspace per
-  // max_fp32_run tokens per head: 0.8 % of the inputs' bytes at d = 128).
-  const int64_t p_max = d >= 128 ? 128 : 64;
-  int64_t P = std::min<int64_t>(p_max, ceil_div(N, tw_min));
+// At most 128 partials at d = 128 and 64 below while that keeps each FP32
+// run within max_fp32_run: longer ranges per wave paid off at d = 64
+// (summary of 32 heads x 262,144 tokens 0.38 -> 0.33 ms), while 8 heads at
+// d = 128 need the 128 to give each SIMD a wave.  Beyond that the partial
+// count grows with N (about (d^2 + d) * 4 bytes of workspace per
+// max_fp32_run tokens per head: 0.8 % of the inputs' bytes at d = 128).
+int64_t max_partials(int d) { return d >= 128 ? 128 : 64; }
+
+// The fused query backward: a partial per wave (d <= 64) or workgroup.
+// At least 2048 (d = 128) or 512 tokens each.
+int64_t fused_partials(int64_t N, int d) {
+  return std::min<int64_t>(max_partials(d), ceil_div(N, d >= 128 ? 2048 : 512));
+}
+
+// The summary: a partial's write and read cost 2 (d + 1) * 4 bytes against
+// 2 * es bytes of K and V a token and feature, so a partial of 32 d bf16
+// tokens adds 6 % and is the rule (16 d in fp32: the same bytes).  Short
+// sequences take up to four (fp32: eight) shorter ones, not below 4 d (2 d)
+// tokens, so that a few heads still fill compute units: one head of 4,096
+// fp32 tokens (d = 64) takes 16 us in eight partials and 26 in four, while
+// 1,024 heads of 8,192 bf16 tokens take 396 + 94 us (summary + combine) in
+// four and 430 + 110 in eight.
+int64_t summary_partials(int64_t N, int d, int dt) {
+  const int64_t unit = dt == LA_BF16 ? 4 * d : 2 * d;
+  const int64_t few = dt == LA_BF16 ? 4 : 8;
+  return std::max(std::min(max_partials(d), ceil_div(N, 8 * unit)), std::min(few, ceil_div(N, unit)));
+}
+
+bool fused_backward(int d, int dt) { return dt == LA_BF16 && d >= 32; }
+
+Tiling choose_tiling(int64_t N, int d, int dt, bool backward) {
+  int64_t P = backward && fused_backward(d, dt) ? fused_partials(N, d) : summary_partials(N, d, dt);
   P = std::max<int64_t>(P, ceil_div(N, max_fp32_run(dt)));
   // a multiple of 64: the summary steps over 32 tokens, the fused
   // backward over 64 (four waves x 16); max_fp32_run is one too, so
@@ -94,6 +113,11 @@ Tiling choose_tiling(int64_t N, int d, int dt) {
   t.Tk = (int)std::min<int64_t>(2048, ceil_div(N, 64) * 64);
   return t;
 }
+
+// Partials the workspace has room for: those of the tiling, or as many as
+// 512 (d = 128: 2048) tokens each would make, which keeps the size the
+// same from 64 (128) of them up to max_fp32_run tokens each.
+int64_t partial_room(int64_t N, int d, int P) { return std::max<int64_t>(P, fused_partials(N, d)); }
 
 // Apply workgroups per head: about kApplyGrid in the whole grid (a few per
 // compute unit), at most one per token block.  Per-token work, so this
@@ -130,12 +154,11 @@ struct Layout {
 // per query token (1/den, -(dO . O)) between the query kernel and the dS
 // reduction, the only part of any workspace that grows with N.  bf16 at
 // d >= 32 fuses the two passes and needs no stash.
-bool fused_backward(const la_attn_desc* d) { return d->in_dtype == LA_BF16 && d->d >= 32; }
-
 Layout layout_for(const la_attn_desc* d, int pass) {
   const int64_t BH = d->B * d->H, D = d->d;
-  const Tiling t = choose_tiling(d->N, (int)D, d->in_dtype);
-  const size_t part = align_up((size_t)BH * t.P * (D * D + D) * sizeof(float));
+  const Tiling t = choose_tiling(d->N, (int)D, d->in_dtype, pass == 1);
+  const size_t part =
+      align_up((size_t)BH * partial_room(d->N, (int)D, t.P) * (D * D + D) * sizeof(float));
   const size_t mat = align_up((size_t)BH * D * D * sizeof(double));
   const size_t vec = align_up((size_t)BH * D * sizeof(double));
   const size_t img = align_up((size_t)BH * head_image_bytes((int)D, d->in_dtype));
@@ -152,7 +175,7 @@ Layout layout_for(const la_attn_desc* d, int pass) {
     L.img = off; off += img;
     L.part = off; off += part;
     L.stash = off;
-    if (!fused_backward(d)) off += align_up((size_t)BH * d->N * 2 * sizeof(float));
+    if (!fused_backward((int)D, d->in_dtype)) off += align_up((size_t)BH * d->N * 2 * sizeof(float));
     L.dS64 = off; off += mat;
     L.dz64 = off; off += vec;
     L.dimg = off; off += img;
@@ -189,7 +212,7 @@ la_status forward_impl(const la_attn_desc* desc, const void* q, const void* k, c
   if (((uintptr_t)s_out & 7u) || ((uintptr_t)z_out & 7u)) return LA_ERR_INVALID_ARG;
   const Layout L = layout_for(desc, 0);
   if (ws_bytes < L.total) return LA_ERR_OOM;
-  const Tiling t = choose_tiling(desc->N, (int)desc->d, desc->in_dtype);
+  const Tiling t = choose_tiling(desc->N, (int)desc->d, desc->in_dtype, false);
   char* w = (char*)ws;
   la::FwdArgs a{};
   a.B = desc->B; a.H = desc->H; a.N = desc->N; a.D = (int)desc->d;
@@ -221,7 +244,6 @@ la_status apply_impl(const la_attn_desc* desc, const void* q, const double* s, c
   if (((uintptr_t)ws % kAlign) != 0) return LA_ERR_INVALID_ARG;
   const Layout L = layout_for(desc, 2);
   if (ws_bytes < L.total) return LA_ERR_OOM;
-  const Tiling t = choose_tiling(desc->N, (int)desc->d, desc->in_dtype);
   la::FwdArgs a{};
   a.B = desc->B; a.H = desc->H; a.N = desc->N; a.D = (int)desc->d;
   a.in_dt = desc->in_dtype; a.out_dt = desc->out_dtype;
@@ -325,7 +347,7 @@ la_status la_backward(const la_attn_desc* desc, const void* q, const void* k,
   if (((uintptr_t)ws % kAlign) != 0) return LA_ERR_INVALID_ARG;
   const Layout L = layout_for(desc, 1);
   if (ws_bytes < L.total) return LA_ERR_OOM;
-  const Tiling t = choose_tiling(desc->N, (int)desc->d, desc->in_dtype);
+  const Tiling t = choose_tiling(desc->N, (int)desc->d, desc->in_dtype, true);
   char* w = (char*)ws;
   la::BwdArgs a{};
   a.B = desc->B; a.H = desc->H; a.N = desc->N; a.D = (int)desc->d;

@@ -70,16 +70,27 @@ __device__ __forceinline__ void summary_load(const char* kh, const char* vh, uin
   }
 }
 
-// Grid: with SPLIT = 1, one dimension of waves in (partial, (b, h)) order,
-// (b, h) fastest: wave w takes partial w / BH of (b, h) = w % BH, so a
-// block's four waves are four heads over the same tokens (with heads
-// interleaved in a token row, BNHD, one compute unit then reads adjacent
-// slices of the same rows: the summary at d = 64, 16 heads, went from 1.55
-// to 1.32 ms; BHND is unaffected).  Otherwise x = partial, y = (b, h), and
-// the block's SPLIT waves share partial x, wave w owning S tile rows
-// [FR*w, +FR).  Which waves share a block does not change any partial's
+// SUM_WAVE: one dimension of waves in (partial, (b, h)) order, (b, h)
+// fastest: wave w takes partial w / BH of (b, h) = w % BH, so a block's four
+// waves are four heads over the same tokens (with heads interleaved in a
+// token row, BNHD, one compute unit then reads adjacent slices of the same
+// rows: the summary at d = 64, 16 heads, went from 1.55 to 1.32 ms; BHND is
+// unaffected).  Which waves share a block does not change any partial's
 // arithmetic.
-template <int DT, int D, int MODE>
+// SUM_TEAM: one workgroup per (partial, (b, h)), in the same order; its four
+// waves take the partial's steps in turn and add their sums in LDS, so a
+// short sequence is four times as many waves of a quarter of the steps for
+// the same partials in memory (one head of 4,096 fp32 tokens at d = 64:
+// 45 -> 16 us; 64 heads of 16,384 bf16 tokens at d = 64: 54 -> 50 us).
+// Each XCD takes a contiguous share of the items (workgroups go to the
+// eight XCDs in turn), so the heads of one token range, which share cache
+// lines on a BNHD view at d <= 32, are read through one L2 (d = 32, 8
+// heads of 30,001 tokens: 47 -> 38 us).
+// SUM_SPLIT (fp32 at d = 128): x = partial, y = (b, h), and the block's
+// SPLIT waves share partial x, wave w owning S tile rows [FR*w, +FR).
+enum { SUM_WAVE = 0, SUM_TEAM = 1, SUM_SPLIT = 2 };
+
+template <int DT, int D, int MODE, int FORM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SummaryCfg<DT, D, MODE>::WAVES_PER_SIMD))) void summary_kernel(
     const void* __restrict__ k, const void* __restrict__ v, int64_t sb,
     int64_t sh, int64_t sn, int H, int64_t N, int P, int Tw,
@@ -89,11 +100,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SummaryCfg<
   constexpr int E = D * D + D;
   const int lane = threadIdx.x & 63, wave = wave_index();
   const int g = lane >> 4, m = lane & 15;
-  const int64_t wid = (int64_t)blockIdx.x * 4 + wave;  // SPLIT = 1
-  const int p = C::SPLIT > 1 ? (int)blockIdx.x : (int)(wid / BH);
-  const int half = C::SPLIT > 1 ? wave : 0;
-  if (p >= P) return;  // uniform across a SPLIT group (it shares p)
-  const int bh = C::SPLIT > 1 ? (int)blockIdx.y : (int)(wid % BH);
+  static_assert((FORM == SUM_SPLIT) == (C::SPLIT > 1), "form of the configuration");
+  int64_t item = (int64_t)blockIdx.x * 4 + wave;
+  if constexpr (FORM == SUM_TEAM)
+    item = (int64_t)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  const int p = FORM == SUM_SPLIT ? (int)blockIdx.x : (int)(item / BH);
+  const int half = FORM == SUM_SPLIT ? wave : 0;
+  if (p >= P) return;  // uniform across the waves that share p
+  const int bh = FORM == SUM_SPLIT ? (int)blockIdx.y : (int)(item % BH);
   const int64_t b = bh / H, h = bh % H;
   const int64_t t_begin = (int64_t)p * Tw;
   const int64_t t_end = min(N, t_begin + (int64_t)Tw);
@@ -127,22 +141,60 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SummaryCfg<
   auto load = [&](int64_t t0, SummaryRegs<DT, D, MODE>& x) {
     summary_load<DT, D, MODE>(kh, vh, koff, voff, tstash, row_bytes, t0, g, m, t_end, x);
   };
-  int64_t t0 = t_begin;
+  // a team's wave past the partial's end runs one step of masked rows,
+  // which adds nothing
+  constexpr int STRIDE = FORM == SUM_TEAM ? 4 * C::STEP : C::STEP;
+  int64_t t0 = t_begin + (FORM == SUM_TEAM ? wave * C::STEP : 0);
   load(t0, ra);
   while (true) {
-    const int64_t t1 = t0 + C::STEP;
+    const int64_t t1 = t0 + STRIDE;
     if (t1 < t_end) load(t1, rb);
     summary_step<DT, D, MODE>(ra, half, lane, xch, acc, zacc);
     if (t1 >= t_end) break;
-    const int64_t t2 = t1 + C::STEP;
+    const int64_t t2 = t1 + STRIDE;
     if (t2 < t_end) load(t2, ra);
     summary_step<DT, D, MODE>(rb, half, lane, xch + C::XW, acc, zacc);
     if (t2 >= t_end) break;
     t0 = t2;
   }
 
-  // this wave's share of the partial: S tiles in lane order, then z
   float* out = part + ((int64_t)bh * P + p) * E;
+  if constexpr (FORM == SUM_TEAM) {
+    // the waves' sums meet in LDS, RT tiles at a time, and are added in
+    // FP64 as (w0 + w1) + (w2 + w3): one more FP32 rounding a partial
+    constexpr int T = F * F, RT = T < 16 ? T : 16;
+    __shared__ f32x4 red[4][RT][64];
+    __shared__ float zred[4][D];
+    auto sum4 = [](float a, float b, float c, float e) {
+      return (float)(((double)a + (double)b) + ((double)c + (double)e));
+    };
+#pragma unroll
+    for (int i = 0; i < F; ++i) {
+      const float zs = sum_groups(zacc[i]);
+      if (g == 0) zred[wave][F * m + i] = zs;
+    }
+#pragma unroll
+    for (int r0 = 0; r0 < T; r0 += RT) {
+      if (r0 > 0) __syncthreads();  // the buffers have been read
+#pragma unroll
+      for (int t = 0; t < RT; ++t) red[wave][t][lane] = acc[(r0 + t) / F][(r0 + t) % F];
+      __syncthreads();
+      for (int t = wave; t < RT; t += 4) {
+        f32x4 s;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          s[r] = sum4(red[0][t][lane][r], red[1][t][lane][r], red[2][t][lane][r], red[3][t][lane][r]);
+        *(f32x4*)(out + ((r0 + t) * 64 + lane) * 4) = s;
+      }
+    }
+    if (threadIdx.x < D) {
+      const int f = threadIdx.x;
+      out[D * D + f] = sum4(zred[0][f], zred[1][f], zred[2][f], zred[3][f]);
+    }
+    return;
+  }
+
+  // this wave's share of the partial: S tiles in lane order, then z
 #pragma unroll
   for (int il = 0; il < FR; ++il) {
     const int i = FR * half + il;
@@ -463,19 +515,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
 // ---------------------------------------------------------------------------
 // Host-side launchers
 // ---------------------------------------------------------------------------
+// Four waves share a partial of at most this many tokens.  Longer ones keep
+// the SIMDs streaming by themselves, and there the workgroups' common end
+// costs (8 heads of 2,097,152 tokens at d = 128, 16,384 to a partial: 1.30
+// ms with a wave to a partial, 1.36 with four; 32 heads of 262,144 at
+// d = 64, 4,096 to a partial: the training step 2.22 and 2.26 ms).
+constexpr int kTeamTokens = 2048;
+
 template <int DT, int D, int MODE>
 static void launch_summary_t(const void* k, const void* v, int64_t sb, int64_t sh, int64_t sn,
                              int64_t BH, int64_t H, int64_t N, int P, int Tw,
                              const float2* stash, float* part, hipStream_t stream) {
   using C = SummaryCfg<DT, D, MODE>;
-  // block geometry comes from the kernel's own configuration: SPLIT waves
-  // share one partial, or four waves take one partial each
-  static_assert(C::THREADS == 64 * (C::SPLIT > 1 ? C::SPLIT : 4), "block shape");
-  static_assert(C::SPLIT == 1 || C::PPB == 1, "split blocks hold one partial");
-  const dim3 grid = C::SPLIT > 1 ? dim3((unsigned)P, (unsigned)BH)
-                                 : dim3((unsigned)((P * BH + 3) / 4));
-  summary_kernel<DT, D, MODE><<<grid, C::THREADS, 0, stream>>>(k, v, sb, sh, sn, (int)H, N, P, Tw,
-                                                               stash, part, (int)BH);
+  if constexpr (C::SPLIT > 1) {
+    summary_kernel<DT, D, MODE, SUM_SPLIT><<<dim3((unsigned)P, (unsigned)BH), C::THREADS, 0, stream>>>(
+        k, v, sb, sh, sn, (int)H, N, P, Tw, stash, part, (int)BH);
+  } else if (Tw <= kTeamTokens) {
+    summary_kernel<DT, D, MODE, SUM_TEAM><<<dim3((unsigned)((P * BH + 7) / 8 * 8)), 256, 0, stream>>>(
+        k, v, sb, sh, sn, (int)H, N, P, Tw, stash, part, (int)BH);
+  } else {
+    summary_kernel<DT, D, MODE, SUM_WAVE><<<dim3((unsigned)((P * BH + 3) / 4)), 256, 0, stream>>>(
+        k, v, sb, sh, sn, (int)H, N, P, Tw, stash, part, (int)BH);
+  }
 }
 
 template <int D>

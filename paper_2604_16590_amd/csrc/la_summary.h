@@ -34,7 +34,6 @@ struct SummaryCfg {
   static constexpr int R = DT == DT_BF16 ? 8 : 4;  // tokens per lane group per step
   static constexpr int STEP = 4 * R;               // tokens per wave per step
   static constexpr int THREADS = SPLIT > 1 ? 64 * SPLIT : 256;
-  static constexpr int PPB = SPLIT > 1 ? 1 : 4;    // partials per workgroup
   // LDS words exchanged per buffer: bf16 -> F operands x 4 words x 64 lanes;
   // fp32 -> R tokens x F values x 64 lanes
   static constexpr int XW = SPLIT > 1 ? (DT == DT_BF16 ? F * 4 * 64 : R * F * 64) : 1;
