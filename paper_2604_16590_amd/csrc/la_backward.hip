@@ -346,8 +346,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void b
 // d x d partial dS stays in registers, so the next step's Q and G are
 // prefetched straight into LDS (global_load_lds, 16 bytes per lane)
 // instead of registers.
-// Partial tile (i, j) holds, in lane (g, n) register r, dS[16i + 4g + r][16j + n]
-// (the combine's block layout); the partial's dz follows at offset d*d.
+// Partial tile (i, j) holds, in lane (g, n) register r, dS[16i + 4g + r][16j + n];
+// the partial is stored as rows of dS, then dz.
 // ---------------------------------------------------------------------------
 template <int D>
 struct FusedCfg {
@@ -607,12 +607,14 @@ void bwd_qds_kernel(const void* __restrict__ q, const void* __restrict__ dout, i
     }
   }
 
-  // the wave's partial: dS tiles in lane order, then dz
+  // the wave's partial: rows of dS, then dz
   float* out = part + ((int64_t)bh * P + p) * E;
 #pragma unroll
   for (int i = 0; i < NB; ++i)
 #pragma unroll
-    for (int j = 0; j < NB; ++j) *(f32x4*)(out + ((i * NB + j) * 64 + lane) * 4) = ds[i][j];
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) out[(16 * i + 4 * g + r) * D + 16 * j + n] = ds[i][j][r];
   // dz: add the four lane groups' token subsets
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
@@ -883,7 +885,9 @@ void bwd_qds4_kernel(const void* __restrict__ q, const void* __restrict__ dout, 
   for (int ii = 0; ii < IW; ++ii)
 #pragma unroll
     for (int jj = 0; jj < JW; ++jj)
-      *(f32x4*)(out + (((i0 + ii) * NB + j0 + jj) * 64 + lane) * 4) = ds[ii][jj];
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        out[(16 * (i0 + ii) + 4 * g + r) * D + 16 * (j0 + jj) + n] = ds[ii][jj][r];
   if (has_dz) {
 #pragma unroll
     for (int ii = 0; ii < IW; ++ii)
@@ -1063,7 +1067,7 @@ static hipError_t launch_rows(const BwdArgs& a) {
         a.q, a.dout, a.sb, a.sh, a.sn, a.dq, a.osb, a.osh, a.osn, (int)a.H, a.N, a.P, a.Tw,
         a.img, a.z64, a.part);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    e = launch_combine(a.part, a.P, a.dS64, a.dz64, a.dimg, DT, BH, D, PART_BLOCKS, a.stream);
+    e = launch_combine(a.part, a.P, a.dS64, a.dz64, a.dimg, DT, BH, D, IMG_T | IMG_N, a.stream);
   } else if constexpr (DT == DT_BF16 && (D == 32 || D == 64)) {
     // one pass: dQ and the per-wave partials of dS, dz (at d = 128 the
     // whole partial dS plus the query pass's state exceed the registers of
@@ -1074,7 +1078,7 @@ static hipError_t launch_rows(const BwdArgs& a) {
         a.q, a.dout, a.sb, a.sh, a.sn, a.dq, a.osb, a.osh, a.osn, (int)a.H, a.N, a.P, a.Tw,
         a.img, a.z64, a.part);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    e = launch_combine(a.part, a.P, a.dS64, a.dz64, a.dimg, DT, BH, D, PART_BLOCKS, a.stream);
+    e = launch_combine(a.part, a.P, a.dS64, a.dz64, a.dimg, DT, BH, D, IMG_T | IMG_N, a.stream);
   } else {
     {
       ProfScope prof("bwd_query", a.stream);
@@ -1086,7 +1090,7 @@ static hipError_t launch_rows(const BwdArgs& a) {
     e = launch_summary(MODE_BWD, DT, D, a.q, a.dout, a.sb, a.sh, a.sn, a.B, a.H, a.N, a.P, a.Tw,
                        a.stash, a.part, a.stream);
     if (e != hipSuccess) return e;
-    e = launch_combine(a.part, a.P, a.dS64, a.dz64, a.dimg, DT, BH, D, PART_SUMMARY, a.stream);
+    e = launch_combine(a.part, a.P, a.dS64, a.dz64, a.dimg, DT, BH, D, IMG_T | IMG_N, a.stream);
   }
   if (e != hipSuccess) return e;
   // both dS images fit in LDS except fp32 at d = 128 (2 x 64 KB): two passes
@@ -1109,7 +1113,7 @@ static hipError_t launch_rows(const BwdArgs& a) {
 
 template <int D>
 static hipError_t launch_backward_d(const BwdArgs& a) {
-  hipError_t e = launch_images(a.S64, a.z64, a.img, a.in_dt, a.B * a.H, D, a.stream);
+  hipError_t e = launch_images(a.S64, a.z64, a.img, a.in_dt, a.B * a.H, D, IMG_Z | IMG_N | IMG_LO, a.stream);
   if (e != hipSuccess) return e;
   if (a.in_dt == DT_BF16 && a.out_dt == DT_BF16) return launch_rows<DT_BF16, DT_BF16, D>(a);
   if (a.in_dt == DT_BF16) return launch_rows<DT_BF16, DT_FP32, D>(a);

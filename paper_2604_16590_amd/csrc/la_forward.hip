@@ -179,12 +179,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SummaryCfg<
 #pragma unroll
       for (int t = 0; t < RT; ++t) red[wave][t][lane] = acc[(r0 + t) / F][(r0 + t) % F];
       __syncthreads();
-      for (int t = wave; t < RT; t += 4) {
-        f32x4 s;
+      // wave w takes rows 4g + w of the round's tiles
+      for (int t = 0; t < RT; t += F) {
+        uint32_t w[F];
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          s[r] = sum4(red[0][t][lane][r], red[1][t][lane][r], red[2][t][lane][r], red[3][t][lane][r]);
-        *(f32x4*)(out + ((r0 + t) * 64 + lane) * 4) = s;
+        for (int j = 0; j < F; ++j)
+          w[j] = __float_as_uint(sum4(red[0][t + j][lane][wave], red[1][t + j][lane][wave],
+                                      red[2][t + j][lane][wave], red[3][t + j][lane][wave]));
+        store_words<4 * F>(out + (F * (4 * g + wave) + (r0 + t) / F) * D + F * m, w);
       }
     }
     if (threadIdx.x < D) {
@@ -194,14 +196,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SummaryCfg<
     return;
   }
 
-  // this wave's share of the partial: S tiles in lane order, then z
+  // this wave's share of the partial: rows of S, F consecutive values a
+  // lane, then z
 #pragma unroll
-  for (int il = 0; il < FR; ++il) {
-    const int i = FR * half + il;
+  for (int il = 0; il < FR; ++il)
 #pragma unroll
-    for (int j = 0; j < F; ++j)
-      *(f32x4*)(out + ((i * F + j) * 64 + lane) * 4) = acc[il][j];
-  }
+    for (int r = 0; r < 4; ++r) {
+      uint32_t w[F];
+#pragma unroll
+      for (int j = 0; j < F; ++j) w[j] = __float_as_uint(acc[il][j][r]);
+      store_words<4 * F>(out + (F * (4 * g + r) + FR * half + il) * D + F * m, w);
+    }
 #pragma unroll
   for (int il = 0; il < FR; ++il) {
     const float zs = sum_groups(zacc[il]);
@@ -210,74 +215,87 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SummaryCfg<
 }
 
 // ---------------------------------------------------------------------------
-// Combine: FP64 sum of the P per-wave partials in a fixed order (so
-// results are bitwise reproducible), writing the dense FP64 matrix M
-// (S or dS) and vector (z or dz), plus the matrix-core operand images.
+// Combine: FP64 sum of the P partials in a fixed order (so results are
+// bitwise reproducible), writing the dense FP64 matrix M (S or dS) and
+// vector (z or dz) and the matrix-core operands `what` asks for.
+//
+// A workgroup takes eight rows of M: four slices of 2 D threads, slice w
+// summing quarter w of the partials, four columns a thread, and the quarters
+// added as (q0 + q1) + (q2 + q3).  Eight rows by D columns are whole 16-byte
+// words of both images (eight contraction indices each), so every store is
+// one: the halfword stores this replaces took most of the time (1,024 heads
+// of 4 partials at d = 64: 94 -> 37 us; 64 heads of 8: 14 -> 7.5 us).  The
+// last workgroup of a head does the same for the vector.  M_IN (double):
+// M and v are given, only the operands are written.
 // ---------------------------------------------------------------------------
-// Partial layouts: PART_SUMMARY (the summary kernel's tiles: tile (i, j),
-// lane (g, n), register r holds M[F(4g + r) + i][F n + j], F = d/16) and
-// PART_BLOCKS (the fused query backward's: M[16i + 4g + r][16j + n]).
-// Block: 64 elements x 4 quarters of the partials; quarter w sums its
-// partials in order, and the four quarter sums are added as
-// (w0 + w1) + (w2 + w3) -- a fixed order for a given P, so results are
-// bitwise reproducible.
-template <int D, int LAYOUT>
-__global__ __launch_bounds__(256) void combine_kernel(
-    const float* __restrict__ part, int P, double* __restrict__ M64,
-    double* __restrict__ v64, void* __restrict__ img, int img_dt) {
-  constexpr int F = D / 16;
-  constexpr int E = D * D + D;
-  __shared__ double qs[4][64];
-  const int bh = blockIdx.y;
-  const int e64 = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int u = blockIdx.x * 64 + e64;
-  const int pq = (P + 3) / 4;
-  const int p0 = min(P, w * pq), p1 = min(P, p0 + pq);
-  double sq = 0.0;
-  if (u < E) {
-    // in order (the sum's order is fixed), but eight loads at a time in
-    // flight rather than one
-    const float* src = part + (int64_t)bh * P * E + u;
-    int p = p0;
-    for (; p + 8 <= p1; p += 8) {
-      float x[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) x[k] = src[(int64_t)(p + k) * E];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) sq += (double)x[k];
-    }
-    for (; p < p1; ++p) sq += (double)src[(int64_t)p * E];
-  }
-  qs[w][e64] = sq;
-  __syncthreads();
-  if (w != 0 || u >= E) return;
-  const double s = (qs[0][e64] + qs[1][e64]) + (qs[2][e64] + qs[3][e64]);
-  if (u < D * D) {
-    const int r = u & 3, lane = (u >> 2) & 63, ij = u >> 8;
-    const int i = ij / F, j = ij % F;
-    const int g = lane >> 4, n = lane & 15;
-    const int c = LAYOUT == PART_SUMMARY ? F * (4 * g + r) + i : 16 * i + 4 * g + r;
-    const int e = LAYOUT == PART_SUMMARY ? F * n + j : 16 * j + n;
-    M64[(int64_t)bh * D * D + c * D + e] = s;
-    write_images<D>(img, img_dt, bh, c, e, s);
+template <int D, int IDT, typename T>
+__global__ __launch_bounds__(8 * D) void combine_kernel(
+    const T* __restrict__ msrc, const T* __restrict__ vsrc, int64_t mstride, int64_t vstride, int P,
+    double* __restrict__ M64, double* __restrict__ v64, void* __restrict__ img, int what) {
+  using IC = ImageCfg<D>;
+  constexpr bool GIVEN = sizeof(T) == 8;
+  __shared__ double qs[GIVEN ? 1 : 4][8][D];
+  __shared__ double sum[8][D];
+  const int bh = blockIdx.y, t = threadIdx.x;
+  const bool vec = blockIdx.x == D / 8;
+  const int rows = vec ? 1 : 8, row0 = 8 * blockIdx.x;
+  const T* src = vec ? vsrc + (int64_t)bh * P * vstride
+                     : msrc + (int64_t)bh * P * mstride + (int64_t)row0 * D;
+  const int64_t stride = vec ? vstride : mstride;
+  if constexpr (GIVEN) {
+    for (int u = t; u < rows * D; u += 8 * D) (&sum[0][0])[u] = src[u];
   } else {
-    v64[(int64_t)bh * D + (u - D * D)] = s;
-    write_z_tile<D>(img, img_dt, bh, u - D * D, s);
+    // slice w, element quad u of the rows; eight loads at a time in flight
+    // (the last repeated past the end), added in order
+    const int w = t / (2 * D), u = 4 * (t % (2 * D));
+    const int pq = (P + 3) / 4, p0 = min(P, w * pq), p1 = min(P, p0 + pq);
+    if (u < rows * D) {
+      double q[4] = {0.0, 0.0, 0.0, 0.0};
+      for (int p = p0; p < p1; p += 8) {
+        f32x4 x[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) x[k] = *(const f32x4*)(src + (int64_t)min(p + k, p1 - 1) * stride + u);
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) q[r] += p + k < p1 ? (double)x[k][r] : 0.0;
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) (&qs[w][0][0])[u + r] = q[r];
+    }
+    __syncthreads();
+    if (t < rows * D) {
+      const double s = ((&qs[0][0][0])[t] + (&qs[1][0][0])[t]) + ((&qs[2][0][0])[t] + (&qs[3][0][0])[t]);
+      (&sum[0][0])[t] = s;
+      if (vec) v64[(int64_t)bh * D + t] = s;
+      else M64[((int64_t)bh * D + row0) * D + t] = s;
+    }
   }
-}
-
-// Images from a dense FP64 matrix and vector (used when S, z come from the
-// caller).
-template <int D>
-__global__ __launch_bounds__(256) void image_kernel(const double* __restrict__ M64,
-                                                    const double* __restrict__ v64,
-                                                    void* __restrict__ img, int img_dt) {
-  const int bh = blockIdx.y;
-  const int u = blockIdx.x * 256 + threadIdx.x;
-  if (u < D * D) {
-    write_images<D>(img, img_dt, bh, u / D, u % D, M64[(int64_t)bh * D * D + u]);
-  } else if (u < D * D + D) {
-    write_z_tile<D>(img, img_dt, bh, u - D * D, v64[(int64_t)bh * D + (u - D * D)]);
+  __syncthreads();
+  char* head = (char*)img + (int64_t)bh * IC::head_bytes(IDT);
+  const bool lo = what & IMG_LO;
+  int i, m;
+  if (vec) {
+    // the z tile: v in each of its 16 rows
+    if ((what & IMG_Z) && t < 2 * D) {
+      const int c0 = 8 * (t >> 4);
+      put_image8<D, IDT>(head, IC::NT, t & 15, c0, &sum[0][c0], lo);
+    }
+    return;
+  }
+  // T image: row e, contraction over the eight rows here
+  if ((what & IMG_T) && t < D) {
+    double x[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x[k] = sum[k][t];
+    image_row<D, IDT>(t, i, m);
+    put_image8<D, IDT>(head, i, m, row0, x, lo);
+  }
+  // N image: row row0 + r, contraction over the columns
+  if ((what & IMG_N) && t >= 7 * D) {
+    const int u = t - 7 * D, r = u & 7, e0 = 8 * (u >> 3);
+    image_row<D, IDT>(row0 + r, i, m);
+    put_image8<D, IDT>(head + IC::img_bytes(IDT), i, m, e0, &sum[r][e0], lo);
   }
 }
 
@@ -570,22 +588,23 @@ hipError_t launch_summary(int mode, int dt, int D, const void* k, const void* v,
 
 template <int D>
 static void launch_combine_d(const float* part, int P, double* M64, double* v64, void* img,
-                             int img_dt, int64_t BH, int layout, hipStream_t stream) {
-  dim3 grid((D * D + D + 63) / 64, (unsigned)BH);
-  if (layout == PART_SUMMARY)
-    combine_kernel<D, PART_SUMMARY><<<grid, 256, 0, stream>>>(part, P, M64, v64, img, img_dt);
+                             int img_dt, int64_t BH, int what, hipStream_t stream) {
+  const dim3 grid(D / 8 + 1, (unsigned)BH);
+  constexpr int E = D * D + D;
+  if (img_dt == DT_BF16)
+    combine_kernel<D, DT_BF16, float><<<grid, 8 * D, 0, stream>>>(part, part + D * D, E, E, P, M64, v64, img, what);
   else
-    combine_kernel<D, PART_BLOCKS><<<grid, 256, 0, stream>>>(part, P, M64, v64, img, img_dt);
+    combine_kernel<D, DT_FP32, float><<<grid, 8 * D, 0, stream>>>(part, part + D * D, E, E, P, M64, v64, img, what);
 }
 
 hipError_t launch_combine(const float* part, int P, double* M64, double* v64, void* img,
-                          int img_dt, int64_t BH, int D, int layout, hipStream_t stream) {
+                          int img_dt, int64_t BH, int D, int what, hipStream_t stream) {
   ProfScope prof("combine", stream);
   switch (D) {
-    case 16: launch_combine_d<16>(part, P, M64, v64, img, img_dt, BH, layout, stream); break;
-    case 32: launch_combine_d<32>(part, P, M64, v64, img, img_dt, BH, layout, stream); break;
-    case 64: launch_combine_d<64>(part, P, M64, v64, img, img_dt, BH, layout, stream); break;
-    case 128: launch_combine_d<128>(part, P, M64, v64, img, img_dt, BH, layout, stream); break;
+    case 16: launch_combine_d<16>(part, P, M64, v64, img, img_dt, BH, what, stream); break;
+    case 32: launch_combine_d<32>(part, P, M64, v64, img, img_dt, BH, what, stream); break;
+    case 64: launch_combine_d<64>(part, P, M64, v64, img, img_dt, BH, what, stream); break;
+    case 128: launch_combine_d<128>(part, P, M64, v64, img, img_dt, BH, what, stream); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -600,10 +619,8 @@ static hipError_t launch_forward_d(const FwdArgs& a) {
   launch_summary_d<D>(MODE_FWD, a.in_dt, a.k, a.v, a.sb, a.sh, a.sn, a.B, a.H, a.N, a.P, a.Tw,
                       nullptr, a.part, a.stream);
   {
-    dim3 cgrid((D * D + D + 63) / 64, BH);
     ProfScope prof("combine", a.stream);
-    combine_kernel<D, PART_SUMMARY><<<cgrid, 256, 0, a.stream>>>(a.part, a.P, a.S64, a.z64, a.img,
-                                                                 a.in_dt);
+    launch_combine_d<D>(a.part, a.P, a.S64, a.z64, a.img, a.in_dt, BH, IMG_T | IMG_Z | IMG_LO, a.stream);
   }
   return launch_apply_only<D>(a);
 }
@@ -643,7 +660,7 @@ hipError_t launch_forward(const FwdArgs& a) {
 }
 
 hipError_t launch_apply(const FwdArgs& a) {
-  hipError_t e = launch_images(a.S64, a.z64, a.img, a.in_dt, a.B * a.H, a.D, a.stream);
+  hipError_t e = launch_images(a.S64, a.z64, a.img, a.in_dt, a.B * a.H, a.D, IMG_T | IMG_Z | IMG_LO, a.stream);
   if (e != hipSuccess) return e;
   switch (a.D) {
     case 16: return launch_apply_only<16>(a);
@@ -654,15 +671,24 @@ hipError_t launch_apply(const FwdArgs& a) {
   return hipErrorInvalidValue;
 }
 
+template <int D>
+static void launch_images_d(const double* M64, const double* v64, void* img, int img_dt, int64_t BH,
+                            int what, hipStream_t stream) {
+  const dim3 grid(D / 8 + 1, (unsigned)BH);
+  if (img_dt == DT_BF16)
+    combine_kernel<D, DT_BF16, double><<<grid, 8 * D, 0, stream>>>(M64, v64, D * D, D, 1, nullptr, nullptr, img, what);
+  else
+    combine_kernel<D, DT_FP32, double><<<grid, 8 * D, 0, stream>>>(M64, v64, D * D, D, 1, nullptr, nullptr, img, what);
+}
+
 hipError_t launch_images(const double* M64, const double* v64, void* img, int img_dt, int64_t BH,
-                         int D, hipStream_t stream) {
-  dim3 grid((D * D + D + 255) / 256, (unsigned)BH);
+                         int D, int what, hipStream_t stream) {
   ProfScope prof("images", stream);
   switch (D) {
-    case 16: image_kernel<16><<<grid, 256, 0, stream>>>(M64, v64, img, img_dt); break;
-    case 32: image_kernel<32><<<grid, 256, 0, stream>>>(M64, v64, img, img_dt); break;
-    case 64: image_kernel<64><<<grid, 256, 0, stream>>>(M64, v64, img, img_dt); break;
-    case 128: image_kernel<128><<<grid, 256, 0, stream>>>(M64, v64, img, img_dt); break;
+    case 16: launch_images_d<16>(M64, v64, img, img_dt, BH, what, stream); break;
+    case 32: launch_images_d<32>(M64, v64, img, img_dt, BH, what, stream); break;
+    case 64: launch_images_d<64>(M64, v64, img, img_dt, BH, what, stream); break;
+    case 128: launch_images_d<128>(M64, v64, img, img_dt, BH, what, stream); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

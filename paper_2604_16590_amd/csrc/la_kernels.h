@@ -100,83 +100,51 @@ struct ImageCfg {
   static constexpr int head_bytes(int dt) { return img_bytes(dt) + mat_bytes(dt); }
 };
 
-// (word, slot) of element (tile i, row m, contraction index k).
-template <int D>
-__device__ __forceinline__ void tile_slot(int i, int m, int k, int& word, int& slot, int dt) {
+// Which operands of a matrix a combine writes.
+enum {
+  IMG_T = 1,   // T image
+  IMG_Z = 2,   // its z tile
+  IMG_N = 4,   // N image
+  IMG_LO = 8   // the bf16 lo parts of these
+};
+
+// Store x[0..8) = the row of 16-row tile i, row m, at contraction indices
+// k0 .. k0 + 7 (k0 a multiple of 8), as bf16 hi (and, with `lo`, lo) parts
+// or fp32: whole 16-byte words, one per chunk of the lane runs.
+template <int D, int DT>
+__device__ __forceinline__ void put_image8(char* base, int i, int m, int k0, const double* x, bool lo) {
+  using R = Run<D, DT>;
   using IC = ImageCfg<D>;
-  constexpr int Q4 = IC::Q4;
-  if (dt == DT_BF16) {
-    using R = Run<D, DT_BF16>;
-    const int krem = R::pos(k);
-    const int lane = 16 * R::group(k) + m;
-    const int s = krem >> 3;
-    slot = krem & 7;
-    word = ((i * IC::NS + s) * 2) * 64 + lane;  // hi part; lo part is +64
-  } else {
-    using R = Run<D, DT_FP32>;
-    const int krem = R::pos(k);
-    const int lane = 16 * R::group(k) + m;
-    slot = krem & 3;
-    word = (i * (Q4 / 4) + (krem >> 2)) * 64 + lane;
-  }
-}
-
-template <int D>
-__device__ __forceinline__ void image_slot(int row, int k, int& word, int& slot, int dt) {
-  int gq, rrem;
-  if (dt == DT_BF16) {
-    gq = Run<D, DT_BF16>::group(row);
-    rrem = Run<D, DT_BF16>::pos(row);
-  } else {
-    gq = Run<D, DT_FP32>::group(row);
-    rrem = Run<D, DT_FP32>::pos(row);
-  }
-  tile_slot<D>(rrem >> 2, 4 * gq + (rrem & 3), k, word, slot, dt);
-}
-
-// Store val (FP64) at (word, slot) of an image: hi/lo bf16 parts or fp32.
-template <int D>
-__device__ __forceinline__ void put_image(char* base, int word, int slot, int dt, double val) {
-  if (dt == DT_BF16) {
-    const uint16_t hi = to_bf16((float)val);
-    const uint16_t lo = to_bf16((float)(val - (double)bf16f(hi)));
-    uint16_t* wh = (uint16_t*)(base + (int64_t)word * 16);
-    uint16_t* wl = (uint16_t*)(base + (int64_t)(word + 64) * 16);
-    wh[slot] = hi;
-    wl[slot] = lo;
-    if (ImageCfg<D>::Q4 < 8) {  // d = 16: slots 4..7 of each k-step are padding
-      wh[slot + 4] = 0;
-      wl[slot + 4] = 0;
+  u32x4* img = (u32x4*)base;
+#pragma unroll
+  for (int c0 = 0; c0 < 8; c0 += R::CH) {
+    const int lane = 16 * R::group(k0 + c0) + m, pos = R::pos(k0 + c0);
+    if constexpr (DT == DT_BF16) {
+      u32x4 h = u32x4{0, 0, 0, 0}, l = u32x4{0, 0, 0, 0};  // d = 16: slots 4..7 are padding
+#pragma unroll
+      for (int j = 0; j < R::CH; j += 2) {
+        const double a = x[c0 + j], b = x[c0 + j + 1];
+        h[j >> 1] = pack_bf16((float)a, (float)b);
+        l[j >> 1] = pack_bf16((float)(a - (double)bf16lo(h[j >> 1])), (float)(b - (double)bf16hi(h[j >> 1])));
+      }
+      const int word = ((i * IC::NS + (pos >> 3)) * 2) * 64 + lane;
+      img[word] = h;
+      if (lo) img[word + 64] = l;
+    } else {
+      const int word = (i * (IC::Q4 / 4) + (pos >> 2)) * 64 + lane;
+      img[word] = u32x4{__float_as_uint((float)x[c0]), __float_as_uint((float)x[c0 + 1]),
+                        __float_as_uint((float)x[c0 + 2]), __float_as_uint((float)x[c0 + 3])};
     }
-  } else {
-    ((float*)(base + (int64_t)word * 16))[slot] = (float)val;
   }
 }
 
-// Store M[c][e] = val into both images of head bh.
-template <int D>
-__device__ __forceinline__ void write_images(void* img, int dt, int bh, int c, int e, double val) {
-  using IC = ImageCfg<D>;
-  char* head = (char*)img + (int64_t)bh * IC::head_bytes(dt);
-  for (int which = 0; which < 2; ++which) {
-    const int row = which == 0 ? e : c;
-    const int k = which == 0 ? c : e;
-    int word, slot;
-    image_slot<D>(row, k, word, slot, dt);
-    put_image<D>(head + which * IC::img_bytes(dt), word, slot, dt, val);
-  }
-}
-
-// Store v[c] = val into all 16 rows of the T image's z tile of head bh.
-template <int D>
-__device__ __forceinline__ void write_z_tile(void* img, int dt, int bh, int c, double val) {
-  using IC = ImageCfg<D>;
-  char* head = (char*)img + (int64_t)bh * IC::head_bytes(dt);
-  for (int m = 0; m < 16; ++m) {
-    int word, slot;
-    tile_slot<D>(IC::NT, m, c, word, slot, dt);
-    put_image<D>(head, word, slot, dt, val);
-  }
+// (16-row tile, row of it) of matrix row `row`.
+template <int D, int DT>
+__device__ __forceinline__ void image_row(int row, int& i, int& m) {
+  using R = Run<D, DT>;
+  const int pos = R::pos(row);
+  i = pos >> 2;
+  m = 4 * R::group(row) + (pos & 3);
 }
 
 struct FwdArgs {
@@ -187,7 +155,7 @@ struct FwdArgs {
   void* o;
   int P, Tw;           // partials per head, tokens per partial
   int Ga;              // apply workgroups per head (they take its token blocks in turn)
-  float* part;         // [BH][P][D*D + D]
+  float* part;         // [BH][P][D*D + D]: S rows, then z
   double* S64;         // [BH][D][D]
   double* z64;         // [BH][D]
   void* img;           // [BH][2 images]
@@ -218,7 +186,6 @@ struct BwdArgs {
 };
 
 enum { MODE_FWD = 0, MODE_BWD = 1 };
-enum { PART_SUMMARY = 0, PART_BLOCKS = 1 };  // layouts of per-wave partial sums
 
 // Keeps a failed hipError_t for la_last_hip_error(); returns LA_ERR_HIP.
 int32_t record_hip_error(int32_t e);
@@ -231,11 +198,13 @@ hipError_t launch_apply(const FwdArgs& a);
 hipError_t launch_summary(int mode, int dt, int D, const void* k, const void* v, int64_t sb,
                           int64_t sh, int64_t sn, int64_t B, int64_t H, int64_t N, int P,
                           int Tw, const float2* stash, float* part, hipStream_t stream);
+// FP64 sum of the P partials [D][D], [D] of each head, and the operands
+// `what` (IMG_*) of the result.
 hipError_t launch_combine(const float* part, int P, double* M64, double* v64, void* img,
-                          int img_dt, int64_t BH, int D, int layout, hipStream_t stream);
+                          int img_dt, int64_t BH, int D, int what, hipStream_t stream);
 hipError_t launch_backward(const BwdArgs& a);
-// Images (both, with the z tile) of a given M and v.
+// The operands `what` of a given M and v.
 hipError_t launch_images(const double* M64, const double* v64, void* img, int img_dt, int64_t BH,
-                         int D, hipStream_t stream);
+                         int D, int what, hipStream_t stream);
 
 }  // namespace la
