@@ -84,14 +84,14 @@ int64_t fused_partials(int64_t N, int d) {
 // The summary: a partial's write and read cost 2 (d + 1) * 4 bytes against
 // 2 * es bytes of K and V a token and feature, so a partial of 32 d bf16
 // tokens adds 6 % and is the rule (16 d in fp32: the same bytes).  Short
-// sequences take up to four (fp32: eight) shorter ones, not below 4 d (2 d)
+// sequences take up to four (fp32: sixteen) shorter ones, not below 4 d (2 d)
 // tokens, so that a few heads still fill compute units: one head of 4,096
-// fp32 tokens (d = 64) takes 16 us in eight partials and 26 in four, while
+// fp32 tokens (d = 64) takes 14 us in sixteen partials and 21 in eight, while
 // 1,024 heads of 8,192 bf16 tokens take 396 + 94 us (summary + combine) in
 // four and 430 + 110 in eight.
 int64_t summary_partials(int64_t N, int d, int dt) {
   const int64_t unit = dt == LA_BF16 ? 4 * d : 2 * d;
-  const int64_t few = dt == LA_BF16 ? 4 : 8;
+  const int64_t few = dt == LA_BF16 ? 4 : 16;
   return std::max(std::min(max_partials(d), ceil_div(N, 8 * unit)), std::min(few, ceil_div(N, unit)));
 }
 

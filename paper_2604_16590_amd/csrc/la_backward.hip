@@ -21,6 +21,7 @@
 
 #include "la_kernels.h"
 #include "la_profile.h"
+#include "la_split.h"
 
 namespace la {
 
@@ -362,20 +363,6 @@ struct FusedCfg {
 };
 
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
-
-// gfx950 transposing LDS read of 16-bit elements: within each 16-lane
-// block, lane i receives as element k (k = 0..3) element i & 3 of the
-// 8-byte chunk addressed by lane (i >> 2) + 4k of the block.  When lane L
-// of a block addresses token row t0 + (L >> 2), features f0 + 4 (L & 3)
-// .. + 3 of a row-major bf16 tile, lane i receives tokens t0 .. t0 + 3 of
-// feature f0 + i: a token-major matrix-core operand straight from LDS.
-__device__ __forceinline__ u32x2 lds_read_tr16(const void* p) {
-  const s16x4 r = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p));
-  return __builtin_bit_cast(u32x2, r);
-}
-
 // Wait until at most N vector memory operations of this wave are
 // outstanding; also a compiler barrier.
 template <int N>

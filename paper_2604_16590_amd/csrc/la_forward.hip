@@ -9,6 +9,7 @@
 // writes O.  The d x d contractions run on the matrix cores.
 #include "la_kernels.h"
 #include "la_profile.h"
+#include "la_split.h"
 #include "la_summary.h"
 
 namespace la {
@@ -32,12 +33,12 @@ namespace la {
 // they add exactly nothing to S or z and the step itself needs no masks.
 // In the backward mode the per-token pair (1/den, -(dO . O)) is loaded too.
 // Addresses split into a wave-uniform part (head + (t0 + r) rows, scalar
-// registers) and a loop-invariant 32-bit lane offset (koff, voff: the lane
-// group's first row and the lane's feature run), so the loads need no
-// per-lane address arithmetic.
+// registers) and a loop-invariant 32-bit lane offset (off: the lane group's
+// first row and the lane's feature run), so the loads need no per-lane
+// address arithmetic.
 template <int DT, int D, int MODE>
-__device__ __forceinline__ void summary_load(const char* kh, const char* vh, uint32_t koff,
-                                             uint32_t voff, const float2* stash,
+__device__ __forceinline__ void summary_load(const char* kh, const char* vh, uint32_t off,
+                                             const float2* stash,
                                              int64_t row_bytes, int64_t t0, int g, int m,
                                              int64_t t_end, SummaryRegs<DT, D, MODE>& x) {
   using C = SummaryCfg<DT, D, MODE>;
@@ -46,16 +47,16 @@ __device__ __forceinline__ void summary_load(const char* kh, const char* vh, uin
 #pragma unroll
     for (int r = 0; r < C::R; ++r) {
       const int64_t ur = (t0 + r) * row_bytes;
-      load_words_nt<C::KB>(kh + ur + koff, x.kw[r]);
-      load_words_nt<C::VB>(vh + ur + voff, x.vw[r]);
+      load_words_nt<C::KB>(kh + ur + off, x.kw[r]);
+      load_words_nt<C::VB>(vh + ur + off, x.vw[r]);
     }
   } else {
 #pragma unroll
     for (int r = 0; r < C::R; ++r) {
       const int64_t ur = (t0 + r) * row_bytes;
       if (t0 + C::R * g + r < t_end) {
-        load_words_nt<C::KB>(kh + ur + koff, x.kw[r]);
-        load_words_nt<C::VB>(vh + ur + voff, x.vw[r]);
+        load_words_nt<C::KB>(kh + ur + off, x.kw[r]);
+        load_words_nt<C::VB>(vh + ur + off, x.vw[r]);
       } else {
 #pragma unroll
         for (int w = 0; w < C::KW; ++w) x.kw[r][w] = neg_inf;
@@ -86,9 +87,8 @@ __device__ __forceinline__ void summary_load(const char* kh, const char* vh, uin
 // eight XCDs in turn), so the heads of one token range, which share cache
 // lines on a BNHD view at d <= 32, are read through one L2 (d = 32, 8
 // heads of 30,001 tokens: 47 -> 38 us).
-// SUM_SPLIT (fp32 at d = 128): x = partial, y = (b, h), and the block's
-// SPLIT waves share partial x, wave w owning S tile rows [FR*w, +FR).
-enum { SUM_WAVE = 0, SUM_TEAM = 1, SUM_SPLIT = 2 };
+// (fp32 inputs at d >= 32 take summary_split_kernel.)
+enum { SUM_WAVE = 0, SUM_TEAM = 1 };
 
 template <int DT, int D, int MODE, int FORM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SummaryCfg<DT, D, MODE>::WAVES_PER_SIMD))) void summary_kernel(
@@ -96,50 +96,42 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SummaryCfg<
     int64_t sh, int64_t sn, int H, int64_t N, int P, int Tw,
     const float2* __restrict__ stash, float* __restrict__ part, int BH) {
   using C = SummaryCfg<DT, D, MODE>;
-  constexpr int F = C::F, FR = C::FR;
+  constexpr int F = C::F;
   constexpr int E = D * D + D;
   const int lane = threadIdx.x & 63, wave = wave_index();
   const int g = lane >> 4, m = lane & 15;
-  static_assert((FORM == SUM_SPLIT) == (C::SPLIT > 1), "form of the configuration");
   int64_t item = (int64_t)blockIdx.x * 4 + wave;
   if constexpr (FORM == SUM_TEAM)
     item = (int64_t)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-  const int p = FORM == SUM_SPLIT ? (int)blockIdx.x : (int)(item / BH);
-  const int half = FORM == SUM_SPLIT ? wave : 0;
+  const int p = (int)(item / BH);
   if (p >= P) return;  // uniform across the waves that share p
-  const int bh = FORM == SUM_SPLIT ? (int)blockIdx.y : (int)(item % BH);
+  const int bh = (int)(item % BH);
   const int64_t b = bh / H, h = bh % H;
   const int64_t t_begin = (int64_t)p * Tw;
   const int64_t t_end = min(N, t_begin + (int64_t)Tw);
   const int64_t head = (b * sb + h * sh) * C::ES;
-  // lane m reads key features [F*m + FR*half, +FR) and value features
-  // [F*m + FC*half, +FC) of rows R*g + r (the host bounds 32 rows of the
-  // token stride to 2^24 bytes, so the lane offsets fit 32 bits)
+  // lane m reads features [F*m, +F) of rows R*g + r (the host bounds 32 rows
+  // of the token stride to 2^24 bytes, so the lane offset fits 32 bits)
   const int64_t row_bytes = sn * C::ES;
   const char* kh = (const char*)k + head;
   const char* vh = (const char*)v + head;
-  const uint32_t roff = (uint32_t)(C::R * g) * (uint32_t)row_bytes;
-  const uint32_t koff = roff + (uint32_t)((F * m + FR * half) * C::ES);
-  const uint32_t voff = roff + (uint32_t)((F * m + C::FC * half) * C::ES);
+  const uint32_t off = (uint32_t)(C::R * g) * (uint32_t)row_bytes + (uint32_t)(F * m * C::ES);
   const float2* tstash = MODE == MODE_BWD ? stash + (int64_t)bh * N : nullptr;
 
-  f32x4 acc[FR][F];
+  f32x4 acc[F][F];
 #pragma unroll
-  for (int i = 0; i < FR; ++i)
+  for (int i = 0; i < F; ++i)
 #pragma unroll
     for (int j = 0; j < F; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float zacc[FR];
+  float zacc[F];
 #pragma unroll
-  for (int i = 0; i < FR; ++i) zacc[i] = 0.f;
+  for (int i = 0; i < F; ++i) zacc[i] = 0.f;
 
-  // double-buffered exchange: one barrier per step suffices, because a
-  // buffer is rewritten only after the barrier of the step in between
-  __shared__ uint32_t xch[2 * C::XW];
   // two register sets in turn: while one step computes, the next one's
   // loads are in flight in the other set (no copies between them)
   SummaryRegs<DT, D, MODE> ra, rb;
   auto load = [&](int64_t t0, SummaryRegs<DT, D, MODE>& x) {
-    summary_load<DT, D, MODE>(kh, vh, koff, voff, tstash, row_bytes, t0, g, m, t_end, x);
+    summary_load<DT, D, MODE>(kh, vh, off, tstash, row_bytes, t0, g, m, t_end, x);
   };
   // a team's wave past the partial's end runs one step of masked rows,
   // which adds nothing
@@ -149,11 +141,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SummaryCfg<
   while (true) {
     const int64_t t1 = t0 + STRIDE;
     if (t1 < t_end) load(t1, rb);
-    summary_step<DT, D, MODE>(ra, half, lane, xch, acc, zacc);
+    summary_step<DT, D, MODE>(ra, acc, zacc);
     if (t1 >= t_end) break;
     const int64_t t2 = t1 + STRIDE;
     if (t2 < t_end) load(t2, ra);
-    summary_step<DT, D, MODE>(rb, half, lane, xch + C::XW, acc, zacc);
+    summary_step<DT, D, MODE>(rb, acc, zacc);
     if (t2 >= t_end) break;
     t0 = t2;
   }
@@ -199,18 +191,244 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SummaryCfg<
   // this wave's share of the partial: rows of S, F consecutive values a
   // lane, then z
 #pragma unroll
-  for (int il = 0; il < FR; ++il)
+  for (int i = 0; i < F; ++i)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       uint32_t w[F];
 #pragma unroll
-      for (int j = 0; j < F; ++j) w[j] = __float_as_uint(acc[il][j][r]);
-      store_words<4 * F>(out + (F * (4 * g + r) + FR * half + il) * D + F * m, w);
+      for (int j = 0; j < F; ++j) w[j] = __float_as_uint(acc[i][j][r]);
+      store_words<4 * F>(out + (F * (4 * g + r) + i) * D + F * m, w);
     }
 #pragma unroll
-  for (int il = 0; il < FR; ++il) {
-    const float zs = sum_groups(zacc[il]);
-    if (g == 0) out[D * D + F * m + FR * half + il] = zs;
+  for (int i = 0; i < F; ++i) {
+    const float zs = sum_groups(zacc[i]);
+    if (g == 0) out[D * D + F * m + i] = zs;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Summary of fp32 inputs at d >= 32, on the bf16 matrix cores (la_split.h).
+// A workgroup takes one partial, 4096 / d tokens a step: its threads load
+// the step's K and V rows whole (16 bytes a thread), form phi, split every
+// value into three bf16 parts and put them in LDS as rows; the transposing
+// LDS read gives the token-major operands, and each wave sums its own tiles
+// of S over all of the step's tokens, so nothing is left to add up between
+// waves.  The next step's rows are in flight while this one is computed, and
+// two (d <= 64: three) workgroups share a compute unit.  Steps that leave
+// the split's range are taken after the others by the fp32 matrix
+// instructions (in the loop, that path's addresses spilled the operands).
+//
+// What bounds it: per 32 tokens at d = 128 a SIMD has 1,536 cycles of matrix
+// products and about 1,700 of vector work (phi, split, sums) in the 2,400
+// that HBM takes; they overlap in part.  8 heads of 524,288 tokens at
+// d = 128: 0.86 ms, 5.0 TB/s (fp32 matrix instructions: 1.33); 32 heads of
+// 20,011 at d = 64: 71 us (81).
+// ---------------------------------------------------------------------------
+template <int D>
+struct SplitCfg {
+  // d = 128: eight waves, so that a wave's share of S and its operands take
+  // 128 registers and four waves fit a SIMD (0.86 ms for 8 heads of 524,288
+  // tokens; four waves of 4 x 4 tiles, two to a SIMD, 0.90)
+  static constexpr int NW = D == 128 ? 8 : 4;
+  static constexpr int QI = D == 128 ? 2 : D / 32, QJ = D / 32;  // a wave's tiles of S
+  static constexpr int WAVES_PER_SIMD = D == 128 ? 4 : 3;
+};
+
+template <int D, int MODE>
+__global__ __launch_bounds__(64 * SplitCfg<D>::NW) __attribute__((amdgpu_waves_per_eu(SplitCfg<D>::WAVES_PER_SIMD))) void summary_split_kernel(
+    const void* __restrict__ k, const void* __restrict__ v, int64_t sb, int64_t sh, int64_t sn,
+    int H, int64_t N, int P, int Tw, const float2* __restrict__ stash, float* __restrict__ part,
+    int BH) {
+  constexpr int E = D * D + D;
+  constexpr int TPS = 4096 / D;       // tokens per step
+  constexpr int RP = SplitCfg<D>::NW * 256 / D;  // rows per pass of the workgroup's loads
+  constexpr int NP = TPS / RP;        // passes
+  constexpr int QI = SplitCfg<D>::QI, QJ = SplitCfg<D>::QJ;
+  constexpr int TILE = TPS * D * 2;   // LDS bytes of one part of one tensor
+  __shared__ __align__(16) char buf[2][3][TILE];
+  __shared__ float zred[RP][D];
+  constexpr int STEPS = 4096 / TPS;   // at most (a partial's tokens)
+  __shared__ int out_of_range[STEPS]; // steps that left the split's range
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = wave_index();
+  const int g = lane >> 4, n = lane & 15;
+  const int64_t item = (int64_t)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  const int p = (int)(item / BH);
+  if (p >= P) return;  // uniform over the workgroup
+  const int bh = (int)(item % BH);
+  const int64_t head = ((int64_t)(bh / H) * sb + (int64_t)(bh % H) * sh) * 4;
+  const char* kh = (const char*)k + head;
+  const char* vh = (const char*)v + head;
+  const float2* tstash = MODE == MODE_BWD ? stash + (int64_t)bh * N : nullptr;
+  const int64_t t_begin = (int64_t)p * Tw, t_end = min(N, t_begin + (int64_t)Tw);
+  const int64_t row_bytes = sn * 4;
+  if (tid < STEPS) out_of_range[tid] = 0;
+
+  // this thread's part of a pass: row r0, features [4 * c4, +4)
+  const int c4 = tid % (D / 4), r0 = tid / (D / 4);
+  // LDS rows: 16-byte chunks XOR-swizzled so that the eight rows a half
+  // wave reads (32 bytes each) lie in distinct banks
+  auto swz = [](int row) { return D == 128 ? 2 * (row & 7) : D == 64 ? 2 * ((row >> 1) & 3) : 2 * ((row >> 2) & 1); };
+
+  struct Regs {
+    f32x4 k[NP], v[NP];
+    float2 st[MODE == MODE_BWD ? NP : 1];
+  };
+  auto load = [&](int64_t t0, Regs& x) {
+    // rows past the end read the last one again (masked when used); a
+    // step's row offsets fit 32 bits (128 rows of at most 2^24 bytes)
+    const int64_t tb = min(t0, t_end - 1);
+    const int last = (int)min((int64_t)(TPS - 1), t_end - 1 - tb);
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const uint32_t row = (uint32_t)min(i * RP + r0, last);
+      const uint32_t off = row * (uint32_t)row_bytes + (uint32_t)(c4 * 16);
+      x.k[i] = __builtin_nontemporal_load((const f32x4*)(kh + tb * row_bytes + off));
+      x.v[i] = __builtin_nontemporal_load((const f32x4*)(vh + tb * row_bytes + off));
+      if constexpr (MODE == MODE_BWD) x.st[i] = tstash[tb + row];
+    }
+  };
+
+  float z[4] = {0.f, 0.f, 0.f, 0.f};
+  // phi, split, LDS
+  auto stage = [&](int64_t t0, Regs& x, int step) {
+    SplitRange kr, vr;
+    if (t0 + TPS > t_end) {  // uniform: rows past the end add nothing
+#pragma unroll
+      for (int i = 0; i < NP; ++i)
+        if (t0 + i * RP + r0 >= t_end) {
+          const float ninf = -__builtin_inff();  // phi = 0
+          x.k[i] = f32x4{ninf, ninf, ninf, ninf};
+          x.v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+          if constexpr (MODE == MODE_BWD) x.st[i] = float2{0.f, 0.f};
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int row = i * RP + r0;
+      float a[4], b[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        a[c] = phi<DT_FP32>(x.k[i][c]);
+        b[c] = x.v[i][c];
+        if constexpr (MODE == MODE_BWD) a[c] *= x.st[i].x;
+      }
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        if constexpr (MODE == MODE_BWD) z[c] = fmaf(x.st[i].y, a[c], z[c]);
+        else z[c] += a[c];
+      }
+      kr.see(a[0], a[1]);
+      kr.see(a[2], a[3]);
+      vr.see(b[0], b[1]);
+      vr.see(b[2], b[3]);
+      const int at = row * (2 * D) + (((c4 >> 1) ^ swz(row)) * 16) + (c4 & 1) * 8;
+      const Split2 a0 = split2(a[0], a[1]), a1 = split2(a[2], a[3]);
+      const Split2 b0 = split2(b[0], b[1]), b1 = split2(b[2], b[3]);
+      *(u32x2*)(buf[0][0] + at) = u32x2{a0.h, a1.h};
+      *(u32x2*)(buf[0][1] + at) = u32x2{a0.m, a1.m};
+      *(u32x2*)(buf[0][2] + at) = u32x2{a0.l, a1.l};
+      *(u32x2*)(buf[1][0] + at) = u32x2{b0.h, b1.h};
+      *(u32x2*)(buf[1][1] + at) = u32x2{b0.m, b1.m};
+      *(u32x2*)(buf[1][2] + at) = u32x2{b0.l, b1.l};
+    }
+    if (kr.bad() || vr.bad()) out_of_range[step] = 1;  // every writer stores the same
+  };
+
+  // wave w sums the tiles of rows [16 i0, +16 QI) and columns [16 j0, +16 QJ)
+  const int i0 = QI * (wave >> 1), j0 = QJ * (wave & 1);
+  f32x4 acc[QI][QJ];
+#pragma unroll
+  for (int i = 0; i < QI; ++i)
+#pragma unroll
+    for (int j = 0; j < QJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  // operand of feature block f: lane (g, n) addresses row 4g + (n >> 2) of
+  // each 16-row half of a 32-token step, features 16f + 4 (n & 3) .. + 3
+  const int rrow = 4 * g + (n >> 2);
+  auto operand = [&](int tensor, int ks, int f) {
+    const int at = (32 * ks + rrow) * (2 * D) + ((2 * f + ((n & 3) >> 1)) ^ swz(rrow)) * 16 + (n & 1) * 8;
+    Bf16x3 r;
+    bf16x8* o[3] = {&r.h, &r.m, &r.l};
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const u32x2 lo = lds_read_tr16(buf[tensor][q] + at);
+      const u32x2 hi = lds_read_tr16(buf[tensor][q] + at + 16 * 2 * D);
+      *o[q] = as_bf16x8(u32x4{lo[0], lo[1], hi[0], hi[1]});
+    }
+    return r;
+  };
+  auto compute = [&]() {
+#pragma unroll
+    for (int ks = 0; ks < TPS / 32; ++ks) {
+      Bf16x3 a[QI];
+#pragma unroll
+      for (int i = 0; i < QI; ++i) a[i] = operand(0, ks, i0 + i);
+#pragma unroll
+      for (int j = 0; j < QJ; ++j) {
+        const Bf16x3 b = operand(1, ks, j0 + j);
+#pragma unroll
+        for (int i = 0; i < QI; ++i) mfma_split(a[i], b, acc[i][j]);
+        __builtin_amdgcn_sched_barrier(0);  // bounded registers
+      }
+    }
+  };
+  // a step out of the split's range: the fp32 matrix instructions, with
+  // operands read again from memory (four tokens a product)
+  auto compute_fp32 = [&](int64_t t0) {
+    for (int tt = 0; tt < TPS; tt += 4) {
+      const int64_t t = t0 + tt + g;
+      const bool ok = t < t_end;
+      const int64_t at = min(t, t_end - 1) * row_bytes + n * 4;
+      float a[QI], b[QJ];
+#pragma unroll
+      for (int i = 0; i < QI; ++i) {
+        const float x = *(const float*)(kh + at + 64 * (i0 + i));
+        a[i] = ok ? phi<DT_FP32>(x) : 0.f;
+        if constexpr (MODE == MODE_BWD) a[i] *= tstash[min(t, t_end - 1)].x;
+      }
+#pragma unroll
+      for (int j = 0; j < QJ; ++j) {
+        const float y = *(const float*)(vh + at + 64 * (j0 + j));
+        b[j] = ok ? y : 0.f;
+      }
+#pragma unroll
+      for (int i = 0; i < QI; ++i)
+#pragma unroll
+        for (int j = 0; j < QJ; ++j) acc[i][j] = mfma_f32(a[i], b[j], acc[i][j]);
+    }
+  };
+
+  Regs x;
+  load(t_begin, x);
+  __syncthreads();  // out_of_range is set
+  const int steps = (int)((t_end - t_begin + TPS - 1) / TPS);
+  for (int s = 0; s < steps; ++s) {
+    const int64_t t0 = t_begin + s * TPS;
+    stage(t0, x, s);
+    load(t0 + TPS, x);
+    __syncthreads();
+    if (!out_of_range[s]) compute();
+    __syncthreads();  // before the rows are written again
+  }
+  for (int s = 0; s < steps; ++s)
+    if (out_of_range[s]) compute_fp32(t_begin + s * TPS);
+
+  float* out = part + ((int64_t)bh * P + p) * E;
+#pragma unroll
+  for (int i = 0; i < QI; ++i)
+#pragma unroll
+    for (int j = 0; j < QJ; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        out[(16 * (i0 + i) + 4 * g + r) * D + 16 * (j0 + j) + n] = acc[i][j][r];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) zred[r0][4 * c4 + c] = z[c];
+  __syncthreads();
+  if (tid < D) {
+    double s = 0.0;
+    for (int r = 0; r < RP; ++r) s += (double)zred[r][tid];
+    out[D * D + tid] = (float)s;
   }
 }
 
@@ -545,8 +763,8 @@ static void launch_summary_t(const void* k, const void* v, int64_t sb, int64_t s
                              int64_t BH, int64_t H, int64_t N, int P, int Tw,
                              const float2* stash, float* part, hipStream_t stream) {
   using C = SummaryCfg<DT, D, MODE>;
-  if constexpr (C::SPLIT > 1) {
-    summary_kernel<DT, D, MODE, SUM_SPLIT><<<dim3((unsigned)P, (unsigned)BH), C::THREADS, 0, stream>>>(
+  if constexpr (DT == DT_FP32 && D >= 32) {
+    summary_split_kernel<D, MODE><<<dim3((unsigned)((P * BH + 7) / 8 * 8)), 64 * SplitCfg<D>::NW, 0, stream>>>(
         k, v, sb, sh, sn, (int)H, N, P, Tw, stash, part, (int)BH);
   } else if (Tw <= kTeamTokens) {
     summary_kernel<DT, D, MODE, SUM_TEAM><<<dim3((unsigned)((P * BH + 7) / 8 * 8)), 256, 0, stream>>>(

@@ -16,27 +16,16 @@ namespace la {
 template <int DT, int D, int MODE = MODE_FWD>
 struct SummaryCfg {
   static constexpr int F = D / 16;                 // features per lane (S tile grid is F x F)
-  // waves sharing one token range; each owns F/SPLIT rows of S tiles and
-  // loads F/SPLIT of the value features, whose matrix-core operands it
-  // shares with the others through LDS, so K and V are each read once.
-  // bf16 at d = 128 keeps the whole S (256 accumulator registers) in one
-  // wave, in the accumulation registers, at one wave per SIMD; fp32 there
-  // needs more registers for its operands and splits in two.
-  static constexpr int SPLIT = D >= 128 && DT == DT_FP32 ? 2 : 1;
-  static constexpr int WAVES_PER_SIMD = D >= 128 && DT == DT_BF16 ? 1 : 2;
-  static constexpr int FR = F / SPLIT;             // S tile rows (key features) per wave
-  static constexpr int FC = F / SPLIT;             // value features loaded per wave
+  // a wave holds a whole S; bf16 at d = 128 (256 accumulator registers) in
+  // the accumulation registers, at one wave per SIMD
+  static constexpr int WAVES_PER_SIMD = D >= 128 ? 1 : 2;
   static constexpr int ES = DT == DT_BF16 ? 2 : 4;
-  static constexpr int KB = FR * ES;               // key bytes per lane per token
-  static constexpr int VB = FC * ES;               // value bytes per lane per token
+  static constexpr int KB = F * ES;                // key bytes per lane per token
+  static constexpr int VB = KB;                    // value bytes per lane per token
   static constexpr int KW = KB >= 4 ? KB / 4 : 1;
   static constexpr int VW = VB >= 4 ? VB / 4 : 1;
   static constexpr int R = DT == DT_BF16 ? 8 : 4;  // tokens per lane group per step
   static constexpr int STEP = 4 * R;               // tokens per wave per step
-  static constexpr int THREADS = SPLIT > 1 ? 64 * SPLIT : 256;
-  // LDS words exchanged per buffer: bf16 -> F operands x 4 words x 64 lanes;
-  // fp32 -> R tokens x F values x 64 lanes
-  static constexpr int XW = SPLIT > 1 ? (DT == DT_BF16 ? F * 4 * 64 : R * F * 64) : 1;
 };
 
 template <int DT, int D, int MODE>
@@ -73,36 +62,26 @@ __device__ __forceinline__ float2 group_bcast(float2 v, int r) {
 // which accumulates dS = sum phi(q) (dO / den)^T and dz = sum dden phi(q)
 // (dden = -(dO . O) / den) of the backward pass; the per-token pair
 // (1/den, -(dO . O)) comes from the query kernel.
-// `xch` is this step's LDS exchange buffer (SPLIT > 1).
 template <int DT, int D, int MODE>
-__device__ __forceinline__ void summary_step(const SummaryRegs<DT, D, MODE>& x, int part, int lane,
-                                             uint32_t* xch,
-                                             f32x4 (&acc)[SummaryCfg<DT, D, MODE>::FR][SummaryCfg<DT, D, MODE>::F],
-                                             float (&zacc)[SummaryCfg<DT, D, MODE>::FR]) {
+__device__ __forceinline__ void summary_step(const SummaryRegs<DT, D, MODE>& x,
+                                             f32x4 (&acc)[D / 16][D / 16], float (&zacc)[D / 16]) {
   using C = SummaryCfg<DT, D, MODE>;
-  constexpr int F = C::F, FR = C::FR, FC = C::FC;
+  constexpr int F = C::F;
   if constexpr (DT == DT_BF16) {
-    // value operands of this wave's features: token pairs of one feature
+    // value operands: token pairs of one feature
     // packed into words
-    uint32_t own[FC][4];
+    uint32_t own[F][4];
 #pragma unroll
-    for (int jj = 0; jj < FC; ++jj)
+    for (int jj = 0; jj < F; ++jj)
 #pragma unroll
       for (int pp = 0; pp < 4; ++pp) {
         const uint32_t lo = word_bits16<DT>(x.vw[2 * pp], jj);
         const uint32_t hi = word_bits16<DT>(x.vw[2 * pp + 1], jj);
         own[jj][pp] = lo | (hi << 16);
       }
-    if constexpr (C::SPLIT > 1) {
-#pragma unroll
-      for (int jj = 0; jj < FC; ++jj)
-#pragma unroll
-        for (int pp = 0; pp < 4; ++pp) xch[((part * FC + jj) * 4 + pp) * 64 + lane] = own[jj][pp];
-      __syncthreads();
-    }
-    // key operands of this wave's rows (token pair outermost, so only
+    // key operands (token pair outermost, so only
     // one pair of per-token scalars is live in the backward mode)
-    uint32_t pk[FR][4];
+    uint32_t pk[F][4];
 #pragma unroll
     for (int pp = 0; pp < 4; ++pp) {
       float2 t0 = float2{1.f, 0.f}, t1 = float2{1.f, 0.f};
@@ -111,7 +90,7 @@ __device__ __forceinline__ void summary_step(const SummaryRegs<DT, D, MODE>& x, 
         t1 = group_bcast(x.tok, 2 * pp + 1);
       }
 #pragma unroll
-      for (int i = 0; i < FR; ++i) {
+      for (int i = 0; i < F; ++i) {
         float p0 = phi<DT>(word_elem<DT>(x.kw[2 * pp], i));
         float p1 = phi<DT>(word_elem<DT>(x.kw[2 * pp + 1], i));
         if constexpr (MODE == MODE_BWD) {
@@ -128,36 +107,23 @@ __device__ __forceinline__ void summary_step(const SummaryRegs<DT, D, MODE>& x, 
         }
       }
     }
-    bf16x8 ak[FR];
+    bf16x8 ak[F];
 #pragma unroll
-    for (int i = 0; i < FR; ++i) ak[i] = as_bf16x8(u32x4{pk[i][0], pk[i][1], pk[i][2], pk[i][3]});
+    for (int i = 0; i < F; ++i) ak[i] = as_bf16x8(u32x4{pk[i][0], pk[i][1], pk[i][2], pk[i][3]});
 #pragma unroll
     for (int j = 0; j < F; ++j) {
-      bf16x8 bv;
-      if constexpr (C::SPLIT > 1) {
-        bv = as_bf16x8(u32x4{xch[(j * 4 + 0) * 64 + lane], xch[(j * 4 + 1) * 64 + lane],
-                             xch[(j * 4 + 2) * 64 + lane], xch[(j * 4 + 3) * 64 + lane]});
-      } else {
-        bv = as_bf16x8(u32x4{own[j][0], own[j][1], own[j][2], own[j][3]});
-      }
+      const bf16x8 bv = as_bf16x8(u32x4{own[j][0], own[j][1], own[j][2], own[j][3]});
 #pragma unroll
-      for (int i = 0; i < FR; ++i) acc[i][j] = mfma_bf16(ak[i], bv, acc[i][j]);
+      for (int i = 0; i < F; ++i) acc[i][j] = mfma_bf16(ak[i], bv, acc[i][j]);
     }
   } else {
-    if constexpr (C::SPLIT > 1) {
-#pragma unroll
-      for (int r = 0; r < C::R; ++r)
-#pragma unroll
-        for (int jj = 0; jj < FC; ++jj) xch[(r * F + part * FC + jj) * 64 + lane] = x.vw[r][jj];
-      __syncthreads();
-    }
 #pragma unroll
     for (int r = 0; r < C::R; ++r) {
-      float pk[FR];
+      float pk[F];
       float2 tr = float2{1.f, 0.f};
       if constexpr (MODE == MODE_BWD) tr = group_bcast(x.tok, r);
 #pragma unroll
-      for (int i = 0; i < FR; ++i) {
+      for (int i = 0; i < F; ++i) {
         pk[i] = phi<DT>(word_elem<DT>(x.kw[r], i));
         if constexpr (MODE == MODE_FWD) {
           zacc[i] += pk[i];
@@ -168,10 +134,9 @@ __device__ __forceinline__ void summary_step(const SummaryRegs<DT, D, MODE>& x, 
       }
 #pragma unroll
       for (int j = 0; j < F; ++j) {
-        const float vj = C::SPLIT > 1 ? __uint_as_float(xch[(r * F + j) * 64 + lane])
-                                      : word_elem<DT>(x.vw[r], j);
+        const float vj = word_elem<DT>(x.vw[r], j);
 #pragma unroll
-        for (int i = 0; i < FR; ++i) acc[i][j] = mfma_f32(pk[i], vj, acc[i][j]);
+        for (int i = 0; i < F; ++i) acc[i][j] = mfma_f32(pk[i], vj, acc[i][j]);
       }
     }
   }

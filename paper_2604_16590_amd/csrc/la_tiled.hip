@@ -197,7 +197,6 @@ void tile_cols_kernel(TGeo g, const void* __restrict__ k, const void* __restrict
                       float* __restrict__ cols) {
   using C = SummaryCfg<DT_BF16, D, MODE_FWD>;
   using Regs = SummaryRegs<DT_BF16, D, MODE_FWD>;
-  static_assert(C::SPLIT == 1 && C::FR == C::F, "one wave holds a whole sum");
   constexpr int F = C::F, R = C::R, STEP = C::STEP, E = D * D + D;
   const int lane = threadIdx.x & 63;
   const int gq = lane >> 4, m = lane & 15;
