@@ -122,8 +122,8 @@ int64_t partial_room(int64_t N, int d, int P) { return std::max<int64_t>(P, fuse
 // Apply workgroups per head: about kApplyGrid in the whole grid (a few per
 // compute unit), at most one per token block.  Per-token work, so this
 // changes no bits and may depend on the batch size.
-int apply_groups(int64_t N, int64_t BH, int dt, int d) {
-  const int64_t blk = dt == LA_FP32 && d >= 128 ? 64 : 128;  // tokens per block
+int apply_groups(int64_t N, int64_t BH) {
+  const int64_t blk = 128;  // tokens per block
   const int64_t grid = 4096;
   int64_t ga = std::min(ceil_div(N, blk), ceil_div(grid, BH));
   // while the grid keeps 2048 workgroups or more, at least four blocks per
@@ -185,9 +185,9 @@ Layout layout_for(const la_attn_desc* d, int pass) {
 }
 
 // The gate's arguments (the attention's own are checked by the caller).
-// Key-backward workgroups per head, as apply_groups (the fp32 path at
-// d = 128 takes one tile per wave step, like the apply).
-int key_groups(int64_t N, int64_t BH, int dt, int d) {
+// Key-backward workgroups per head, as apply_groups (fp32 takes one tile per
+// wave step).
+int key_groups(int64_t N, int64_t BH, int dt) {
   const int64_t blk = dt == LA_FP32 ? 64 : 128;  // tokens per block (4 waves x 16 x TT)
   int64_t grid = 8192;
   return (int)std::max<int64_t>(1, std::min(ceil_div(N, blk), ceil_div(grid, BH)));
@@ -221,7 +221,7 @@ la_status forward_impl(const la_attn_desc* desc, const void* q, const void* k, c
   a.osb = desc->out_sb; a.osh = desc->out_sh; a.osn = desc->out_sn;
   a.q = q; a.k = k; a.v = v; a.o = o;
   a.P = t.P; a.Tw = t.Tw;
-  a.Ga = apply_groups(desc->N, desc->B * desc->H, desc->in_dtype, (int)desc->d);
+  a.Ga = apply_groups(desc->N, desc->B * desc->H);
   a.part = (float*)(w + L.part);
   a.S64 = s_out ? s_out : (double*)(w + L.S64);
   a.z64 = z_out ? z_out : (double*)(w + L.z64);
@@ -250,7 +250,7 @@ la_status apply_impl(const la_attn_desc* desc, const void* q, const double* s, c
   a.sb = desc->in_sb; a.sh = desc->in_sh; a.sn = desc->in_sn;
   a.osb = desc->out_sb; a.osh = desc->out_sh; a.osn = desc->out_sn;
   a.q = q; a.o = o;
-  a.Ga = apply_groups(desc->N, desc->B * desc->H, desc->in_dtype, (int)desc->d);
+  a.Ga = apply_groups(desc->N, desc->B * desc->H);
   a.S64 = const_cast<double*>(s);
   a.z64 = const_cast<double*>(z);
   a.img = (char*)ws + L.img;
@@ -358,7 +358,7 @@ la_status la_backward(const la_attn_desc* desc, const void* q, const void* k,
   a.dq = dq; a.dk = dk; a.dv = dv;
   a.S64 = s; a.z64 = z;
   a.P = t.P; a.Tw = t.Tw; a.Ta = t.Tk;
-  a.Gk = key_groups(desc->N, desc->B * desc->H, desc->in_dtype, (int)desc->d);
+  a.Gk = key_groups(desc->N, desc->B * desc->H, desc->in_dtype);
   a.img = w + L.img;
   a.part = (float*)(w + L.part);
   a.stash = (float2*)(w + L.stash);

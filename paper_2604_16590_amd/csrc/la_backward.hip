@@ -44,8 +44,8 @@ struct RowCfg {
   // fp32 -> one float per feature
   static constexpr int PW = DT == DT_BF16 ? NS * 4 : Q4;
   // prefetch one step ahead, except where it would not fit the registers
-  // of two waves per SIMD (d = 128, and fp32 from d = 64)
-  static constexpr bool PF = D < 128 && !(DT == DT_FP32 && D >= 64);
+  // of two waves per SIMD
+  static constexpr bool PF = D < 128;
 };
 
 // phi over the lane's run: bf16 packs phi rounded to bf16 (the values the
@@ -138,7 +138,6 @@ __device__ __forceinline__ void image_times_runs(
             acc[t][i] = mfma_f32(__uint_as_float(a[t4]), __uint_as_float(pw[t][4 * s4 + t4]),
                                  s4 == 0 && t4 == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[t][i]);
       }
-      if constexpr (D >= 128) __builtin_amdgcn_sched_barrier(0);
     }
   }
 }
@@ -888,13 +887,13 @@ void bwd_qds4_kernel(const void* __restrict__ q, const void* __restrict__ dout, 
 
 // ---------------------------------------------------------------------------
 // Key kernel: dV = phi(K) dS (T image of dS) and dK = (V dS^T + dz) phi'(K)
-// (N image of dS).  WHICH: 1 = dV only, 2 = dK only, 3 = both.
+// (N image of dS).
 // The dS operands are the hi parts of the bf16 images.  As in the apply,
 // the G workgroups of a head take its blocks of 4 * 16 * TT tokens in turn
 // (blocks g, g + G, ...), so the whole grid moves through the tensors
 // together.
 // ---------------------------------------------------------------------------
-template <int DT, int OT, int D, int WHICH>
+template <int DT, int OT, int D>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void bwd_key_kernel(
     const void* __restrict__ k, const void* __restrict__ v, int64_t sb, int64_t sh,
     int64_t sn, void* __restrict__ dk, void* __restrict__ dv, int64_t osb, int64_t osh,
@@ -906,27 +905,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void b
   constexpr int OES = OT == DT_BF16 ? 2 : 4;
   // matrix tiles only (the z tile is not needed here); bf16: hi parts only
   constexpr int ONE = DT == DT_BF16 ? IC::mat_bytes(DT) / 32 : IC::mat_bytes(DT) / 16;
-  constexpr bool DO_V = WHICH & 1, DO_K = WHICH & 2;
-  __shared__ u32x4 simg[(DO_V ? ONE : 0) + (DO_K ? ONE : 0)];
+  __shared__ u32x4 simg[2 * ONE];
   u32x4* timg = simg;
-  u32x4* nimg = simg + (DO_V ? ONE : 0);
+  u32x4* nimg = simg + ONE;
 
   const int bh = blockIdx.y;
   const int64_t b = bh / H, h = bh % H;
   const u32x4* head = (const u32x4*)((const char*)dimg + (int64_t)bh * IC::head_bytes(DT));
-  if (DO_V) stage_image(timg, head, ONE, DT == DT_BF16);
-  if (DO_K) stage_image(nimg, head + IC::img_bytes(DT) / 16, ONE, DT == DT_BF16);
+  stage_image(timg, head, ONE, DT == DT_BF16);
+  stage_image(nimg, head + IC::img_bytes(DT) / 16, ONE, DT == DT_BF16);
   const int lane = threadIdx.x & 63, wave = wave_index();
   const int g = lane >> 4, n = lane & 15;
   // dz is added in FP32 for bf16 inputs (their dS operands are bf16 hi
   // parts, whose rounding is some 2^15 times that of dz to FP32) and in
   // FP64 for fp32 inputs
   using DzT = typename std::conditional<DT == DT_BF16, float, double>::type;
-  DzT dzr[DO_K ? Q4 : 1];
-  if constexpr (DO_K) {
+  DzT dzr[Q4];
 #pragma unroll
-    for (int c = 0; c < Q4; ++c) dzr[c] = (DzT)dz64[(int64_t)bh * D + Run<D, DT>::feature(g, c)];
-  }
+  for (int c = 0; c < Q4; ++c) dzr[c] = (DzT)dz64[(int64_t)bh * D + Run<D, DT>::feature(g, c)];
   __syncthreads();
 
   const int64_t in_head = (b * sb + h * sh) * C::ES + (int64_t)g * Run<D, DT>::CB;
@@ -940,7 +936,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void b
     const int64_t t = t0 + n;
     if (t < N) {
       load_run<D, DT>(kbase + t * sn * C::ES, kw);
-      if (DO_K) load_run<D, DT>(vbase + t * sn * C::ES, vw);
+      load_run<D, DT>(vbase + t * sn * C::ES, vw);
     } else {
 #pragma unroll
       for (int w = 0; w < C::RWD; ++w) { kw[w] = 0; vw[w] = 0; }
@@ -972,7 +968,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void b
 #pragma unroll
       for (int tt = 0; tt < TT; ++tt) {
         phi_words<DT, D>(kcur[tt], pk[tt]);
-        if (DO_K) raw_words<DT, D>(vcur[tt], pv[tt]);
+        raw_words<DT, D>(vcur[tt], pv[tt]);
       }
     } else {
       // load and convert one tile at a time (fewer live registers)
@@ -981,10 +977,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void b
         uint32_t one_k[C::RWD], one_v[C::RWD];
         load_one(t0 + 16 * tt, one_k, one_v);
         phi_words<DT, D>(one_k, pk[tt]);
-        if (DO_K) raw_words<DT, D>(one_v, pv[tt]);
+        raw_words<DT, D>(one_v, pv[tt]);
       }
     }
-    if constexpr (DO_V) {
+    {
       f32x4 acc[TT][NT];
 #pragma unroll
       for (int tt = 0; tt < TT; ++tt)
@@ -1004,7 +1000,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void b
         }
       }
     }
-    if constexpr (DO_K) {
+    {
       f32x4 acc[TT][NT];
 #pragma unroll
       for (int tt = 0; tt < TT; ++tt)
@@ -1080,32 +1076,26 @@ static hipError_t launch_rows(const BwdArgs& a) {
     e = launch_combine(a.part, a.P, a.dS64, a.dz64, a.dimg, DT, BH, D, IMG_T | IMG_N, a.stream);
   }
   if (e != hipSuccess) return e;
-  // both dS images fit in LDS except fp32 at d = 128 (2 x 64 KB): two passes
   ProfScope prof("bwd_key", a.stream);
   const dim3 kgrid((unsigned)a.Gk, BH);
-  if constexpr (DT == DT_FP32 && D >= 128) {
-    bwd_key_kernel<DT, OT, D, 1><<<kgrid, 256, 0, a.stream>>>(
-        a.k, a.v, a.sb, a.sh, a.sn, a.dk, a.dv, a.osb, a.osh, a.osn, (int)a.H, a.N, a.Gk,
-        a.dimg, a.dz64);
-    bwd_key_kernel<DT, OT, D, 2><<<kgrid, 256, 0, a.stream>>>(
-        a.k, a.v, a.sb, a.sh, a.sn, a.dk, a.dv, a.osb, a.osh, a.osn, (int)a.H, a.N, a.Gk,
-        a.dimg, a.dz64);
-  } else {
-    bwd_key_kernel<DT, OT, D, 3><<<kgrid, 256, 0, a.stream>>>(
-        a.k, a.v, a.sb, a.sh, a.sn, a.dk, a.dv, a.osb, a.osh, a.osn, (int)a.H, a.N, a.Gk,
-        a.dimg, a.dz64);
-  }
+  bwd_key_kernel<DT, OT, D><<<kgrid, 256, 0, a.stream>>>(
+      a.k, a.v, a.sb, a.sh, a.sn, a.dk, a.dv, a.osb, a.osh, a.osn, (int)a.H, a.N, a.Gk, a.dimg,
+      a.dz64);
   return hipGetLastError();
 }
 
 template <int D>
 static hipError_t launch_backward_d(const BwdArgs& a) {
+  if (fp32_rows(a.in_dt, D)) return launch_backward_fp32(a);
   hipError_t e = launch_images(a.S64, a.z64, a.img, a.in_dt, a.B * a.H, D, IMG_Z | IMG_N | IMG_LO, a.stream);
   if (e != hipSuccess) return e;
   if (a.in_dt == DT_BF16 && a.out_dt == DT_BF16) return launch_rows<DT_BF16, DT_BF16, D>(a);
   if (a.in_dt == DT_BF16) return launch_rows<DT_BF16, DT_FP32, D>(a);
-  if (a.out_dt == DT_BF16) return launch_rows<DT_FP32, DT_BF16, D>(a);
-  return launch_rows<DT_FP32, DT_FP32, D>(a);
+  if constexpr (!fp32_rows(DT_FP32, D)) {
+    if (a.out_dt == DT_BF16) return launch_rows<DT_FP32, DT_BF16, D>(a);
+    return launch_rows<DT_FP32, DT_FP32, D>(a);
+  }
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_backward(const BwdArgs& a) {

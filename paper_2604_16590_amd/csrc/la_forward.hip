@@ -443,8 +443,8 @@ __global__ __launch_bounds__(64 * SplitCfg<D>::NW) __attribute__((amdgpu_waves_p
 // words of both images (eight contraction indices each), so every store is
 // one: the halfword stores this replaces took most of the time (1,024 heads
 // of 4 partials at d = 64: 94 -> 37 us; 64 heads of 8: 14 -> 7.5 us).  The
-// last workgroup of a head does the same for the vector.  M_IN (double):
-// M and v are given, only the operands are written.
+// last workgroup of a head does the same for the vector.  T = double: M
+// and v are given, only the operands are written.
 // ---------------------------------------------------------------------------
 template <int D, int IDT, typename T>
 __global__ __launch_bounds__(8 * D) void combine_kernel(
@@ -535,9 +535,8 @@ __global__ __launch_bounds__(8 * D) void combine_kernel(
 // ---------------------------------------------------------------------------
 template <int DT, int D>
 struct ApplyCfg {
-  // 16-token tiles per step; every LDS operand read feeds TT matrix-core
-  // ops (fp32 at d = 128: one, for registers)
-  static constexpr int TT = DT == DT_FP32 && D >= 128 ? 1 : 2;
+  // 16-token tiles per step; every LDS operand read feeds TT matrix-core ops
+  static constexpr int TT = 2;
   static constexpr int ES = DT == DT_BF16 ? 2 : 4;
   static constexpr int QB = D / 4 * ES;             // bytes of a lane's query run
   static constexpr int QW = QB / 4;
@@ -687,7 +686,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
             for (int tt = 0; tt < TT; ++tt)
               acc[tt][i] = mfma_f32(__uint_as_float(a[t4]), pq[tt][4 * s4 + t4],
                                     s4 == 0 && t4 == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[tt][i]);
-          if constexpr (D >= 128) __builtin_amdgcn_sched_barrier(0);
         }
     }
 #pragma unroll
@@ -838,13 +836,15 @@ static hipError_t launch_forward_d(const FwdArgs& a) {
                       nullptr, a.part, a.stream);
   {
     ProfScope prof("combine", a.stream);
-    launch_combine_d<D>(a.part, a.P, a.S64, a.z64, a.img, a.in_dt, BH, IMG_T | IMG_Z | IMG_LO, a.stream);
+    launch_combine_d<D>(a.part, a.P, a.S64, a.z64, a.img, a.in_dt, BH,
+                        fp32_rows(a.in_dt, D) ? 0 : IMG_T | IMG_Z | IMG_LO, a.stream);
   }
   return launch_apply_only<D>(a);
 }
 
 template <int D>
 static hipError_t launch_apply_only(const FwdArgs& a) {
+  if (fp32_rows(a.in_dt, D)) return launch_apply_fp32(a);
   const int BH = (int)(a.B * a.H);
   dim3 agrid((unsigned)a.Ga, BH);
   ProfScope prof(a.other ? "apply_gated" : "apply", a.stream);
@@ -855,8 +855,10 @@ static hipError_t launch_apply_only(const FwdArgs& a) {
 #define LA_APPLY_DT(MIX)                                                \
   if (a.in_dt == DT_BF16 && a.out_dt == DT_BF16) LA_APPLY(DT_BF16, DT_BF16, MIX); \
   else if (a.in_dt == DT_BF16) LA_APPLY(DT_BF16, DT_FP32, MIX);                   \
-  else if (a.out_dt == DT_BF16) LA_APPLY(DT_FP32, DT_BF16, MIX);                  \
-  else LA_APPLY(DT_FP32, DT_FP32, MIX);
+  else if constexpr (!fp32_rows(DT_FP32, D)) {                                    \
+    if (a.out_dt == DT_BF16) LA_APPLY(DT_FP32, DT_BF16, MIX);                     \
+    else LA_APPLY(DT_FP32, DT_FP32, MIX);                                         \
+  }
   if (a.other) {
     LA_APPLY_DT(true)
   } else {
@@ -878,7 +880,9 @@ hipError_t launch_forward(const FwdArgs& a) {
 }
 
 hipError_t launch_apply(const FwdArgs& a) {
-  hipError_t e = launch_images(a.S64, a.z64, a.img, a.in_dt, a.B * a.H, a.D, IMG_T | IMG_Z | IMG_LO, a.stream);
+  hipError_t e = hipSuccess;
+  if (!fp32_rows(a.in_dt, a.D))
+    e = launch_images(a.S64, a.z64, a.img, a.in_dt, a.B * a.H, a.D, IMG_T | IMG_Z | IMG_LO, a.stream);
   if (e != hipSuccess) return e;
   switch (a.D) {
     case 16: return launch_apply_only<16>(a);

@@ -203,6 +203,11 @@ hipError_t launch_summary(int mode, int dt, int D, const void* k, const void* v,
 hipError_t launch_combine(const float* part, int P, double* M64, double* v64, void* img,
                           int img_dt, int64_t BH, int D, int what, hipStream_t stream);
 hipError_t launch_backward(const BwdArgs& a);
+// fp32 inputs at d = 64 and 128, where the row kernels take S and dS in FP64
+// and need no operand images: the apply, and the whole backward.
+constexpr bool fp32_rows(int dt, int D) { return dt == DT_FP32 && D >= 64; }
+hipError_t launch_apply_fp32(const FwdArgs& a);
+hipError_t launch_backward_fp32(const BwdArgs& a);
 // The operands `what` of a given M and v.
 hipError_t launch_images(const double* M64, const double* v64, void* img, int img_dt, int64_t BH,
                          int D, int what, hipStream_t stream);

@@ -92,3 +92,66 @@ def test_fp32_extremes(kind, d):
         assert np.array_equal(np.isnan(got), np.isnan(ref))
         assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
         assert normwise(np.where(ok, got, 0), np.where(ok, ref, 0)) < tol
+
+
+# tokens: one 16-token tile and its neighbours; a workgroup's block (d = 128:
+# eight waves, 64: four; two tiles a wave in the apply) and its neighbours
+@pytest.mark.parametrize("d,N", [(d, n) for d in (64, 128) for n in (1, 15, 17, 127, 129, 255, 257, 1100)])
+@pytest.mark.parametrize("out", ["fp32", "bf16"])
+def test_fp32_rows(d, N, out):
+    # the fp32 row kernels against the oracle, with the gated apply, on
+    # views of [B, N, H, d] storage
+    dev = require_gpu()
+    B, H = 2, 3
+    od = torch.float32 if out == "fp32" else torch.bfloat16
+    host = make_inputs((B, H, N, d), "fp32", seed=900 + N + d, streams=(0, 1, 2, 3))
+    view = lambda dt: torch.empty((B, N, H, d), dtype=dt, device=dev).permute(0, 2, 1, 3)
+    q, k, v, g = (view(torch.float32).copy_(to_device(x, dev)) for x in host)
+    o, S, z = la.forward(q, k, v, out=view(od), return_summary=True)
+    dq, dk, dv = la.backward(q, k, v, S, z, g, grad_dtype=od)
+    other = view(od).copy_(to_device(make_inputs((B, H, N, d), "fp32", seed=901)[0], dev))
+    sigma = torch.tensor([0.3, 4.0], dtype=torch.float64, device=dev)
+    mixed = la.apply_gated(q, S, z, other, sigma, out=view(od))
+    torch.cuda.synchronize()
+    tol = TOL[out]
+    ref = oracle.forward(*host[:3])
+    assert normwise(as64(o), ref) < tol
+    w = (0.5 / (0.5 + np.array([0.3, 4.0])))[:, None, None, None]
+    assert normwise(as64(mixed), w * ref + (1 - w) * as64(other)) < tol
+    grads = oracle.backward(*host)
+    if N == 1:  # the gradients of q and k vanish
+        grads, got = grads[2:], (dv,)
+    else:
+        got = (dq, dk, dv)
+    for x, r in zip(got, grads):
+        assert normwise(as64(x), r) < tol
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_rows_outside_the_split_range(d):
+    # scales below the split's range take the fp32 instructions: the
+    # problem is linear in v and in the upstream gradient, so scaling
+    # either by 2^-100 scales the results, to rounding
+    dev = require_gpu()
+    host = make_inputs((1, 2, 333, d), "fp32", seed=41, streams=(0, 1, 2, 3))
+    q, k, v, g = (to_device(x, dev) for x in host)
+    c = 2.0 ** -100
+    o, S, z = la.forward(q, k, v, return_summary=True)
+    grads = la.backward(q, k, v, S, z, g)
+    o1, S1, z1 = la.forward(q, k, v * c, return_summary=True)
+    grads_v = la.backward(q, k, v * c, S1, z1, g)
+    grads_g = la.backward(q, k, v, S, z, g * c)
+    # a few of a tile's tokens outside the range, the rest as they were
+    q2 = q.clone()
+    q2[:, :, 40:43] = -75.0  # phi ~ 2^-108
+    o2 = la.forward(q2, k, v)
+    torch.cuda.synchronize()
+    assert normwise(as64(o1) / c, as64(o)) < 1e-5
+    for i, name in enumerate(("dq", "dk", "dv")):
+        assert normwise(as64(grads_g[i]) / c, as64(grads[i])) < 1e-5, name
+    assert normwise(as64(grads_v[0]) / c, as64(grads[0])) < 1e-5
+    assert normwise(as64(grads_v[2]), as64(grads[2])) < 1e-5
+    keep = np.r_[0:40, 43:333]
+    assert normwise(as64(o2)[:, :, keep], as64(o)[:, :, keep]) < 1e-5
+    mean = as64(S).sum(2) / as64(z).sum(2)[..., None]  # equal weights
+    assert normwise(as64(o2)[:, :, 41], mean) < 1e-5
