@@ -75,10 +75,12 @@ int64_t max_fp32_run(int dt) { return dt == LA_BF16 ? 16384 : 4096; }
 // max_fp32_run tokens per head: 0.8 % of the inputs' bytes at d = 128).
 int64_t max_partials(int d) { return d >= 128 ? 128 : 64; }
 
-// The fused query backward: a partial per wave (d <= 64) or workgroup.
-// At least 2048 (d = 128) or 512 tokens each.
+// The fused query backward, a workgroup to a partial: at least 2048 (d =
+// 128) or 512 tokens each, but up to four partials of at least 4 d (two
+// heads of 1,000 tokens at d = 128: 42 us in two partials, 62 in one).
 int64_t fused_partials(int64_t N, int d) {
-  return std::min<int64_t>(max_partials(d), ceil_div(N, d >= 128 ? 2048 : 512));
+  return std::max(std::min(max_partials(d), ceil_div(N, d >= 128 ? 2048 : 512)),
+                  std::min<int64_t>(4, ceil_div(N, 4 * d)));
 }
 
 // The summary: a partial's write and read cost 2 (d + 1) * 4 bytes against
@@ -88,11 +90,14 @@ int64_t fused_partials(int64_t N, int d) {
 // tokens, so that a few heads still fill compute units: one head of 4,096
 // fp32 tokens (d = 64) takes 14 us in sixteen partials and 21 in eight, while
 // 1,024 heads of 8,192 bf16 tokens take 396 + 94 us (summary + combine) in
-// four and 430 + 110 in eight.
+// four and 430 + 110 in eight.  bf16 at d <= 32 gives a partial to a single
+// wave (see the kernel): 512 tokens, or up to sixteen of at least 4 d.
 int64_t summary_partials(int64_t N, int d, int dt) {
+  const bool single = dt == LA_BF16 && d <= 32;
   const int64_t unit = dt == LA_BF16 ? 4 * d : 2 * d;
-  const int64_t few = dt == LA_BF16 ? 4 : 16;
-  return std::max(std::min(max_partials(d), ceil_div(N, 8 * unit)), std::min(few, ceil_div(N, unit)));
+  const int64_t few = single || dt == LA_FP32 ? 16 : 4;
+  return std::max(std::min(max_partials(d), ceil_div(N, single ? 512 : 8 * unit)),
+                  std::min(few, ceil_div(N, unit)));
 }
 
 bool fused_backward(int d, int dt) { return dt == LA_BF16 && d >= 32; }
@@ -117,7 +122,9 @@ Tiling choose_tiling(int64_t N, int d, int dt, bool backward) {
 // Partials the workspace has room for: those of the tiling, or as many as
 // 512 (d = 128: 2048) tokens each would make, which keeps the size the
 // same from 64 (128) of them up to max_fp32_run tokens each.
-int64_t partial_room(int64_t N, int d, int P) { return std::max<int64_t>(P, fused_partials(N, d)); }
+int64_t partial_room(int64_t N, int d, int P) {
+  return std::max<int64_t>(P, std::min(max_partials(d), ceil_div(N, d >= 128 ? 2048 : 512)));
+}
 
 // Apply workgroups per head: about kApplyGrid in the whole grid (a few per
 // compute unit), at most one per token block.  Per-token work, so this

@@ -204,7 +204,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void b
     const void* __restrict__ q, const void* __restrict__ dout, int64_t sb, int64_t sh,
     int64_t sn, void* __restrict__ dq, int64_t osb, int64_t osh, int64_t osn, int H,
     int64_t N, int Ta, const void* __restrict__ img, const double* __restrict__ z64,
-    float2* __restrict__ stash) {
+    float2* __restrict__ stash, int G, int BH, bool shared_lines) {
   using C = RowCfg<DT, D>;
   using IC = ImageCfg<D>;
   using real = typename std::conditional<DT == DT_BF16, float, double>::type;
@@ -215,7 +215,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void b
   __shared__ u32x4 simg[IMG_WORDS + Z_WORDS];
   const u32x4* zimg = simg + IMG_WORDS;
 
-  const int bh = blockIdx.y;
+  const HeadPart hp = head_part(G, BH, shared_lines);
+  if (hp.out) return;  // uniform over the workgroup
+  const int bh = hp.bh;
   const int64_t b = bh / H, h = bh % H;
   {
     const char* head = (const char*)img + (int64_t)bh * IC::head_bytes(DT);
@@ -229,7 +231,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void b
   for (int c = 0; c < Q4; ++c) zr[c] = (real)z64[(int64_t)bh * D + Run<D, DT>::feature(g, c)];
   __syncthreads();
 
-  const int64_t wg_begin = (int64_t)blockIdx.x * Ta;
+  const int64_t wg_begin = (int64_t)hp.g * Ta;
   const int64_t wg_end = min(N, wg_begin + (int64_t)Ta);
   // wave-uniform head pointers plus loop-invariant 32-bit lane offsets
   const int64_t row_bytes = sn * C::ES, orow_bytes = osn * OES;
@@ -334,64 +336,52 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void b
 
 // ---------------------------------------------------------------------------
 // Fused query backward (bf16 inputs, d = 32 or 64): dQ exactly as in the
-// query kernel, and in the same pass each wave's partial sums over its own
-// tokens (32-token blocks p, p + P, ..., at most Tw tokens) of
+// query kernel, and in the same pass a workgroup's partial sums (each wave
+// over its own tokens, added up in LDS at the end) of
 //   dS = sum_i phi(q_i) (G_i / den_i)^T,   dz = sum_i dden_i phi(q_i),
 // so Q and G are read once.  The reduction contracts over tokens, but the
-// query pass holds one token per lane; the token-major operands are made
-// on the matrix cores themselves: a lane run taken as A[m = token][k =
-// feature] times a 0/1 selection matrix B[k][n] = (k == n + 16h) gives
-// D[token][n] = run feature 32s + 16h + n, i.e. 16 features x 4 tokens in
-// each lane, which is what a contraction over tokens takes.  The whole
-// d x d partial dS stays in registers, so the next step's Q and G are
-// prefetched straight into LDS (global_load_lds, 16 bytes per lane)
-// instead of registers.
-// Partial tile (i, j) holds, in lane (g, n) register r, dS[16i + 4g + r][16j + n];
+// query pass holds one token per lane: each wave puts its 32 tokens' G and
+// phi(q)/den rows into its own part of LDS and reads token-major operands
+// back with the transposing read (no barrier: nothing is shared between
+// waves).  dz is summed per lane, in FP32, over the tokens the lane holds,
+// and across lanes at the end.  The whole d x d sum stays in registers.
+//
+// What bounds it: HBM (32 heads of 262,144 tokens at d = 64: 0.64 ms, 5.0
+// TB/s; 0.66 with the operands made in registers by selection products,
+// which takes 40 % more matrix instructions and twice the packing).
+// Tile (i, j) of the sum holds, in lane (g, n) register r, dS[16i + 4g + r][16j + n];
 // the partial is stored as rows of dS, then dz.
 // ---------------------------------------------------------------------------
-template <int D>
-struct FusedCfg {
-  using R = Run<D, DT_BF16>;
-  static constexpr int NB = D / 16;                   // 16-feature blocks
-  static constexpr int NS = D / 32;                   // k-steps of a run
-  static constexpr int TT = 2;                        // tiles per step: 32 tokens
-  static constexpr int RW = D / 8;                    // words of a lane's run
-  static constexpr int NCH = R::NCH;                  // 16-byte chunks per run
-  static constexpr int STAGE = TT * 2 * NCH * 1024;   // LDS bytes per wave per step
-  static constexpr int WAVES_PER_SIMD = 2;
-};
-
-typedef __attribute__((address_space(3))) void* lds_void_ptr;
-// Wait until at most N vector memory operations of this wave are
-// outstanding; also a compiler barrier.
-template <int N>
-__device__ __forceinline__ void wait_vmem() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
 template <int OT, int D>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FusedCfg<D>::WAVES_PER_SIMD)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 4)))
 void bwd_qds_kernel(const void* __restrict__ q, const void* __restrict__ dout, int64_t sb,
                     int64_t sh, int64_t sn, void* __restrict__ dq, int64_t osb, int64_t osh,
-                    int64_t osn, int H, int64_t N, int P, int Tw, const void* __restrict__ img,
-                    const double* __restrict__ z64, float* __restrict__ part) {
+                    int64_t osn, int H, int64_t N, int P, const void* __restrict__ img,
+                    const double* __restrict__ z64, float* __restrict__ part, int BH,
+                    bool shared_lines) {
   using C = RowCfg<DT_BF16, D>;
-  using FC = FusedCfg<D>;
   using IC = ImageCfg<D>;
   using RN = Run<D, DT_BF16>;
-  constexpr int Q4 = D / 4, NT = D / 16, TT = FC::TT, NB = FC::NB, NS = FC::NS;
-  constexpr int RW = FC::RW, NCH = FC::NCH;
+  constexpr int Q4 = D / 4, NT = D / 16, TT = 2, NB = D / 16;
+  constexpr int RW = D / 8, NCH = RN::NCH;                // words, 16-byte chunks of a lane's run
   constexpr int OES = OT == DT_BF16 ? 2 : 4;
   constexpr int IMG_WORDS = IC::mat_bytes(DT_BF16) / 16;  // the N image
   constexpr int Z_WORDS = IC::tile_bytes(DT_BF16) / 16;   // the T image's z tile
   constexpr int E = D * D + D;
+  constexpr int RC = D * 2 / 16;                          // 16-byte chunks of a row
+  constexpr int ROWS = 16 * TT * RC;                      // words of a wave's 32 rows of one tensor
   static_assert(TT == C::TT && RW == C::PW, "run layout");
-  __shared__ u32x4 simg[IMG_WORDS + Z_WORDS];
+  // the images and the four waves' rows (phi(q)/den, then G); at the end,
+  // RT tiles of each wave's sum at a time
+  __shared__ u32x4 smem[IMG_WORDS + Z_WORDS + 4 * 2 * ROWS];
   __shared__ float zf[D];
-  __shared__ u32x4 stage[4 * FC::STAGE / 16];
+  __shared__ float zred[4][D];
+  u32x4* simg = smem;
   const u32x4* zimg = simg + IMG_WORDS;
 
-  const int bh = blockIdx.y;
+  const HeadPart hp = head_part(P, BH, shared_lines);
+  if (hp.out) return;  // uniform over the workgroup
+  const int bh = hp.bh;
   const int64_t b = bh / H, h = bh % H;
   {
     const char* head = (const char*)img + (int64_t)bh * IC::head_bytes(DT_BF16);
@@ -402,93 +392,79 @@ void bwd_qds_kernel(const void* __restrict__ q, const void* __restrict__ dout, i
   __syncthreads();
   const int lane = threadIdx.x & 63, wave = wave_index();
   const int g = lane >> 4, n = lane & 15;
-  const int p = blockIdx.x * 4 + wave;
-  if (p >= P) return;  // no barriers follow
-  // partial p takes the head's 32-token blocks p, p + P, p + 2P, ... (at
-  // most Tw tokens), so the grid's waves move through Q, G and dQ together
-  const int64_t nb = (N + 16 * TT - 1) / (16 * TT);
-  const int nsteps = (int)((nb - 1 - p) / P + 1);  // >= 1: P <= N / 64 < nb
-  auto first_token = [&](int k) { return ((int64_t)p + (int64_t)k * P) * (16 * TT); };
+  // wave w of partial p takes the head's 32-token blocks 4p + w, 4p + w +
+  // 4P, ... (a partial at most Tw tokens), so the grid's waves move through
+  // Q, G and dQ together
+  const int p = hp.g;
+  const int64_t nb = (N + 16 * TT - 1) / (16 * TT), b0 = 4 * (int64_t)p + wave;
+  const int nsteps = b0 < nb ? (int)((nb - 1 - b0) / (4 * (int64_t)P) + 1) : 0;
+  auto first_token = [&](int k) { return (b0 + (int64_t)k * 4 * P) * (16 * TT); };
 
   const int64_t row_bytes = sn * 2, orow_bytes = osn * OES;
   const char* qh = (const char*)q + (b * sb + h * sh) * 2;
   const char* gh = (const char*)dout + (b * sb + h * sh) * 2;
   char* oh = (char*)dq + (b * osb + h * osh) * OES;
-  const uint32_t ioff = (uint32_t)n * (uint32_t)row_bytes + (uint32_t)(g * RN::CB);
   const uint32_t ooff = (uint32_t)n * (uint32_t)orow_bytes + (uint32_t)(g * RN::CH * OES);
-  u32x4* stg = stage + wave * (FC::STAGE / 16);
+  char* rowq = (char*)(smem + IMG_WORDS + Z_WORDS + wave * 2 * ROWS);
+  char* rowg = rowq + ROWS * 16;
+  // byte of 16-byte chunk c of row r: chunks XOR-swizzled so that the eight
+  // rows a half wave reads (32 bytes each) lie in distinct banks
+  auto at = [](int r, int c) { return (r * RC + (c ^ (2 * ((r >> (D == 64 ? 1 : 2)) & (RC / 2 - 1))))) * 16; };
 
-  // Prefetch a step's Q and G runs into this wave's LDS stage: slot
-  // [(tt*2 + tensor)*NCH + chunk][lane].  Rows past the head's end are
-  // skipped (their slots keep stale data; the reader zeroes those tokens).
-  auto prefetch = [&](int64_t t0) {
+  typedef uint32_t Regs[TT][2][RW];  // Q run, G run of the step's tiles
+  // Rows past the head's end read its last token again (finite values, no
+  // branch around the loads); the step gives such tokens a zero scale, so
+  // they add nothing to dS or dz and their dQ rows are not stored.
+  auto load = [&](int k, Regs& x) {
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) {
-      const bool ok = t0 + 16 * tt + n < N;
-#pragma unroll
-      for (int ten = 0; ten < 2; ++ten) {
-        const char* src = (ten == 0 ? qh : gh) + (t0 + 16 * tt) * row_bytes + ioff;
-#pragma unroll
-        for (int w = 0; w < NCH; ++w) {
-          if (ok)
-            __builtin_amdgcn_global_load_lds((const void*)(src + w * 4 * RN::CB),
-                                             (lds_void_ptr)(stg + ((tt * 2 + ten) * NCH + w) * 64),
-                                             16, 0, 0);
-        }
-      }
+      const int64_t tb = min(first_token(k) + 16 * tt, N - 1);  // wave-uniform
+      const int last = (int)min((int64_t)15, N - 1 - tb);
+      const uint32_t off = (uint32_t)min(n, last) * (uint32_t)row_bytes + (uint32_t)(g * RN::CB);
+      load_run<D, DT_BF16>(qh + tb * row_bytes + off, x[tt][0]);
+      load_run<D, DT_BF16>(gh + tb * row_bytes + off, x[tt][1]);
     }
   };
-
-  // 0/1 selection operands: lane (g, n) supplies B[8g + j][n] = (8g + j == n + 16h)
-  bf16x8 sel[2];
-#pragma unroll
-  for (int hh = 0; hh < 2; ++hh) {
-    uint32_t w4[4] = {0u, 0u, 0u, 0u};
-    const int k = n + 16 * hh;
-    if (k / 8 == g) w4[(k % 8) >> 1] = (k & 1) ? 0x3f800000u : 0x00003f80u;
-    sel[hh] = as_bf16x8(u32x4{w4[0], w4[1], w4[2], w4[3]});
-  }
 
   f32x4 ds[NB][NB];
 #pragma unroll
   for (int i = 0; i < NB; ++i)
 #pragma unroll
     for (int j = 0; j < NB; ++j) ds[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // dz partial sums: lane (g', n) of block i holds feature 16i + n over the
-  // tokens 4g' + r it saw
-  float dzb[NB];
+  float dz[Q4];  // per lane: its run's features over the tokens it holds
 #pragma unroll
-  for (int i = 0; i < NB; ++i) dzb[i] = 0.f;
+  for (int c = 0; c < Q4; ++c) dz[c] = 0.f;
 
-  prefetch(first_token(0));
-  for (int kstep = 0; kstep < nsteps; ++kstep) {
-    const int64_t t0 = first_token(kstep);
-    // this step's runs: wait for its prefetch, read them, then refill the
-    // stage.  The loads into LDS share the vector memory counter with the
-    // previous step's dQ stores, and nothing orders a load's retirement
-    // before a store issued after it, so only a zero count proves the
-    // stage has landed (the compiler emits the same full wait before any
-    // LDS read that a load into LDS may have written)
-    wait_vmem<0>();
+  // token-major operand of feature block f: lane (g, m) addresses row 4g +
+  // (m >> 2) of each tile, features 16f + 4 (m & 3) .. + 3, and receives
+  // tokens 4g .. 4g + 3 of feature 16f + m of tile 0, then of tile 1
+  const int rrow = 4 * g + (n >> 2);
+  auto operand = [&](const char* rows, int f) {
+    const char* r = rows + at(rrow, 2 * f + ((n & 3) >> 1)) + (n & 1) * 8;
+    const u32x2 lo = lds_read_tr16(r), hi = lds_read_tr16(r + 16 * RC * 16);
+    return as_bf16x8(u32x4{lo[0], lo[1], hi[0], hi[1]});
+  };
+
+  // The loads are unconditional (a step past the end reads the head's last
+  // row), and the scheduling barrier keeps the next step's at the start of
+  // the step that they overlap.
+  Regs x;
+  if (nsteps > 0) load(0, x);
+  for (int k = 0; k < nsteps; ++k) {
+    const int64_t t0 = first_token(k);
     uint32_t pq[TT][RW], pg[TT][RW];
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) {
-      const bool ok = t0 + 16 * tt + n < N;
-      uint32_t qw[RW];
+      phi_words<DT_BF16, D>(x[tt][0], pq[tt]);
+      raw_words<DT_BF16, D>(x[tt][1], pg[tt]);
+      // chunk w of the lane's run is the row's 16-byte chunk 4w + g
 #pragma unroll
-      for (int w = 0; w < NCH; ++w) {
-        const u32x4 a = stg[((tt * 2 + 0) * NCH + w) * 64 + lane];
-        const u32x4 c = stg[((tt * 2 + 1) * NCH + w) * 64 + lane];
-        qw[4 * w] = ok ? a.x : 0u; qw[4 * w + 1] = ok ? a.y : 0u;
-        qw[4 * w + 2] = ok ? a.z : 0u; qw[4 * w + 3] = ok ? a.w : 0u;
-        pg[tt][4 * w] = ok ? c.x : 0u; pg[tt][4 * w + 1] = ok ? c.y : 0u;
-        pg[tt][4 * w + 2] = ok ? c.z : 0u; pg[tt][4 * w + 3] = ok ? c.w : 0u;
-      }
-      phi_words<DT_BF16, D>(qw, pq[tt]);
+      for (int w = 0; w < NCH; ++w)
+        *(u32x4*)(rowg + at(16 * tt + n, 4 * w + g)) =
+            u32x4{pg[tt][4 * w], pg[tt][4 * w + 1], pg[tt][4 * w + 2], pg[tt][4 * w + 3]};
     }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    if (kstep + 1 < nsteps) prefetch(first_token(kstep + 1));
-
+    load(k + 1, x);
+    __builtin_amdgcn_sched_barrier(0);
     // X = S G and den = phi(q) . z on the matrix cores
     f32x4 acc[TT][NT];
 #pragma unroll
@@ -501,25 +477,7 @@ void bwd_qds_kernel(const void* __restrict__ q, const void* __restrict__ dout, i
     for (int tt = 0; tt < TT; ++tt) dacc[tt][0] = f32x4{0.f, 0.f, 0.f, 0.f};
     tile_times_runs<DT_BF16, D>(zimg, lane, pq, dacc);
 
-    // token-major G operands for dS: bg[j] = G of feature block j, 8 tokens
-    bf16x8 bg[NB];
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      f32x4 tr[TT];
-#pragma unroll
-      for (int tt = 0; tt < TT; ++tt) {
-        const int s0 = j >> 1;
-        const bf16x8 a = as_bf16x8(u32x4{pg[tt][4 * s0], pg[tt][4 * s0 + 1], pg[tt][4 * s0 + 2],
-                                         pg[tt][4 * s0 + 3]});
-        tr[tt] = mfma_bf16(a, sel[j & 1], f32x4{0.f, 0.f, 0.f, 0.f});
-      }
-      // exact: the products are bf16 values times 1
-      bg[j] = as_bf16x8(u32x4{pack_bf16(tr[0][0], tr[0][1]), pack_bf16(tr[0][2], tr[0][3]),
-                              pack_bf16(tr[1][0], tr[1][1]), pack_bf16(tr[1][2], tr[1][3])});
-    }
-
     // per token: den, G . O, dQ, and the scales 1/den and dden = -(G . O)/den
-    float rdt[TT], ddt[TT];
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) {
       float gn = 0.f;
@@ -529,28 +487,29 @@ void bwd_qds_kernel(const void* __restrict__ q, const void* __restrict__ dout, i
         for (int r = 0; r < 4; ++r) gn += run_val<DT_BF16>(pq[tt], 4 * i + r) * acc[tt][i][r];
       gn = sum_groups(gn);
       const double rden = 1.0 / (double)dacc[tt][0][0];
-      const float rd = (float)rden;
-      const float go = gn * rd;  // G . O
-      rdt[tt] = rd;
-      ddt[tt] = -go * rd;        // zero for padded tokens (G = 0)
-      const int64_t t = t0 + 16 * tt + n;
-      const bool ok = t < N;
-      // dQ chunk by chunk (few live registers): run positions [CH*w, +CH)
+      const bool ok = t0 + 16 * tt + n < N;
+      const float rd = ok ? (float)rden : 0.f;  // zero past the end: no dS, dz share
+      const float go = gn * rd;                 // G . O
+      const float dd = -go * rd;
+      // dQ chunk by chunk (few live registers): run positions [CH*w, +CH);
+      // phi(q)/den rows into LDS
       constexpr int CH = RN::CH;
       constexpr int OCB = CH * OES;
       char* orow = oh + (t0 + 16 * tt) * orow_bytes + ooff;
 #pragma unroll
       for (int w = 0; w < NCH; ++w) {
-        uint32_t ow[OCB / 4];
+        uint32_t ow[OCB / 4], wa[CH / 2];
 #pragma unroll
         for (int j = 0; j < CH; j += 2) {
-          float o2[2];
+          float o2[2], s2[2];
 #pragma unroll
           for (int u = 0; u < 2; ++u) {
             const int c = CH * w + j + u;
             const float ph = run_val<DT_BF16>(pq[tt], c);
             const float zc = zf[RN::feature(g, c)];
             o2[u] = (fmaf(-go, zc, acc[tt][c >> 2][c & 3]) * rd) * dphi_of_phi(ph);
+            s2[u] = ph * rd;
+            dz[c] = fmaf(dd, ph, dz[c]);
           }
           if constexpr (OT == DT_BF16) {
             ow[j >> 1] = pack_bf16(o2[0], o2[1]);
@@ -558,54 +517,60 @@ void bwd_qds_kernel(const void* __restrict__ q, const void* __restrict__ dout, i
             ow[j] = __float_as_uint(o2[0]);
             ow[j + 1] = __float_as_uint(o2[1]);
           }
+          wa[j >> 1] = pack_bf16(s2[0], s2[1]);
         }
         if (ok) store_words<OCB>(orow + w * 4 * OCB, ow);
+        *(u32x4*)(rowq + at(16 * tt + n, 4 * w + g)) = u32x4{wa[0], wa[1], wa[2], wa[3]};
       }
     }
 
-    // dS[i][j] += (phi(q)/den of block i, token-major) x bg[j], and
-    // dz[block i] += token sums of phi(q) dden, both made token-major by
-    // the selection product
+    // dS[i][j] += (phi(q)/den of block i) x (G of block j) over the tokens
+    bf16x8 bg[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) bg[j] = operand(rowg, j);
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
-      const int s0 = i >> 1;
-      f32x4 tr[TT], tz[TT];
-#pragma unroll
-      for (int tt = 0; tt < TT; ++tt) {
-        uint32_t wa[4], wz[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const uint32_t w = pq[tt][4 * s0 + k];
-          wa[k] = pack_bf16(bf16lo(w) * rdt[tt], bf16hi(w) * rdt[tt]);
-          wz[k] = pack_bf16(bf16lo(w) * ddt[tt], bf16hi(w) * ddt[tt]);
-        }
-        tr[tt] = mfma_bf16(as_bf16x8(u32x4{wa[0], wa[1], wa[2], wa[3]}), sel[i & 1],
-                           f32x4{0.f, 0.f, 0.f, 0.f});
-        tz[tt] = mfma_bf16(as_bf16x8(u32x4{wz[0], wz[1], wz[2], wz[3]}), sel[i & 1],
-                           f32x4{0.f, 0.f, 0.f, 0.f});
-      }
-      dzb[i] += ((tz[0][0] + tz[0][1]) + (tz[0][2] + tz[0][3])) +
-                ((tz[1][0] + tz[1][1]) + (tz[1][2] + tz[1][3]));
-      const bf16x8 ai = as_bf16x8(u32x4{pack_bf16(tr[0][0], tr[0][1]), pack_bf16(tr[0][2], tr[0][3]),
-                                        pack_bf16(tr[1][0], tr[1][1]), pack_bf16(tr[1][2], tr[1][3])});
+      const bf16x8 ai = operand(rowq, i);
 #pragma unroll
       for (int j = 0; j < NB; ++j) ds[i][j] = mfma_bf16(ai, bg[j], ds[i][j]);
     }
   }
 
-  // the wave's partial: rows of dS, then dz
+  // the partial: rows of dS, then dz.  The waves' sums meet in LDS and are
+  // added in FP64 as (w0 + w1) + (w2 + w3)
   float* out = part + ((int64_t)bh * P + p) * E;
+  auto sum4 = [](float a, float b, float c, float e) {
+    return (float)(((double)a + (double)b) + ((double)c + (double)e));
+  };
+  // dz: add the 16 lanes' token subsets
 #pragma unroll
-  for (int i = 0; i < NB; ++i)
+  for (int c = 0; c < Q4; ++c) {
+    float v = dz[c];
 #pragma unroll
-    for (int j = 0; j < NB; ++j)
+    for (int m = 1; m < 16; m *= 2) v += __shfl_xor(v, m);
+    if (n == 0) zred[wave][RN::feature(g, c)] = v;
+  }
+  constexpr int T = NB * NB, RT = T < 8 ? T : 8;
+  static_assert(4 * RT * 64 <= IMG_WORDS + Z_WORDS + 4 * 2 * ROWS, "the sums fit the rows");
+  f32x4* red = (f32x4*)smem;  // [wave][tile][lane]
 #pragma unroll
-      for (int r = 0; r < 4; ++r) out[(16 * i + 4 * g + r) * D + 16 * j + n] = ds[i][j][r];
-  // dz: add the four lane groups' token subsets
+  for (int t0 = 0; t0 < T; t0 += RT) {
+    __syncthreads();  // the operands, or the last round's sums, have been read
 #pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    const float v = sum_groups(dzb[i]);
-    if (g == 0) out[D * D + 16 * i + n] = v;
+    for (int t = 0; t < RT; ++t) red[(wave * RT + t) * 64 + lane] = ds[(t0 + t) / NB][(t0 + t) % NB];
+    __syncthreads();
+    for (int t = wave; t < RT; t += 4) {
+      const int i = (t0 + t) / NB, j = (t0 + t) % NB;
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        out[(16 * i + 4 * g + r) * D + 16 * j + n] =
+            sum4(red[t * 64 + lane][r], red[(RT + t) * 64 + lane][r], red[(2 * RT + t) * 64 + lane][r],
+                 red[(3 * RT + t) * 64 + lane][r]);
+    }
+  }
+  if (threadIdx.x < D) {
+    const int f = threadIdx.x;
+    out[D * D + f] = sum4(zred[0][f], zred[1][f], zred[2][f], zred[3][f]);
   }
 }
 
@@ -614,8 +579,7 @@ void bwd_qds_kernel(const void* __restrict__ q, const void* __restrict__ dout, i
 // share one partial (64-token blocks p, p + P, ..., at most Tw tokens),
 // taking 16-token tiles in turn (one block per step); two workgroups fit a compute unit, so one
 // waiting at a barrier leaves the SIMDs to the other.  Each wave does the
-// query pass for its tile and makes its tile's token-major operands (as in
-// bwd_qds_kernel, by selection products) into LDS; after a barrier, wave w
+// query pass for its tile and puts its tile's rows into LDS; after a barrier, wave w
 // accumulates a 4 x 4 patch of the 8 x 8 grid of dS tiles over the four
 // tiles (two 32-token contractions), so its share of the partial is 16
 // tiles (64 registers) instead of the whole 128 x 128.  dz = sum_i dden_i
@@ -898,7 +862,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void b
     const void* __restrict__ k, const void* __restrict__ v, int64_t sb, int64_t sh,
     int64_t sn, void* __restrict__ dk, void* __restrict__ dv, int64_t osb, int64_t osh,
     int64_t osn, int H, int64_t N, int G, const void* __restrict__ dimg,
-    const double* __restrict__ dz64) {
+    const double* __restrict__ dz64, int BH, bool shared_lines) {
   using C = RowCfg<DT, D>;
   using IC = ImageCfg<D>;
   constexpr int Q4 = C::Q4, NT = C::NT, TT = C::TT;
@@ -909,7 +873,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void b
   u32x4* timg = simg;
   u32x4* nimg = simg + ONE;
 
-  const int bh = blockIdx.y;
+  const HeadPart hp = head_part(G, BH, shared_lines);
+  if (hp.out) return;  // uniform over the workgroup
+  const int bh = hp.bh;
   const int64_t b = bh / H, h = bh % H;
   const u32x4* head = (const u32x4*)((const char*)dimg + (int64_t)bh * IC::head_bytes(DT));
   stage_image(timg, head, ONE, DT == DT_BF16);
@@ -949,7 +915,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void b
   };
   constexpr int BLK = 16 * TT * 4;  // tokens per block
   const int64_t nblk = (N + BLK - 1) / BLK;
-  const int64_t blk0 = blockIdx.x;
+  const int64_t blk0 = hp.g;
   const int nk = blk0 < nblk ? (int)((nblk - 1 - blk0) / G + 1) : 0;
   // first token of this wave's part of the k-th block it takes
   auto tok = [&](int kk) { return (blk0 + (int64_t)kk * G) * BLK + 16 * TT * wave; };
@@ -1041,7 +1007,7 @@ template <int DT, int OT, int D>
 static hipError_t launch_rows(const BwdArgs& a) {
   hipError_t e = hipSuccess;
   const int BH = (int)(a.B * a.H);
-  dim3 grid((unsigned)((a.N + a.Ta - 1) / a.Ta), BH);
+  const bool shared = lines_shared(a.sh * (DT == DT_BF16 ? 2 : 4), a.H);
   if constexpr (DT == DT_BF16 && D == 128) {
     // one pass, four waves sharing each partial
     ProfScope prof("bwd_query_ds", a.stream);
@@ -1052,22 +1018,22 @@ static hipError_t launch_rows(const BwdArgs& a) {
     if ((e = hipGetLastError()) != hipSuccess) return e;
     e = launch_combine(a.part, a.P, a.dS64, a.dz64, a.dimg, DT, BH, D, IMG_T | IMG_N, a.stream);
   } else if constexpr (DT == DT_BF16 && (D == 32 || D == 64)) {
-    // one pass: dQ and the per-wave partials of dS, dz (at d = 128 the
+    // one pass: dQ and the workgroups' partials of dS, dz (at d = 128 the
     // whole partial dS plus the query pass's state exceed the registers of
     // one wave, so there four waves share a partial, above)
     ProfScope prof("bwd_query_ds", a.stream);
-    dim3 fgrid((unsigned)((a.P + 3) / 4), BH);
-    bwd_qds_kernel<OT, D><<<fgrid, 256, 0, a.stream>>>(
-        a.q, a.dout, a.sb, a.sh, a.sn, a.dq, a.osb, a.osh, a.osn, (int)a.H, a.N, a.P, a.Tw,
-        a.img, a.z64, a.part);
+    bwd_qds_kernel<OT, D><<<row_grid(a.P, BH, shared), 256, 0, a.stream>>>(
+        a.q, a.dout, a.sb, a.sh, a.sn, a.dq, a.osb, a.osh, a.osn, (int)a.H, a.N, a.P, a.img, a.z64,
+        a.part, BH, shared);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     e = launch_combine(a.part, a.P, a.dS64, a.dz64, a.dimg, DT, BH, D, IMG_T | IMG_N, a.stream);
   } else {
     {
       ProfScope prof("bwd_query", a.stream);
-      bwd_query_kernel<DT, OT, D><<<grid, 256, 0, a.stream>>>(
+      const int64_t G = (a.N + a.Ta - 1) / a.Ta;
+      bwd_query_kernel<DT, OT, D><<<row_grid(G, BH, shared), 256, 0, a.stream>>>(
           a.q, a.dout, a.sb, a.sh, a.sn, a.dq, a.osb, a.osh, a.osn, (int)a.H, a.N, a.Ta, a.img,
-          a.z64, a.stash);
+          a.z64, a.stash, (int)G, BH, shared);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     e = launch_summary(MODE_BWD, DT, D, a.q, a.dout, a.sb, a.sh, a.sn, a.B, a.H, a.N, a.P, a.Tw,
@@ -1077,10 +1043,9 @@ static hipError_t launch_rows(const BwdArgs& a) {
   }
   if (e != hipSuccess) return e;
   ProfScope prof("bwd_key", a.stream);
-  const dim3 kgrid((unsigned)a.Gk, BH);
-  bwd_key_kernel<DT, OT, D><<<kgrid, 256, 0, a.stream>>>(
+  bwd_key_kernel<DT, OT, D><<<row_grid(a.Gk, BH, shared), 256, 0, a.stream>>>(
       a.k, a.v, a.sb, a.sh, a.sn, a.dk, a.dv, a.osb, a.osh, a.osn, (int)a.H, a.N, a.Gk, a.dimg,
-      a.dz64);
+      a.dz64, BH, shared);
   return hipGetLastError();
 }
 

@@ -84,9 +84,7 @@ __device__ __forceinline__ void summary_load(const char* kh, const char* vh, uin
 // the same partials in memory (one head of 4,096 fp32 tokens at d = 64:
 // 45 -> 16 us; 64 heads of 16,384 bf16 tokens at d = 64: 54 -> 50 us).
 // Each XCD takes a contiguous share of the items (workgroups go to the
-// eight XCDs in turn), so the heads of one token range, which share cache
-// lines on a BNHD view at d <= 32, are read through one L2 (d = 32, 8
-// heads of 30,001 tokens: 47 -> 38 us).
+// eight in turn).
 // (fp32 inputs at d >= 32 take summary_split_kernel.)
 enum { SUM_WAVE = 0, SUM_TEAM = 1 };
 
@@ -754,6 +752,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
 // costs (8 heads of 2,097,152 tokens at d = 128, 16,384 to a partial: 1.30
 // ms with a wave to a partial, 1.36 with four; 32 heads of 262,144 at
 // d = 64, 4,096 to a partial: the training step 2.22 and 2.26 ms).
+// At d <= 32 a wave keeps its partial: heads of a BNHD view share cache
+// lines there, and a workgroup of four heads reads them through one L1 (d =
+// 32, 8 heads of 30,001 tokens: 34 us, 38 with four waves to a partial).
 constexpr int kTeamTokens = 2048;
 
 template <int DT, int D, int MODE>
@@ -764,9 +765,10 @@ static void launch_summary_t(const void* k, const void* v, int64_t sb, int64_t s
   if constexpr (DT == DT_FP32 && D >= 32) {
     summary_split_kernel<D, MODE><<<dim3((unsigned)((P * BH + 7) / 8 * 8)), 64 * SplitCfg<D>::NW, 0, stream>>>(
         k, v, sb, sh, sn, (int)H, N, P, Tw, stash, part, (int)BH);
-  } else if (Tw <= kTeamTokens) {
-    summary_kernel<DT, D, MODE, SUM_TEAM><<<dim3((unsigned)((P * BH + 7) / 8 * 8)), 256, 0, stream>>>(
-        k, v, sb, sh, sn, (int)H, N, P, Tw, stash, part, (int)BH);
+  } else if (D >= 64 && Tw <= kTeamTokens) {
+    if constexpr (D >= 64)
+      summary_kernel<DT, D, MODE, SUM_TEAM><<<dim3((unsigned)((P * BH + 7) / 8 * 8)), 256, 0, stream>>>(
+          k, v, sb, sh, sn, (int)H, N, P, Tw, stash, part, (int)BH);
   } else {
     summary_kernel<DT, D, MODE, SUM_WAVE><<<dim3((unsigned)((P * BH + 3) / 4)), 256, 0, stream>>>(
         k, v, sb, sh, sn, (int)H, N, P, Tw, stash, part, (int)BH);

@@ -147,6 +147,31 @@ __device__ __forceinline__ void image_row(int row, int& i, int& m) {
   m = 4 * R::group(row) + (pos & 3);
 }
 
+// Workgroup g of G of head bh, in a backward row kernel's grid of
+// row_grid(G, BH) workgroups.  Normally a head's workgroups are neighbours.  Where heads
+// share cache lines (a token's slice of a head is narrower than the 128
+// bytes of one, and the heads are interleaved in a token row), the heads of
+// one token range are, and each XCD (workgroups go to the eight in turn)
+// takes a contiguous share of the ranges, so that a line is read and written
+// through one L2 (d = 32, 8 heads of 30,001 tokens: the query backward 65 ->
+// 58 us, key 60 -> 58; d = 16: query 49 -> 35, key 49 -> 35; the apply, with
+// one tensor in and one out, is slower that way, 35 -> 39 us at d = 32).
+struct HeadPart {
+  int g, bh;
+  bool out;  // beyond the work
+};
+__device__ __forceinline__ HeadPart head_part(int G, int BH, bool shared_lines) {
+  const uint32_t id = blockIdx.x;
+  if (!shared_lines) return HeadPart{(int)(id % (uint32_t)G), (int)(id / (uint32_t)G), false};
+  const uint32_t item = (id & 7) * (gridDim.x >> 3) + (id >> 3);
+  return HeadPart{(int)(item / (uint32_t)BH), (int)(item % (uint32_t)BH),
+                  item >= (uint32_t)G * (uint32_t)BH};
+}
+inline bool lines_shared(int64_t head_stride_bytes, int64_t H) { return H > 1 && head_stride_bytes < 128; }
+inline dim3 row_grid(int64_t G, int64_t BH, bool shared) {
+  return dim3((unsigned)(shared ? (G * BH + 7) / 8 * 8 : G * BH));
+}
+
 struct FwdArgs {
   int64_t B, H, N;
   int D, in_dt, out_dt;

@@ -155,3 +155,27 @@ def test_fp32_rows_outside_the_split_range(d):
     assert normwise(as64(o2)[:, :, keep], as64(o)[:, :, keep]) < 1e-5
     mean = as64(S).sum(2) / as64(z).sum(2)[..., None]  # equal weights
     assert normwise(as64(o2)[:, :, 41], mean) < 1e-5
+
+
+# the fused query backward: one 32-token block of a wave and its neighbours,
+# a partial's end, heads that share cache lines (views of [B, N, H, d])
+@pytest.mark.parametrize("d,N", [(d, n) for d in (16, 32, 64, 128) for n in (31, 33, 127, 129, 513, 2049)])
+@pytest.mark.parametrize("layout", ["bhnd", "bnhd"])
+def test_backward_forms(layout, d, N):
+    dev = require_gpu()
+    B, H = 1, 5
+    host = make_inputs((B, H, N, d), "bf16", seed=300 + N + d, streams=(0, 1, 2, 3))
+    q, k, v, g = (to_device(x, dev) for x in host)
+    if layout == "bnhd":
+        q, k, v, g = (x.permute(0, 2, 1, 3).contiguous().permute(0, 2, 1, 3) for x in (q, k, v, g))
+    _, S, z = la.forward(q, k, v, return_summary=True)
+    got = la.backward(q, k, v, S, z, g)
+    torch.cuda.synchronize()
+    for x, r in zip(got, oracle.backward(*host)):
+        assert normwise(as64(x), r) < TOL["bf16"]
+    # the last head alone: the same bits
+    one = [x[:, H - 1:] for x in (q, k, v, S, z, g)]
+    alone = la.backward(*one)
+    torch.cuda.synchronize()
+    for x, y in zip(got, alone):
+        assert torch.equal(x[:, H - 1:], y)
