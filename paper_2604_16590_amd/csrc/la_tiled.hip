@@ -40,6 +40,8 @@
 namespace la {
 namespace {
 
+typedef __attribute__((address_space(3))) void* lds_void_ptr;
+
 struct TGeo {
   int64_t dims[3], core[3], halo[3], L[3], n[3];
   int64_t cells[3];  // cells per dimension: n + 1
@@ -50,7 +52,11 @@ struct TGeo {
   int Pf;            // parts per segment pair footprint (<= 8)
   int64_t CH, nch;   // tiles per t chunk, chunks
   int64_t n_items;   // column walks: nch * ns[1] * ns[2] * Pf * H
+  bool table;        // the walks keep their positions' offsets in LDS
 };
+
+// Positions of a footprint part whose offsets a walk keeps in LDS, at most.
+constexpr int kTable = 512;
 
 __device__ __forceinline__ uint32_t clamp32(int32_t v, int32_t hi) {
   return (uint32_t)min(max(v, 0), hi);
@@ -74,15 +80,20 @@ struct TiledCfg {
   using IC = ImageCfg<D>;
   static constexpr int NT = D / 16, NS = IC::NS, Q4 = D / 4;
   static constexpr int S_WORDS = NT * NS * 64;  // S^T hi parts
-  // z tile: one operand per k-step whose even rows hold z's bf16 hi parts
-  // and odd rows its lo parts, so output rows 4g and 4g + 1 of a product
-  // are the hi and lo parts of den in the same lane
-  static constexpr int Z_WORDS = NS * 64;
+  // z: one operand per k-step whose even rows hold z's bf16 hi parts and odd
+  // rows its lo parts, so output rows 4g and 4g + 1 of a product are the hi
+  // and lo parts of den in the same lane; the rows of a parity are the same,
+  // so lane (g, m) reads word 2g + (m & 1)
+  static constexpr int Z_WORDS = NS * 8;
   static constexpr int SLOT = S_WORDS + Z_WORDS;
   // four waves per apply workgroup: two workgroups share a compute unit
-  // (the eight slots take 80 KiB of LDS at d = 64), so one's staging
-  // overlaps the other's streaming (3.75 -> 3.29 ms against eight waves)
+  // (the eight slots and the window take 78 KiB of LDS at d = 64), so one's
+  // staging overlaps the other's streaming (3.75 -> 3.29 ms against eight
+  // waves)
   static constexpr int WAVES = 4, TT = 2;
+  // window weights of a cell's coordinates kept in LDS (three dimensions
+  // together); longer cells take the sine for every token
+  static constexpr int WINDOW = 1536;
   static constexpr int QW = Q4 * 2 / 4;         // words of a lane's query run
 };
 
@@ -190,8 +201,14 @@ __device__ __forceinline__ void col_step(const SummaryRegs<DT_BF16, D, MODE_FWD>
 // by side.  The bound of one wave per SIMD lets the compiler keep the two
 // tiles' sums in the accumulation registers: at d = 64 it takes 242
 // registers in all, so two waves per SIMD still run; held to two waves per
-// SIMD it kept them in the vector registers and spilled (5 % slower)
-template <int D>
+// SIMD it kept them in the vector registers and spilled (5 % slower).
+// A walk visits the same (y, x) positions in every plane, so with TABLE it
+// keeps their clamped offsets in LDS and each load takes a scalar plane base
+// and one lane offset; clamping and indexing every token of every plane
+// instead took 220 of 530 vector instructions a step (16 planes of the 32 x
+// 64 patch grid, 8 heads of d = 32: 19.4 -> 16.2 us).  What bounds the long
+// walks is memory (2.09 ms at the geometry below either way, 4.9 TB/s).
+template <int D, bool TABLE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1)))
 void tile_cols_kernel(TGeo g, const void* __restrict__ k, const void* __restrict__ v,
                       float* __restrict__ cols) {
@@ -200,16 +217,19 @@ void tile_cols_kernel(TGeo g, const void* __restrict__ k, const void* __restrict
   constexpr int F = C::F, R = C::R, STEP = C::STEP, E = D * D + D;
   const int lane = threadIdx.x & 63;
   const int gq = lane >> 4, m = lane & 15;
-  const int64_t item = (int64_t)blockIdx.x * 4 + wave_index();
-  if (item >= g.n_items) return;  // uniform over the wave
-  const int64_t head = item % g.H;
-  int64_t rest = item / g.H;
-  const int f = (int)(rest % g.Pf);
-  rest /= g.Pf;
-  const int64_t sx = rest % g.ns[2];
-  rest /= g.ns[2];
-  const int64_t sy = rest % g.ns[1];
-  const int64_t q = rest / g.ns[1];
+  // indices fit 32 bits (the host bounds the items; 64-bit divisions took
+  // some 700 instructions here)
+  const uint32_t item = blockIdx.x * 4 + (uint32_t)wave_index();
+  if (item >= (uint64_t)g.n_items) return;  // uniform over the wave
+  uint32_t rest = item / (uint32_t)g.H;
+  const uint32_t head = item - rest * (uint32_t)g.H;
+  uint32_t next = rest / (uint32_t)g.Pf;
+  const int f = (int)(rest - next * (uint32_t)g.Pf);
+  rest = next;
+  next = rest / (uint32_t)g.ns[2];
+  const uint32_t sx = rest - next * (uint32_t)g.ns[2];
+  const uint32_t q = next / (uint32_t)g.ns[1];
+  const uint32_t sy = next - q * (uint32_t)g.ns[1];
   int32_t ys, xs;
   uint32_t xw, p0, p1;
   if (!col_part(g, sy, sx, f, ys, xs, xw, p0, p1)) return;  // uniform
@@ -221,34 +241,56 @@ void tile_cols_kernel(TGeo g, const void* __restrict__ k, const void* __restrict
   const int64_t total = (int64_t)(t_stop - t_first) * spp;
 
   const int64_t rowb = g.C * 2;  // bytes per token of a field
-  const char* kb = (const char*)k + head * D * 2 + (int64_t)(F * m) * 2;
-  const char* vb = (const char*)v + head * D * 2 + (int64_t)(F * m) * 2;
+  const char* kb = (const char*)k + head * D * 2;
+  const char* vb = (const char*)v + head * D * 2;
+  const uint32_t fm = (uint32_t)(F * m) * 2;  // the lane's features
   const int32_t M0 = (int32_t)g.dims[0] - 1, M1 = (int32_t)g.dims[1] - 1,
                 M2 = (int32_t)g.dims[2] - 1;
   const uint32_t N1 = (uint32_t)g.dims[1], N2 = (uint32_t)g.dims[2];
   const uint32_t neg_inf = 0xff80ff80u;
+  // offsets of the part's positions within a plane, a wave's own
+  __shared__ __align__(16) uint32_t tables[TABLE ? 4 * kTable : 4];
+  uint32_t* table = tables + (TABLE ? wave_index() * kTable : 0);
+  const int64_t plane = (int64_t)N1 * N2 * rowb;
+  if constexpr (TABLE) {
+    for (uint32_t i = lane; i < spp * STEP; i += 64) {
+      const uint32_t j = min(p0 + i, p1 - 1), uy = j / xw, ux = j - uy * xw;
+      table[i] = (clamp32(ys + (int32_t)uy, M1) * N2 + clamp32(xs + (int32_t)ux, M2)) * (uint32_t)rowb;
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
   // the step js of plane t: lane group gq takes footprint positions
   // p0 + STEP*js + R*gq + r; 32-bit coordinates (a field holds fewer
   // than 2^31 tokens).  Every load is issued: positions past the part's
   // end are clamped into the grid like all others, and the step drops
-  // them (bit r of the lane's mask is clear), so no branch stands between
-  // a step's loads and the compiler's count of them
-  auto load = [&](int32_t t, uint32_t js, Regs& x, uint32_t& mask) {
+  // them, so no branch stands between a step's loads and the compiler's
+  // count of them
+  auto load = [&](int32_t t, uint32_t js, Regs& x) {
+    const uint32_t gt = clamp32(t, M0);
+    if constexpr (TABLE) {
+      const u32x4* at = (const u32x4*)(table + STEP * js + R * gq);
+      const u32x4 o[2] = {at[0], at[1]};
+      const char *kp = kb + gt * plane, *vp = vb + gt * plane;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const uint32_t off = o[r >> 2][r & 3] + fm;
+        load_words<C::KB>(kp + off, x.kw[r]);
+        load_words<C::VB>(vp + off, x.vw[r]);
+      }
+      return;
+    }
     const uint32_t j = p0 + STEP * js + R * gq;
     uint32_t uy = j / xw;
     uint32_t ux = j - uy * xw;
-    const uint32_t gt = clamp32(t, M0);
-    mask = 0;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      mask |= (uint32_t)(j + r < p1) << r;
       const uint32_t gy = clamp32(ys + (int32_t)uy, M1);
       const uint32_t gx = clamp32(xs + (int32_t)ux, M2);
       const int64_t off = (int64_t)((gt * N1 + gy) * N2 + gx) * rowb;
       // plain loads (non-temporal ones ran 1 % slower here, and the slot
       // pass after them 10 % slower)
-      load_words<C::KB>(kb + off, x.kw[r]);
-      load_words<C::VB>(vb + off, x.vw[r]);
+      load_words<C::KB>(kb + off + fm, x.kw[r]);
+      load_words<C::VB>(vb + off + fm, x.vw[r]);
       if (++ux == xw) {
         ux = 0;
         ++uy;
@@ -269,12 +311,12 @@ void tile_cols_kernel(TGeo g, const void* __restrict__ k, const void* __restrict
     }
   }
   int64_t a = a0;  // the tile whose sum is ac; an is tile a + 1's
-  auto process = [&](Regs& x, uint32_t mask, int32_t t, uint32_t js) {
+  auto process = [&](Regs& x, int32_t t, uint32_t js) {
     if (p0 + STEP * (js + 1) > p1) {  // a part's last, partial step (wave-uniform)
       // dropped positions: phi(-inf) = 0 and v = 0 add nothing
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        const bool keep = (mask >> r) & 1u;
+        const bool keep = p0 + STEP * js + R * gq + r < p1;
 #pragma unroll
         for (int w = 0; w < C::KW; ++w) x.kw[r][w] = keep ? x.kw[r][w] : neg_inf;
 #pragma unroll
@@ -322,20 +364,19 @@ void tile_cols_kernel(TGeo g, const void* __restrict__ k, const void* __restrict
     if (lt != t_stop - 1 || ljs != spp - 1) advance(lt, ljs);
   };
   Regs ra, rb;
-  uint32_t ma, mb;
-  load(lt, ljs, ra, ma);
+  load(lt, ljs, ra);
   advance_load();
   for (int64_t s = 0; s < total; s += 2) {
-    load(lt, ljs, rb, mb);
+    load(lt, ljs, rb);
     advance_load();
     __builtin_amdgcn_sched_barrier(0);
-    process(ra, ma, ct, cjs);
+    process(ra, ct, cjs);
     advance(ct, cjs);
-    load(lt, ljs, ra, ma);
+    load(lt, ljs, ra);
     advance_load();
     __builtin_amdgcn_sched_barrier(0);
     if (s + 1 < total) {
-      process(rb, mb, ct, cjs);
+      process(rb, ct, cjs);
       advance(ct, cjs);
     }
   }
@@ -349,25 +390,31 @@ void tile_slot_kernel(TGeo g, const float* __restrict__ cols, u32x4* __restrict_
   using RB = Run<D, DT_BF16>;
   constexpr int F = D / 16, E = D * D + D;
   static_assert(E % 4 == 0, "whole 16-byte groups of a partial");
-  const int64_t tile = blockIdx.x / g.H;
-  const int64_t head = blockIdx.x % g.H;
-  const int64_t a = tile / (g.n[1] * g.n[2]), b = (tile / g.n[2]) % g.n[1], c = tile % g.n[2];
-  // the tile's column partials (at most 9 x 8), in a fixed order
+  const uint32_t tile = blockIdx.x / (uint32_t)g.H, head = blockIdx.x - tile * (uint32_t)g.H;
+  const uint32_t nx = (uint32_t)g.n[2], ny = (uint32_t)g.n[1];
+  const uint32_t ab = tile / nx, c = tile - ab * nx, a = ab / ny, b = ab - a * ny;
+  // the tile's column partials (at most 9 x 8), in a fixed order: thread k
+  // looks at the k-th of the tile's 9 segment pairs times Pf parts
   __shared__ int64_t src[9 * 8];
-  __shared__ int nsrc;
-  if (threadIdx.x == 0) {
-    int n = 0;
-    for (int64_t sy = 2 * b; sy <= 2 * b + 2; ++sy)
-      for (int64_t sx = 2 * c; sx <= 2 * c + 2; ++sx)
-        for (int f = 0; f < g.Pf; ++f) {
-          int32_t ys, xs;
-          uint32_t xw, p0, p1;
-          if (col_part(g, sy, sx, f, ys, xs, xw, p0, p1)) src[n++] = col_index(g, a, sy, sx, f, head) * E;
-        }
-    nsrc = n;
+  __shared__ uint64_t live[2];
+  const int k = threadIdx.x;
+  const int pair = k / g.Pf, f = k - pair * g.Pf;
+  const int64_t sy = 2 * (int64_t)b + pair / 3, sx = 2 * (int64_t)c + pair % 3;
+  bool has = false;
+  if (k < 9 * g.Pf) {
+    int32_t ys, xs;
+    uint32_t xw, p0, p1;
+    has = col_part(g, sy, sx, f, ys, xs, xw, p0, p1);
+  }
+  const uint64_t m = __ballot(has);
+  if (k < 128 && (k & 63) == 0) live[k >> 6] = m;
+  __syncthreads();
+  if (has) {
+    const int before = (k >= 64 ? __popcll(live[0]) : 0) + __popcll(m & ((1ull << (k & 63)) - 1));
+    src[before] = col_index(g, a, sy, sx, f, head) * E;
   }
   __syncthreads();
-  const int ns = nsrc;
+  const int ns = __popcll(live[0]) + __popcll(live[1]);
   // FP64 sum of the column partials, four consecutive elements per thread
   // (16-byte loads of every partial in flight together); element u of the
   // partial layout (tile (i, j), lane (g, n), register r: S[F(4g + r) + i]
@@ -408,16 +455,16 @@ void tile_slot_kernel(TGeo g, const float* __restrict__ cols, u32x4* __restrict_
         const int cc = u - D * D;
         const uint16_t lo = to_bf16((float)(sum[r4] - (double)bf16f(hi)));
         const int kp = RB::pos(cc);
-        for (int mm = 0; mm < 16; ++mm) {
-          const int word = TC::S_WORDS + (kp >> 3) * 64 + 16 * RB::group(cc) + mm;
-          slot[word * 8 + (kp & 7)] = (mm & 1) ? lo : hi;
+        for (int par = 0; par < 2; ++par) {
+          const int word = TC::S_WORDS + (kp >> 3) * 8 + 2 * RB::group(cc) + par;
+          slot[word * 8 + (kp & 7)] = par ? lo : hi;
           if (TC::Q4 < 8) slot[word * 8 + (kp & 7) + 4] = 0;
         }
       }
     }
   }
   __syncthreads();
-  u32x4* dst = slots + (tile * g.H + head) * TC::SLOT;
+  u32x4* dst = slots + ((int64_t)tile * g.H + head) * TC::SLOT;
   for (int w = threadIdx.x; w < TC::SLOT; w += 256) dst[w] = simg[w];
 }
 
@@ -429,8 +476,12 @@ void tile_slot_kernel(TGeo g, const float* __restrict__ cols, u32x4* __restrict_
 // tile (jt - 1 + st, jy - 1 + sy, jx - 1 + sx) if it exists: the S^T hi
 // parts (S_t to about 2^-9) and the hi / lo z tile.  The waves take the
 // cell's 16-token tiles (row-major over the cell) two at a time.  The
-// eight slots take 80 KiB of LDS at d = 64, so two workgroups share a
-// compute unit and one's staging overlaps the other's streaming.
+// eight slots and the window table take 78 KiB of LDS at d = 64, so two
+// workgroups share a compute unit and one's staging overlaps the other's
+// streaming.  T256 x 64 x 128, 16 heads of d = 64, cores 8 x 16 x 16, halos
+// 2 x 4 x 4: 2.15 ms, 2.38 with each token's coordinates divided out and its
+// six sines taken anew; bound by issue (750 vector and up to 160 matrix
+// instructions per 32 tokens) as much as by HBM.
 // ---------------------------------------------------------------------------
 
 template <int D>
@@ -438,128 +489,129 @@ __global__ __launch_bounds__(64 * TiledCfg<D>::WAVES) __attribute__((amdgpu_wave
 void tile_apply_kernel(TGeo g, const void* __restrict__ q, void* __restrict__ o,
                        const void* __restrict__ img) {
   using TC = TiledCfg<D>;
-  using IC = ImageCfg<D>;
   using RN = Run<D, DT_BF16>;
   constexpr int NT = TC::NT, NS = TC::NS, Q4 = TC::Q4, TT = TC::TT, QW = TC::QW;
   __shared__ u32x4 simg[8 * TC::SLOT];
+  __shared__ f32x2 window[TC::WINDOW];
 
   // one workgroup per (cell, head), cell fastest: neighbouring cells share
   // covering tiles, whose operand slots they then stage from L2 (head
-  // fastest ran 1.5 % slower)
-  const int64_t head = blockIdx.x / g.n_cells;
-  const int64_t cell = blockIdx.x % g.n_cells;
-  const int64_t jc[3] = {cell / (g.cells[1] * g.cells[2]), (cell / g.cells[2]) % g.cells[1],
-                         cell % g.cells[2]};
-  int64_t lo[3], ext[3];
+  // fastest ran 1.5 % slower).  Indices fit 32 bits (the host bounds them).
+  const uint32_t nc = (uint32_t)g.n_cells;
+  const uint32_t head = blockIdx.x / nc, cell = blockIdx.x - head * nc;
+  const uint32_t c2 = (uint32_t)g.cells[2], c1 = (uint32_t)g.cells[1];
+  const uint32_t c01 = cell / c2;
+  const int32_t jc[3] = {(int32_t)(c01 / c1), (int32_t)(c01 % c1), (int32_t)(cell - c01 * c2)};
+  // the cell's first coordinates and extents; its two covering tiles'
+  // origins per dimension (-1 << 30 marks a tile outside the grid: weight 0)
+  int32_t lo[3], ext[3], org[3][2], Lk[3];
+  float inv2L[3];
+  uint32_t exists[3];
+#pragma unroll
   for (int k = 0; k < 3; ++k) {
-    const int64_t a = g.core[k] / 2;
-    const int64_t s0 = jc[k] * g.core[k] - a;
-    lo[k] = max(s0, (int64_t)0);
-    ext[k] = min(s0 + g.core[k], g.dims[k]) - lo[k];
+    const int32_t core = (int32_t)g.core[k], dim = (int32_t)g.dims[k];
+    const int64_t s0 = (int64_t)jc[k] * core - core / 2;
+    lo[k] = (int32_t)max(s0, (int64_t)0);
+    ext[k] = (int32_t)(min(s0 + core, (int64_t)dim) - lo[k]);
+    Lk[k] = (int32_t)g.L[k];
+    inv2L[k] = 0.5f / (float)Lk[k];
+    exists[k] = 0;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int32_t tix = jc[k] - 1 + u;
+      const bool in = tix >= 0 && tix < (int32_t)g.n[k];
+      org[k][u] = in ? tix * core - (int32_t)g.halo[k] : -(1 << 30);
+      exists[k] |= (uint32_t)in << u;
+    }
   }
   if (ext[0] <= 0 || ext[1] <= 0 || ext[2] <= 0) return;  // uniform over the workgroup
-  const int64_t vol = ext[0] * ext[1] * ext[2];
+  const uint32_t E0 = (uint32_t)ext[0], E1 = (uint32_t)ext[1], E2 = (uint32_t)ext[2];
+  const uint32_t VOL = E0 * E1 * E2;  // at most 65,536 (a tile's tokens)
 
   const int lane = threadIdx.x & 63, wave = wave_index();
   const int gl = lane >> 4, n = lane & 15;
   const int64_t rowb = g.C * 2;
   const char* qh = (const char*)q + head * D * 2;
   char* oh = (char*)o + head * D * 2;
-
-  // per lane: token e of the cell -> grid position, field offset and the
-  // Hann weights of the (up to) two covering tiles per dimension.  32-bit
-  // coordinates (a cell holds fewer than 65,536 tokens, the field fewer
-  // than 2^31); the covering tiles' origins are the same for the whole
-  // workgroup (origin -1 << 30 marks a tile outside the grid: weight 0)
-  struct Tok {
-    int64_t off;
-    float wt[2], wy[2], wx[2];
-    bool ok;
-  };
-  const uint32_t E1 = (uint32_t)ext[1], E2 = (uint32_t)ext[2], E12 = E1 * E2;
-  const uint32_t VOL = (uint32_t)vol;
-  const int32_t P0 = (int32_t)lo[0], P1 = (int32_t)lo[1], P2 = (int32_t)lo[2];
   const uint32_t N1 = (uint32_t)g.dims[1], N2 = (uint32_t)g.dims[2];
-  int32_t org[3][2], Lk[3];
-  float inv2L[3];
-  for (int k = 0; k < 3; ++k) {
-    Lk[k] = (int32_t)g.L[k];
-    inv2L[k] = 0.5f / (float)g.L[k];
-    for (int sidx = 0; sidx < 2; ++sidx) {
-      const int64_t tix = jc[k] - 1 + sidx;
-      org[k][sidx] = (tix >= 0 && tix < g.n[k]) ? (int32_t)(tix * g.core[k] - g.halo[k]) : -(1 << 30);
-    }
-  }
-  auto locate = [&](int64_t e64) {
-    Tok t;
-    const uint32_t e = (uint32_t)e64;
-    t.ok = e64 < (int64_t)VOL;
-    const uint32_t ee = t.ok ? e : VOL - 1;
-    const uint32_t a0 = ee / E12, r0 = ee - a0 * E12;
-    const uint32_t a1 = r0 / E2, a2 = r0 - a1 * E2;
-    const int32_t p[3] = {P0 + (int32_t)a0, P1 + (int32_t)a1, P2 + (int32_t)a2};
-    t.off = (int64_t)(((uint32_t)p[0] * N1 + (uint32_t)p[1]) * N2 + (uint32_t)p[2]) * rowb;
-    float* w[3] = {t.wt, t.wy, t.wx};
-#pragma unroll
-    for (int k = 0; k < 3; ++k)
-#pragma unroll
-      for (int sidx = 0; sidx < 2; ++sidx) w[k][sidx] = hann_w(p[k] - org[k][sidx], Lk[k], inv2L[k]);
-    return t;
-  };
 
-  const int64_t ntile = (vol + 15) / 16;
-  const int64_t per_step = (int64_t)TC::WAVES * TT;
-  // two register sets in turn: a step's queries are loaded while the
-  // previous step computes
+  // A lane's token of the cell (row-major): its coordinates walk on by the
+  // workgroup's step with carries (no divisions).  Two sets of queries in
+  // turn: a step's are loaded while the previous step computes.
+  constexpr uint32_t STRIDE = 16 * TT * TC::WAVES;
+  const uint32_t st0 = STRIDE / (E1 * E2), st1 = STRIDE / E2 % E1, st2 = STRIDE % E2;
+  struct Pos {
+    uint32_t e, a0, a1, a2;
+  };
+  Pos pos[TT];
+#pragma unroll
+  for (int u = 0; u < TT; ++u) {
+    const uint32_t e = (uint32_t)(wave * TT + u) * 16 + n;
+    const uint32_t r = e / E2;
+    pos[u] = Pos{e, r / E1, r % E1, e - r * E2};
+  }
   struct Step {
-    Tok tk[TT];
+    uint32_t a0[TT], a1[TT], a2[TT];
+    bool ok[TT];
+    int64_t off[TT];
     uint32_t qw[TT][QW];
   };
-  auto fetch = [&](int64_t base, Step& x) {
+  // past the cell's end the coordinates stay inside it (no branch around
+  // the loads); such tokens are not ok: no weight, nothing stored
+  auto fetch = [&](Step& x) {
 #pragma unroll
     for (int u = 0; u < TT; ++u) {
-      x.tk[u] = locate((base + u) * 16 + n);
-      load_run<D, DT_BF16>(qh + x.tk[u].off + gl * RN::CB, x.qw[u]);
+      Pos& t = pos[u];
+      x.ok[u] = t.e < VOL;
+      x.a0[u] = min(t.a0, E0 - 1);
+      x.a1[u] = t.a1;
+      x.a2[u] = t.a2;
+      x.off[u] = (int64_t)(((lo[0] + x.a0[u]) * N1 + lo[1] + t.a1) * N2 + lo[2] + t.a2) * rowb;
+      load_run<D, DT_BF16>(qh + x.off[u] + gl * RN::CB, x.qw[u]);
+      t.e += STRIDE;
+      t.a2 += st2;
+      const bool c2 = t.a2 >= E2;
+      t.a2 -= c2 ? E2 : 0;
+      t.a1 += st1 + c2;
+      const bool c1 = t.a1 >= E1;
+      t.a1 -= c1 ? E1 : 0;
+      t.a0 += st0 + c1;
     }
   };
-  // fetches past the cell's end locate its last token again (no branch
-  // around the loads); such tokens are not ok: no weight, nothing stored
   Step sa, sb;
-  const int64_t base0 = (int64_t)wave * TT;
-  fetch(base0, sa);
+  fetch(sa);
 
-  // stage the covering tiles' operands (the first queries are in flight):
-  // every load of a thread is issued before its LDS stores (in two rounds
-  // of loads, then stores, to bound the registers held)
-  {
-    constexpr int NTH = 64 * TC::WAVES;
-    constexpr int PER = (8 * TC::SLOT + NTH - 1) / NTH;  // words per thread
-    constexpr int HALF = (PER + 1) / 2;
-#pragma unroll
-    for (int r0 = 0; r0 < PER; r0 += HALF) {
-      u32x4 buf[HALF];
-#pragma unroll
-      for (int i = 0; i < HALF; ++i) {
-        const int w = threadIdx.x + NTH * (r0 + i);
-        const int s = w / TC::SLOT, ws = w % TC::SLOT;
-        const int64_t tt = jc[0] - 1 + (s >> 2), ty = jc[1] - 1 + ((s >> 1) & 1), tx = jc[2] - 1 + (s & 1);
-        const bool ok = r0 + i < PER && w < 8 * TC::SLOT && tt >= 0 && tt < g.n[0] && ty >= 0 &&
-                        ty < g.n[1] && tx >= 0 && tx < g.n[2];
-        if (ok) buf[i] = ((const u32x4*)img)[(((tt * g.n[1] + ty) * g.n[2] + tx) * g.H + head) * TC::SLOT + ws];
-      }
-#pragma unroll
-      for (int i = 0; i < HALF; ++i) {
-        const int w = threadIdx.x + NTH * (r0 + i);
-        if (r0 + i < PER && w < 8 * TC::SLOT) simg[w] = buf[i];  // slots of missing tiles are never read
-      }
-    }
-  }
-  // the slots whose tile exists (the same for every thread)
-  int vmask = 0;
+  // stage the covering tiles' operands straight into LDS, 1 KB a wave
+  // instruction (the first queries are in flight); slots of missing tiles
+  // are never read
+  const uint32_t vmask = [&] {
+    uint32_t m = 0;
+    for (int s = 0; s < 8; ++s)
+      m |= (exists[0] >> (s >> 2) & exists[1] >> ((s >> 1) & 1) & exists[2] >> (s & 1) & 1u) << s;
+    return m;
+  }();
   for (int s = 0; s < 8; ++s) {
-    const int64_t tt = jc[0] - 1 + (s >> 2), ty = jc[1] - 1 + ((s >> 1) & 1), tx = jc[2] - 1 + (s & 1);
-    if (tt >= 0 && tt < g.n[0] && ty >= 0 && ty < g.n[1] && tx >= 0 && tx < g.n[2]) vmask |= 1 << s;
+    if (!(vmask >> s & 1)) continue;
+    const int64_t tile = ((int64_t)(jc[0] - 1 + (s >> 2)) * g.n[1] + (jc[1] - 1 + ((s >> 1) & 1))) * g.n[2] +
+                         (jc[2] - 1 + (s & 1));
+    const u32x4* src = (const u32x4*)img + (tile * g.H + head) * TC::SLOT;
+    for (int w = wave * 64; w < TC::SLOT; w += 64 * TC::WAVES)
+      if (w + lane < TC::SLOT)
+        __builtin_amdgcn_global_load_lds((const void*)(src + w + lane), (lds_void_ptr)(simg + s * TC::SLOT + w),
+                                         16, 0, 0);
   }
+  // the window weights of the cell's coordinates, both covering tiles'
+  const bool table = E0 + E1 + E2 <= (uint32_t)TC::WINDOW;
+  auto weights = [&](int k, uint32_t a) {
+    const int32_t p = lo[k] + (int32_t)a;
+    return f32x2{hann_w(p - org[k][0], Lk[k], inv2L[k]), hann_w(p - org[k][1], Lk[k], inv2L[k])};
+  };
+  if (table)
+    for (uint32_t i = threadIdx.x; i < E0 + E1 + E2; i += 64 * TC::WAVES)
+      window[i] = i < E0 ? weights(0, i) : i < E0 + E1 ? weights(1, i - E0) : weights(2, i - E0 - E1);
+  // the loads into LDS count as vector memory operations: all have landed
+  // before the barrier
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
 
   auto compute = [&](const Step& x) {
@@ -580,19 +632,34 @@ void tile_apply_kernel(TGeo g, const void* __restrict__ q, void* __restrict__ o,
         bq[u][s] = as_bf16x8(w);
       }
     float oacc[TT][Q4], wacc[TT];
+    f32x2 wx[TT];
+    float wty[TT][4];
 #pragma unroll
     for (int u = 0; u < TT; ++u) {
+      f32x2 wt, wy;
+      if (table) {
+        wt = window[x.a0[u]];
+        wy = window[E0 + x.a1[u]];
+        wx[u] = window[E0 + E1 + x.a2[u]];
+      } else {
+        wt = weights(0, x.a0[u]);
+        wy = weights(1, x.a1[u]);
+        wx[u] = weights(2, x.a2[u]);
+      }
+#pragma unroll
+      for (int s = 0; s < 4; ++s) wty[u][s] = x.ok[u] ? wt[s >> 1] * wy[s & 1] : 0.f;
       wacc[u] = 0.f;
 #pragma unroll
       for (int c = 0; c < Q4; ++c) oacc[u][c] = 0.f;
     }
+#pragma unroll
     for (int s = 0; s < 8; ++s) {
       if (!((vmask >> s) & 1)) continue;
       float ws[TT];
       bool any = false;
 #pragma unroll
       for (int u = 0; u < TT; ++u) {
-        ws[u] = x.tk[u].ok ? x.tk[u].wt[s >> 2] * x.tk[u].wy[(s >> 1) & 1] * x.tk[u].wx[s & 1] : 0.f;
+        ws[u] = wty[u][s >> 1] * wx[u][s & 1];
         any |= ws[u] > 0.f;
       }
       if (!__any(any)) continue;  // no token of these tiles in this slot's tile
@@ -610,7 +677,7 @@ void tile_apply_kernel(TGeo g, const void* __restrict__ q, void* __restrict__ o,
         }
 #pragma unroll
       for (int ks = 0; ks < NS; ++ks) {
-        const bf16x8 z2 = as_bf16x8(zt[ks * 64 + lane]);
+        const bf16x8 z2 = as_bf16x8(zt[ks * 8 + 2 * gl + (n & 1)]);
 #pragma unroll
         for (int u = 0; u < TT; ++u)
           acc[u][NT] = mfma_bf16(z2, bq[u][ks], ks == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[u][NT]);
@@ -630,12 +697,12 @@ void tile_apply_kernel(TGeo g, const void* __restrict__ q, void* __restrict__ o,
     }
 #pragma unroll
     for (int u = 0; u < TT; ++u) {
-      if (!x.tk[u].ok) continue;
+      if (!x.ok[u]) continue;
       const float rw = __builtin_amdgcn_rcpf(wacc[u]);
       float out[Q4];
 #pragma unroll
       for (int c = 0; c < Q4; ++c) out[c] = oacc[u][c] * rw;
-      store_run<D, DT_BF16, DT_BF16>(oh + x.tk[u].off + gl * RN::CH * 2, out);
+      store_run<D, DT_BF16, DT_BF16>(oh + x.off[u] + gl * RN::CH * 2, out);
     }
   };
 
@@ -645,12 +712,13 @@ void tile_apply_kernel(TGeo g, const void* __restrict__ q, void* __restrict__ o,
   // that step's queries, not the next step's nor the previous outputs'
   // stores; the scheduling barriers keep each fetch ahead of the step it
   // overlaps
-  const int64_t nsteps = base0 < ntile ? (ntile - 1 - base0) / per_step + 1 : 0;
-  for (int64_t k = 0; k < nsteps; k += 2) {
-    fetch(base0 + (k + 1) * per_step, sb);
+  const uint32_t first = (uint32_t)wave * TT * 16;
+  const uint32_t nsteps = first < VOL ? (VOL - 1 - first) / STRIDE + 1 : 0;
+  for (uint32_t k = 0; k < nsteps; k += 2) {
+    fetch(sb);
     __builtin_amdgcn_sched_barrier(0);
     compute(sa);
-    fetch(base0 + (k + 2) * per_step, sa);
+    fetch(sa);
     __builtin_amdgcn_sched_barrier(0);
     compute(sb);
   }
@@ -703,6 +771,9 @@ la_status make_tgeo(const la_tile_desc* td, int64_t heads, TGeo* g) {
   while (g->L[0] * ((fpmax + Pf - 1) / Pf) > 16384) ++Pf;
   if (Pf > 8) return LA_ERR_UNSUPPORTED;
   g->Pf = Pf;
+  // steps of 32 positions; offsets within a plane in 32 bits
+  g->table = (((fpmax + Pf - 1) / Pf + 31) / 32) * 32 <= kTable &&
+             g->dims[1] * g->dims[2] * g->C * 2 < (int64_t(1) << 32);
   // t chunks: enough column walks to fill the machine a few times over;
   // each chunk re-reads the planes its first tile shares with the one
   // before (2 halo of every CH * core)
@@ -745,8 +816,9 @@ hipError_t launch_tiled(const TGeo& g, const TLayout& L, const void* q, const vo
                         const void* v, void* o, char* ws, hipStream_t st) {
   {
     ProfScope prof("tile_cols", st);
-    hipLaunchKernelGGL(tile_cols_kernel<D>, dim3((unsigned)((g.n_items + 3) / 4)), dim3(256), 0, st,
-                       g, k, v, (float*)(ws + L.cols));
+    const dim3 grid((unsigned)((g.n_items + 3) / 4));
+    if (g.table) tile_cols_kernel<D, true><<<grid, 256, 0, st>>>(g, k, v, (float*)(ws + L.cols));
+    else tile_cols_kernel<D, false><<<grid, 256, 0, st>>>(g, k, v, (float*)(ws + L.cols));
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

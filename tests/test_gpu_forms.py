@@ -179,3 +179,22 @@ def test_backward_forms(layout, d, N):
     torch.cuda.synchronize()
     for x, y in zip(got, alone):
         assert torch.equal(x[:, H - 1:], y)
+
+
+# the tiled step where its kernels change: footprints of 512 positions and
+# one more (offsets kept in LDS or not), cells longer than the window table,
+# a cell's last 16-token tile, one position per cell row
+@pytest.mark.parametrize("dims,core,halo,H,d", [
+    ((3, 16, 64), (2, 16, 32), (1, 0, 0), 2, 32), ((3, 16, 66), (2, 16, 33), (1, 0, 0), 2, 32),
+    ((1, 1, 3300), (1, 1, 3300), (0, 0, 40), 2, 16), ((1, 3, 3000), (1, 2, 1500), (0, 1, 700), 1, 32),
+    ((5, 7, 3), (2, 3, 1), (1, 1, 0), 3, 64), ((9, 4, 17), (3, 4, 16), (1, 2, 8), 1, 64)])
+def test_tiled_forms(dims, core, halo, H, d):
+    from test_gpu_tiles import oracle_tiled
+    dev = require_gpu()
+    q, k, v = make_inputs((1, 1, dims[0] * dims[1] * dims[2], H * d), "bf16", seed=60)
+    shape = tuple(dims) + (H, d)
+    o = la.tiled_forward(*(to_device(x, dev).view(shape) for x in (q, k, v)), core, halo)
+    torch.cuda.synchronize()
+    flat = tuple(dims) + (H * d,)
+    ref = oracle_tiled(*(x.reshape(flat) for x in (q, k, v)), dims, core, halo, H, d)
+    assert normwise(as64(o).reshape(1, 1, -1), ref.reshape(1, 1, -1)) < TOL["bf16"]
