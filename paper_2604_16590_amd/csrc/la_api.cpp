@@ -83,21 +83,33 @@ int64_t fused_partials(int64_t N, int d) {
                   std::min<int64_t>(4, ceil_div(N, 4 * d)));
 }
 
-// The summary: a partial's write and read cost 2 (d + 1) * 4 bytes against
-// 2 * es bytes of K and V a token and feature, so a partial of 32 d bf16
-// tokens adds 6 % and is the rule (16 d in fp32: the same bytes).  Short
-// sequences take up to four (fp32: sixteen) shorter ones, not below 4 d (2 d)
-// tokens, so that a few heads still fill compute units: one head of 4,096
-// fp32 tokens (d = 64) takes 14 us in sixteen partials and 21 in eight, while
-// 1,024 heads of 8,192 bf16 tokens take 396 + 94 us (summary + combine) in
-// four and 430 + 110 in eight.  bf16 at d <= 32 gives a partial to a single
-// wave (see the kernel): 512 tokens, or up to sixteen of at least 4 d.
+// bf16 summaries with four waves to a partial: sequences too short for
+// max_partials of a single wave's 2048 (d = 128) or 512 tokens.  Longer ones
+// keep the SIMDs streaming with a wave to a partial, whose four waves of a
+// workgroup, four heads of a token range, read a BNHD view best (8 x 8 heads
+// of 63,607 tokens at d = 64, BNHD: 200 us, 224 with teams).  At d <= 32
+// heads of a BNHD view share cache lines, and it is the better form for all
+// (d = 32, 8 heads of 30,001 tokens: 34 us, 38).
+bool team_summary(int64_t N, int d, int dt) {
+  return dt == LA_BF16 && d >= 64 && N <= max_partials(d) * (d >= 128 ? 2048 : 512);
+}
+
+// The summary's partials.  A partial's write and read cost 2 (d + 1) * 4
+// bytes against 2 * es bytes of K and V a token and feature, so a partial of
+// 32 d bf16 tokens adds 6 % and is the rule of the teams (16 d in fp32: the
+// same bytes).  Short sequences take up to four (fp32: sixteen) shorter ones,
+// not below 4 d (2 d) tokens, so that a few heads still fill compute units:
+// one head of 4,096 fp32 tokens (d = 64) takes 14 us in sixteen partials and
+// 21 in eight, while 1,024 heads of 8,192 bf16 tokens take 396 + 94 us
+// (summary + combine) in four and 430 + 110 in eight.  A single wave's
+// partials: 2048 (512) tokens, at d <= 32 up to sixteen of at least 4 d.
 int64_t summary_partials(int64_t N, int d, int dt) {
-  const bool single = dt == LA_BF16 && d <= 32;
   const int64_t unit = dt == LA_BF16 ? 4 * d : 2 * d;
-  const int64_t few = single || dt == LA_FP32 ? 16 : 4;
-  return std::max(std::min(max_partials(d), ceil_div(N, single ? 512 : 8 * unit)),
-                  std::min(few, ceil_div(N, unit)));
+  if (dt == LA_FP32 || team_summary(N, d, dt))
+    return std::max(std::min(max_partials(d), ceil_div(N, 8 * unit)),
+                    std::min<int64_t>(dt == LA_FP32 ? 16 : 4, ceil_div(N, unit)));
+  return std::max(std::min(max_partials(d), ceil_div(N, d >= 128 ? 2048 : 512)),
+                  std::min<int64_t>(d <= 32 ? 16 : 1, ceil_div(N, unit)));
 }
 
 bool fused_backward(int d, int dt) { return dt == LA_BF16 && d >= 32; }
@@ -228,6 +240,7 @@ la_status forward_impl(const la_attn_desc* desc, const void* q, const void* k, c
   a.osb = desc->out_sb; a.osh = desc->out_sh; a.osn = desc->out_sn;
   a.q = q; a.k = k; a.v = v; a.o = o;
   a.P = t.P; a.Tw = t.Tw;
+  a.team = team_summary(desc->N, (int)desc->d, desc->in_dtype);
   a.Ga = apply_groups(desc->N, desc->B * desc->H);
   a.part = (float*)(w + L.part);
   a.S64 = s_out ? s_out : (double*)(w + L.S64);

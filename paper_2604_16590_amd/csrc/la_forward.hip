@@ -747,26 +747,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
 // ---------------------------------------------------------------------------
 // Host-side launchers
 // ---------------------------------------------------------------------------
-// Four waves share a partial of at most this many tokens.  Longer ones keep
-// the SIMDs streaming by themselves, and there the workgroups' common end
-// costs (8 heads of 2,097,152 tokens at d = 128, 16,384 to a partial: 1.30
-// ms with a wave to a partial, 1.36 with four; 32 heads of 262,144 at
-// d = 64, 4,096 to a partial: the training step 2.22 and 2.26 ms).
-// At d <= 32 a wave keeps its partial: heads of a BNHD view share cache
-// lines there, and a workgroup of four heads reads them through one L1 (d =
-// 32, 8 heads of 30,001 tokens: 34 us, 38 with four waves to a partial).
-constexpr int kTeamTokens = 2048;
-
 template <int DT, int D, int MODE>
 static void launch_summary_t(const void* k, const void* v, int64_t sb, int64_t sh, int64_t sn,
-                             int64_t BH, int64_t H, int64_t N, int P, int Tw,
+                             int64_t BH, int64_t H, int64_t N, int P, int Tw, bool team,
                              const float2* stash, float* part, hipStream_t stream) {
-  using C = SummaryCfg<DT, D, MODE>;
   if constexpr (DT == DT_FP32 && D >= 32) {
     summary_split_kernel<D, MODE><<<dim3((unsigned)((P * BH + 7) / 8 * 8)), 64 * SplitCfg<D>::NW, 0, stream>>>(
         k, v, sb, sh, sn, (int)H, N, P, Tw, stash, part, (int)BH);
-  } else if (D >= 64 && Tw <= kTeamTokens) {
-    if constexpr (D >= 64)
+  } else if (D >= 64 && MODE == MODE_FWD && team) {
+    if constexpr (D >= 64 && MODE == MODE_FWD)
       summary_kernel<DT, D, MODE, SUM_TEAM><<<dim3((unsigned)((P * BH + 7) / 8 * 8)), 256, 0, stream>>>(
           k, v, sb, sh, sn, (int)H, N, P, Tw, stash, part, (int)BH);
   } else {
@@ -778,11 +767,12 @@ static void launch_summary_t(const void* k, const void* v, int64_t sb, int64_t s
 template <int D>
 static void launch_summary_d(int mode, int dt, const void* k, const void* v, int64_t sb,
                              int64_t sh, int64_t sn, int64_t B, int64_t H, int64_t N, int P,
-                             int Tw, const float2* stash, float* part, hipStream_t stream) {
+                             int Tw, bool team, const float2* stash, float* part,
+                             hipStream_t stream) {
   ProfScope prof(mode == MODE_FWD ? "summary_fwd" : "summary_bwd", stream);
   const int64_t BH = B * H;
 #define LA_SUM(DTI, M) \
-  launch_summary_t<DTI, D, M>(k, v, sb, sh, sn, BH, H, N, P, Tw, stash, part, stream)
+  launch_summary_t<DTI, D, M>(k, v, sb, sh, sn, BH, H, N, P, Tw, team, stash, part, stream)
   if (mode == MODE_FWD) {
     if (dt == DT_BF16) LA_SUM(DT_BF16, MODE_FWD); else LA_SUM(DT_FP32, MODE_FWD);
   } else {
@@ -795,10 +785,10 @@ hipError_t launch_summary(int mode, int dt, int D, const void* k, const void* v,
                           int64_t sh, int64_t sn, int64_t B, int64_t H, int64_t N, int P,
                           int Tw, const float2* stash, float* part, hipStream_t stream) {
   switch (D) {
-    case 16: launch_summary_d<16>(mode, dt, k, v, sb, sh, sn, B, H, N, P, Tw, stash, part, stream); break;
-    case 32: launch_summary_d<32>(mode, dt, k, v, sb, sh, sn, B, H, N, P, Tw, stash, part, stream); break;
-    case 64: launch_summary_d<64>(mode, dt, k, v, sb, sh, sn, B, H, N, P, Tw, stash, part, stream); break;
-    case 128: launch_summary_d<128>(mode, dt, k, v, sb, sh, sn, B, H, N, P, Tw, stash, part, stream); break;
+    case 16: launch_summary_d<16>(mode, dt, k, v, sb, sh, sn, B, H, N, P, Tw, false, stash, part, stream); break;
+    case 32: launch_summary_d<32>(mode, dt, k, v, sb, sh, sn, B, H, N, P, Tw, false, stash, part, stream); break;
+    case 64: launch_summary_d<64>(mode, dt, k, v, sb, sh, sn, B, H, N, P, Tw, false, stash, part, stream); break;
+    case 128: launch_summary_d<128>(mode, dt, k, v, sb, sh, sn, B, H, N, P, Tw, false, stash, part, stream); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -835,7 +825,7 @@ template <int D>
 static hipError_t launch_forward_d(const FwdArgs& a) {
   const int BH = (int)(a.B * a.H);
   launch_summary_d<D>(MODE_FWD, a.in_dt, a.k, a.v, a.sb, a.sh, a.sn, a.B, a.H, a.N, a.P, a.Tw,
-                      nullptr, a.part, a.stream);
+                      a.team, nullptr, a.part, a.stream);
   {
     ProfScope prof("combine", a.stream);
     launch_combine_d<D>(a.part, a.P, a.S64, a.z64, a.img, a.in_dt, BH,

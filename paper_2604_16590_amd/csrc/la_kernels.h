@@ -179,6 +179,7 @@ struct FwdArgs {
   const void *q, *k, *v;
   void* o;
   int P, Tw;           // partials per head, tokens per partial
+  bool team;           // bf16 summary: four waves share a partial
   int Ga;              // apply workgroups per head (they take its token blocks in turn)
   float* part;         // [BH][P][D*D + D]: S rows, then z
   double* S64;         // [BH][D][D]

@@ -17,18 +17,19 @@ pytestmark = pytest.mark.gpu
 
 # tokens: one step of four waves (bf16: 32 a wave, fp32: 16) less and more
 # one; around the first second partial (4 d in bf16, 2 d in fp32); for the
-# narrowest heads the last and first counts on either side of 2,048 tokens
-# to a partial (64 partials)
+# narrowest heads the last and first counts of one wave to a partial of 2,048 tokens
+# (64 partials); the longest sequence of four waves to a partial and one more
 SIZES = [(128, "fp32", n) for n in (31, 33, 128, 129, 300)] + [(64, "bf16", n) for n in (31, 127, 128, 129, 256, 257, 8193)] + \
         [(64, "fp32", n) for n in (15, 63, 65, 128, 129, 8193)] + \
         [(128, "bf16", n) for n in (127, 129, 512, 513)] + \
+        [(64, "bf16", 64 * 512), (64, "bf16", 64 * 512 + 1)] + \
         [(16, "bf16", 64 * 2048), (16, "bf16", 64 * 2048 + 1), (32, "fp32", 5 * 64 + 1)]
 
 
 @pytest.mark.parametrize("d,dtype,N", SIZES)
 def test_summary_forms(d, dtype, N):
     dev = require_gpu()
-    B, H = (1, 1) if N > 100000 else (3, 3)  # nine items: not a multiple of eight
+    B, H = (1, 1) if N > 30000 else (3, 3)  # nine items: not a multiple of eight
     q, k, v = make_inputs((B, H, N, d), dtype, seed=500 + N)
     tq, tk, tv = (to_device(x, dev) for x in (q, k, v))
     o, S, z = la.forward(tq, tk, tv, return_summary=True)
