@@ -245,6 +245,7 @@ la_status forward_impl(const la_attn_desc* desc, const void* q, const void* k, c
   a.part = (float*)(w + L.part);
   a.S64 = s_out ? s_out : (double*)(w + L.S64);
   a.z64 = z_out ? z_out : (double*)(w + L.z64);
+  a.want_summary = s_out || z_out;
   a.img = w + L.img;
   a.other = other; a.sigma = sigma; a.sigma_data = sigma_data;
   a.stream = (hipStream_t)stream;

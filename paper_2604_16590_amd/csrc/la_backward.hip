@@ -356,7 +356,7 @@ template <int OT, int D>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 4)))
 void bwd_qds_kernel(const void* __restrict__ q, const void* __restrict__ dout, int64_t sb,
                     int64_t sh, int64_t sn, void* __restrict__ dq, int64_t osb, int64_t osh,
-                    int64_t osn, int H, int64_t N, int P, const void* __restrict__ img,
+                    int64_t osn, int H, int64_t N, int P, const double* __restrict__ S64,
                     const double* __restrict__ z64, float* __restrict__ part, int BH,
                     bool shared_lines) {
   using C = RowCfg<DT_BF16, D>;
@@ -384,9 +384,9 @@ void bwd_qds_kernel(const void* __restrict__ q, const void* __restrict__ dout, i
   const int bh = hp.bh;
   const int64_t b = bh / H, h = bh % H;
   {
-    const char* head = (const char*)img + (int64_t)bh * IC::head_bytes(DT_BF16);
-    stage_image(simg, (const u32x4*)(head + IC::img_bytes(DT_BF16)), IMG_WORDS, false);
-    stage_image(simg + IMG_WORDS, (const u32x4*)(head + IC::mat_bytes(DT_BF16)), Z_WORDS, false);
+    const MatrixSrc<D> src{S64 + (int64_t)bh * D * D, z64 + (int64_t)bh * D, nullptr, 0};
+    make_image<D, 2, false, 0, 256>(simg, src);
+    make_z_tile<D, 0>(simg + IMG_WORDS, src);
     for (int c = threadIdx.x; c < D; c += 256) zf[c] = (float)z64[(int64_t)bh * D + c];
   }
   __syncthreads();
@@ -590,7 +590,7 @@ template <int OT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 void bwd_qds4_kernel(const void* __restrict__ q, const void* __restrict__ dout, int64_t sb,
                      int64_t sh, int64_t sn, void* __restrict__ dq, int64_t osb, int64_t osh,
-                     int64_t osn, int H, int64_t N, int P, int Tw, const void* __restrict__ img,
+                     int64_t osn, int H, int64_t N, int P, const double* __restrict__ S64,
                      const double* __restrict__ z64, float* __restrict__ part) {
   constexpr int D = 128;
   using IC = ImageCfg<D>;
@@ -624,9 +624,9 @@ void bwd_qds4_kernel(const void* __restrict__ q, const void* __restrict__ dout, 
   const int bh = blockIdx.y;
   const int64_t b = bh / H, h = bh % H;
   {
-    const char* head = (const char*)img + (int64_t)bh * IC::head_bytes(DT_BF16);
-    stage_image(simg, (const u32x4*)(head + IC::img_bytes(DT_BF16)), IMG_WORDS, true);
-    stage_image(simg + IMG_WORDS, (const u32x4*)(head + IC::mat_bytes(DT_BF16)), Z_WORDS, false);
+    const MatrixSrc<D> src{S64 + (int64_t)bh * D * D, z64 + (int64_t)bh * D, nullptr, 0};
+    make_image<D, 1, false, 0, 64 * NW>(simg, src);
+    make_z_tile<D, 0>(simg + IMG_WORDS, src);
     for (int c = threadIdx.x; c < D; c += 64 * NW) zf[c] = (float)z64[(int64_t)bh * D + c];
   }
   __syncthreads();
@@ -862,7 +862,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void b
     const void* __restrict__ k, const void* __restrict__ v, int64_t sb, int64_t sh,
     int64_t sn, void* __restrict__ dk, void* __restrict__ dv, int64_t osb, int64_t osh,
     int64_t osn, int H, int64_t N, int G, const void* __restrict__ dimg,
-    const double* __restrict__ dz64, int BH, bool shared_lines) {
+    const double* __restrict__ dz64, const float* __restrict__ part, int P, int BH,
+    bool shared_lines) {
   using C = RowCfg<DT, D>;
   using IC = ImageCfg<D>;
   constexpr int Q4 = C::Q4, NT = C::NT, TT = C::TT;
@@ -877,19 +878,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void b
   if (hp.out) return;  // uniform over the workgroup
   const int bh = hp.bh;
   const int64_t b = bh / H, h = bh % H;
-  const u32x4* head = (const u32x4*)((const char*)dimg + (int64_t)bh * IC::head_bytes(DT));
-  stage_image(timg, head, ONE, DT == DT_BF16);
-  stage_image(nimg, head + IC::img_bytes(DT) / 16, ONE, DT == DT_BF16);
   const int lane = threadIdx.x & 63, wave = wave_index();
   const int g = lane >> 4, n = lane & 15;
   // dz is added in FP32 for bf16 inputs (their dS operands are bf16 hi
   // parts, whose rounding is some 2^15 times that of dz to FP32) and in
   // FP64 for fp32 inputs
   using DzT = typename std::conditional<DT == DT_BF16, float, double>::type;
+  __shared__ DzT dzl[D];
+  if (DT != DT_BF16 || !part) {
+    const u32x4* head = (const u32x4*)((const char*)dimg + (int64_t)bh * IC::head_bytes(DT));
+    stage_image(timg, head, ONE, DT == DT_BF16);
+    stage_image(nimg, head + IC::img_bytes(DT) / 16, ONE, DT == DT_BF16);
+    if (threadIdx.x < D) dzl[threadIdx.x] = (DzT)dz64[(int64_t)bh * D + threadIdx.x];
+  } else if constexpr (DT == DT_BF16) {
+    // few partials of dS, dz: added up here
+    const MatrixSrc<D> src{nullptr, nullptr, part + (int64_t)bh * P * (D * D + D), P};
+    by_partials(P, [&](auto pn) {
+      constexpr int PN = decltype(pn)::value;
+      make_image<D, 1, true, PN, 256>(timg, src);
+      make_image<D, 1, false, PN, 256>(nimg, src);
+      if (threadIdx.x < D) {
+        double x;
+        src.template get<PN, 1>(threadIdx.x, true, &x);
+        dzl[threadIdx.x] = (DzT)x;
+      }
+    });
+  }
+  __syncthreads();
   DzT dzr[Q4];
 #pragma unroll
-  for (int c = 0; c < Q4; ++c) dzr[c] = (DzT)dz64[(int64_t)bh * D + Run<D, DT>::feature(g, c)];
-  __syncthreads();
+  for (int c = 0; c < Q4; ++c) dzr[c] = dzl[Run<D, DT>::feature(g, c)];
 
   const int64_t in_head = (b * sb + h * sh) * C::ES + (int64_t)g * Run<D, DT>::CB;
   const char* kbase = (const char*)k + in_head;
@@ -1008,25 +1026,27 @@ static hipError_t launch_rows(const BwdArgs& a) {
   hipError_t e = hipSuccess;
   const int BH = (int)(a.B * a.H);
   const bool shared = lines_shared(a.sh * (DT == DT_BF16 ? 2 : 4), a.H);
+  // few partials of dS: the key pass's workgroups add them up themselves
+  const bool fold = DT == DT_BF16 && fold_partials(a.P, a.Gk, BH, D);
   if constexpr (DT == DT_BF16 && D == 128) {
     // one pass, four waves sharing each partial
     ProfScope prof("bwd_query_ds", a.stream);
     dim3 fgrid((unsigned)a.P, BH);
     bwd_qds4_kernel<OT><<<fgrid, 256, 0, a.stream>>>(
-        a.q, a.dout, a.sb, a.sh, a.sn, a.dq, a.osb, a.osh, a.osn, (int)a.H, a.N, a.P, a.Tw,
-        a.img, a.z64, a.part);
+        a.q, a.dout, a.sb, a.sh, a.sn, a.dq, a.osb, a.osh, a.osn, (int)a.H, a.N, a.P, a.S64,
+        a.z64, a.part);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    e = launch_combine(a.part, a.P, a.dS64, a.dz64, a.dimg, DT, BH, D, IMG_T | IMG_N, a.stream);
+    if (!fold) e = launch_combine(a.part, a.P, a.dS64, a.dz64, a.dimg, DT, BH, D, IMG_T | IMG_N, a.stream);
   } else if constexpr (DT == DT_BF16 && (D == 32 || D == 64)) {
     // one pass: dQ and the workgroups' partials of dS, dz (at d = 128 the
     // whole partial dS plus the query pass's state exceed the registers of
     // one wave, so there four waves share a partial, above)
     ProfScope prof("bwd_query_ds", a.stream);
     bwd_qds_kernel<OT, D><<<row_grid(a.P, BH, shared), 256, 0, a.stream>>>(
-        a.q, a.dout, a.sb, a.sh, a.sn, a.dq, a.osb, a.osh, a.osn, (int)a.H, a.N, a.P, a.img, a.z64,
+        a.q, a.dout, a.sb, a.sh, a.sn, a.dq, a.osb, a.osh, a.osn, (int)a.H, a.N, a.P, a.S64, a.z64,
         a.part, BH, shared);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    e = launch_combine(a.part, a.P, a.dS64, a.dz64, a.dimg, DT, BH, D, IMG_T | IMG_N, a.stream);
+    if (!fold) e = launch_combine(a.part, a.P, a.dS64, a.dz64, a.dimg, DT, BH, D, IMG_T | IMG_N, a.stream);
   } else {
     {
       ProfScope prof("bwd_query", a.stream);
@@ -1039,21 +1059,24 @@ static hipError_t launch_rows(const BwdArgs& a) {
     e = launch_summary(MODE_BWD, DT, D, a.q, a.dout, a.sb, a.sh, a.sn, a.B, a.H, a.N, a.P, a.Tw,
                        a.stash, a.part, a.stream);
     if (e != hipSuccess) return e;
-    e = launch_combine(a.part, a.P, a.dS64, a.dz64, a.dimg, DT, BH, D, IMG_T | IMG_N, a.stream);
+    if (!fold) e = launch_combine(a.part, a.P, a.dS64, a.dz64, a.dimg, DT, BH, D, IMG_T | IMG_N, a.stream);
   }
   if (e != hipSuccess) return e;
   ProfScope prof("bwd_key", a.stream);
   bwd_key_kernel<DT, OT, D><<<row_grid(a.Gk, BH, shared), 256, 0, a.stream>>>(
       a.k, a.v, a.sb, a.sh, a.sn, a.dk, a.dv, a.osb, a.osh, a.osn, (int)a.H, a.N, a.Gk, a.dimg,
-      a.dz64, BH, shared);
+      a.dz64, fold ? a.part : nullptr, a.P, BH, shared);
   return hipGetLastError();
 }
 
 template <int D>
 static hipError_t launch_backward_d(const BwdArgs& a) {
   if (fp32_rows(a.in_dt, D)) return launch_backward_fp32(a);
-  hipError_t e = launch_images(a.S64, a.z64, a.img, a.in_dt, a.B * a.H, D, IMG_Z | IMG_N | IMG_LO, a.stream);
-  if (e != hipSuccess) return e;
+  if (a.in_dt != DT_BF16 || D < 32) {  // the two-pass query kernel's operands
+    const hipError_t e =
+        launch_images(a.S64, a.z64, a.img, a.in_dt, a.B * a.H, D, IMG_Z | IMG_N | IMG_LO, a.stream);
+    if (e != hipSuccess) return e;
+  }
   if (a.in_dt == DT_BF16 && a.out_dt == DT_BF16) return launch_rows<DT_BF16, DT_BF16, D>(a);
   if (a.in_dt == DT_BF16) return launch_rows<DT_BF16, DT_FP32, D>(a);
   if constexpr (!fp32_rows(DT_FP32, D)) {

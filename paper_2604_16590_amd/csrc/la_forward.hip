@@ -548,11 +548,22 @@ struct ApplyCfg {
 // store.  The other branch's rows travel in the same register sets as the
 // queries, a step ahead, where registers allow (bf16 in and out).  `other`
 // may be `o` itself: each lane reads its elements before it writes them.
+//
+// img: the operands as the combine left them; null (bf16): each workgroup
+// makes them from src, and where that holds partial sums the first of a head
+// writes their FP64 sum if it is a result.
+struct ApplySrc {
+  const double *M, *v;     // FP64 summary, or
+  const float* part;       // P partial sums a head, and where their sum goes
+  int P;
+  double *M_out, *v_out;   // (may be null)
+};
+
 template <int DT, int OT, int D, bool MIX>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void apply_kernel(
     const void* __restrict__ q, int64_t sb, int64_t sh, int64_t sn,
     void* o, int64_t osb, int64_t osh, int64_t osn, int H,
-    int64_t N, int G, const void* __restrict__ img, const void* other,
+    int64_t N, int G, const void* __restrict__ img, ApplySrc src, const void* other,
     const double* __restrict__ sigma, double sigma_data) {
   using IC = ImageCfg<D>;
   using AC = ApplyCfg<DT, D>;
@@ -727,9 +738,33 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
   // (the first of the head's two, S^T operands) into LDS
   QRegs qa, qb;
   if (nk > 0) load_q(tok(0), qa);
-  {
-    const u32x4* src = (const u32x4*)((const char*)img + (int64_t)bh * IC::head_bytes(DT));
-    for (int w = threadIdx.x; w < IMG_WORDS; w += 256) simg[w] = src[w];
+  if (DT != DT_BF16 || img) {
+    const u32x4* from = (const u32x4*)((const char*)img + (int64_t)bh * IC::head_bytes(DT));
+    for (int w = threadIdx.x; w < IMG_WORDS; w += 256) simg[w] = from[w];
+  } else if constexpr (DT == DT_BF16) {
+    const MatrixSrc<D> s{src.M ? src.M + (int64_t)bh * D * D : nullptr,
+                         src.v ? src.v + (int64_t)bh * D : nullptr,
+                         src.part ? src.part + (int64_t)bh * src.P * (D * D + D) : nullptr, src.P};
+    if (!src.part) {
+      make_image<D, 2, true, 0, 256>(simg, s);
+      make_z_tile<D, 0>(simg + IC::mat_bytes(DT) / 16, s);
+    } else {
+      by_partials(src.P, [&](auto pn) {
+        constexpr int PN = decltype(pn)::value;
+        make_image<D, 2, true, PN, 256>(simg, s);
+        make_z_tile<D, PN>(simg + IC::mat_bytes(DT) / 16, s);
+        if (src.M_out && blockIdx.x == 0) {
+          double x[2];
+          for (int u = threadIdx.x; u < (D * D + D) / 2; u += 256) {
+            const bool vec = u >= D * D / 2;
+            const int i = 2 * u - (vec ? D * D : 0);
+            s.template get<PN, 2>(i, vec, x);
+            double* to = vec ? src.v_out + (int64_t)bh * D + i : src.M_out + (int64_t)bh * D * D + i;
+            to[0] = x[0]; to[1] = x[1];
+          }
+        }
+      });
+    }
   }
   __syncthreads();
   if (nk > 0) {
@@ -819,30 +854,34 @@ hipError_t launch_combine(const float* part, int P, double* M64, double* v64, vo
 }
 
 template <int D>
-static hipError_t launch_apply_only(const FwdArgs& a);
+static hipError_t launch_apply_only(const FwdArgs& a, const void* img, const ApplySrc& src);
 
 template <int D>
 static hipError_t launch_forward_d(const FwdArgs& a) {
   const int BH = (int)(a.B * a.H);
   launch_summary_d<D>(MODE_FWD, a.in_dt, a.k, a.v, a.sb, a.sh, a.sn, a.B, a.H, a.N, a.P, a.Tw,
                       a.team, nullptr, a.part, a.stream);
+  // few partials: the apply's workgroups add them up themselves
+  if (a.in_dt == DT_BF16 && fold_partials(a.P, a.Ga, BH, D))
+    return launch_apply_only<D>(a, nullptr, ApplySrc{nullptr, nullptr, a.part, a.P,
+                                                     a.want_summary ? a.S64 : nullptr, a.z64});
   {
     ProfScope prof("combine", a.stream);
     launch_combine_d<D>(a.part, a.P, a.S64, a.z64, a.img, a.in_dt, BH,
                         fp32_rows(a.in_dt, D) ? 0 : IMG_T | IMG_Z | IMG_LO, a.stream);
   }
-  return launch_apply_only<D>(a);
+  return launch_apply_only<D>(a, a.img, ApplySrc{});
 }
 
 template <int D>
-static hipError_t launch_apply_only(const FwdArgs& a) {
+static hipError_t launch_apply_only(const FwdArgs& a, const void* img, const ApplySrc& src) {
   if (fp32_rows(a.in_dt, D)) return launch_apply_fp32(a);
   const int BH = (int)(a.B * a.H);
   dim3 agrid((unsigned)a.Ga, BH);
   ProfScope prof(a.other ? "apply_gated" : "apply", a.stream);
 #define LA_APPLY(DTI, DTO, MIX)                                                   \
   apply_kernel<DTI, DTO, D, MIX><<<agrid, 256, 0, a.stream>>>(                     \
-      a.q, a.sb, a.sh, a.sn, a.o, a.osb, a.osh, a.osn, (int)a.H, a.N, a.Ga, a.img, a.other, \
+      a.q, a.sb, a.sh, a.sn, a.o, a.osb, a.osh, a.osn, (int)a.H, a.N, a.Ga, img, src, a.other, \
       a.sigma, a.sigma_data)
 #define LA_APPLY_DT(MIX)                                                \
   if (a.in_dt == DT_BF16 && a.out_dt == DT_BF16) LA_APPLY(DT_BF16, DT_BF16, MIX); \
@@ -871,16 +910,23 @@ hipError_t launch_forward(const FwdArgs& a) {
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_apply(const FwdArgs& a) {
-  hipError_t e = hipSuccess;
-  if (!fp32_rows(a.in_dt, a.D))
-    e = launch_images(a.S64, a.z64, a.img, a.in_dt, a.B * a.H, a.D, IMG_T | IMG_Z | IMG_LO, a.stream);
+template <int D>
+static hipError_t launch_apply_d(const FwdArgs& a) {
+  if (fp32_rows(a.in_dt, D)) return launch_apply_fp32(a);
+  if (a.in_dt == DT_BF16)
+    return launch_apply_only<D>(a, nullptr, ApplySrc{a.S64, a.z64, nullptr, 0, nullptr, nullptr});
+  const hipError_t e =
+      launch_images(a.S64, a.z64, a.img, a.in_dt, a.B * a.H, D, IMG_T | IMG_Z, a.stream);
   if (e != hipSuccess) return e;
+  return launch_apply_only<D>(a, a.img, ApplySrc{});
+}
+
+hipError_t launch_apply(const FwdArgs& a) {
   switch (a.D) {
-    case 16: return launch_apply_only<16>(a);
-    case 32: return launch_apply_only<32>(a);
-    case 64: return launch_apply_only<64>(a);
-    case 128: return launch_apply_only<128>(a);
+    case 16: return launch_apply_d<16>(a);
+    case 32: return launch_apply_d<32>(a);
+    case 64: return launch_apply_d<64>(a);
+    case 128: return launch_apply_d<128>(a);
   }
   return hipErrorInvalidValue;
 }

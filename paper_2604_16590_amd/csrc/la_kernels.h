@@ -110,8 +110,9 @@ enum {
 
 // Store x[0..8) = the row of 16-row tile i, row m, at contraction indices
 // k0 .. k0 + 7 (k0 a multiple of 8), as bf16 hi (and, with `lo`, lo) parts
-// or fp32: whole 16-byte words, one per chunk of the lane runs.
-template <int D, int DT>
+// or fp32: whole 16-byte words, one per chunk of the lane runs.  PARTS: bf16
+// parts that the image has room for.
+template <int D, int DT, int PARTS = 2>
 __device__ __forceinline__ void put_image8(char* base, int i, int m, int k0, const double* x, bool lo) {
   using R = Run<D, DT>;
   using IC = ImageCfg<D>;
@@ -127,9 +128,9 @@ __device__ __forceinline__ void put_image8(char* base, int i, int m, int k0, con
         h[j >> 1] = pack_bf16((float)a, (float)b);
         l[j >> 1] = pack_bf16((float)(a - (double)bf16lo(h[j >> 1])), (float)(b - (double)bf16hi(h[j >> 1])));
       }
-      const int word = ((i * IC::NS + (pos >> 3)) * 2) * 64 + lane;
+      const int word = ((i * IC::NS + (pos >> 3)) * PARTS) * 64 + lane;
       img[word] = h;
-      if (lo) img[word + 64] = l;
+      if (PARTS > 1 && lo) img[word + 64] = l;
     } else {
       const int word = (i * (IC::Q4 / 4) + (pos >> 2)) * 64 + lane;
       img[word] = u32x4{__float_as_uint((float)x[c0]), __float_as_uint((float)x[c0 + 1]),
@@ -172,6 +173,115 @@ inline dim3 row_grid(int64_t G, int64_t BH, bool shared) {
   return dim3((unsigned)(shared ? (G * BH + 7) / 8 * 8 : G * BH));
 }
 
+// A head's d x d matrix and d vector where a workgroup makes its operands
+// itself: in FP64, or (part) as P <= 4 partial sums [d][d], [d] still to be
+// added, in the combine's order.
+template <int D>
+struct MatrixSrc {
+  const double* M;
+  const double* v;
+  const float* part;
+  int P;
+  // W neighbouring elements from i (a multiple of W) of the matrix or, vec,
+  // of the vector.  PN: 0 for FP64, else the loads an element takes: 1, 2 or
+  // 4 >= P (no branch divides them; those past P read the last partial and
+  // count 0).
+  template <int PN, int W>
+  __device__ __forceinline__ void get(int i, bool vec, double* x) const {
+    if constexpr (PN == 0) {
+      typedef double dw __attribute__((ext_vector_type(W), aligned(8)));
+      const dw w = *(const dw*)((vec ? v : M) + i);
+#pragma unroll
+      for (int c = 0; c < W; ++c) x[c] = w[c];
+    } else {
+      typedef float fw __attribute__((ext_vector_type(W)));
+      const int e = (vec ? D * D : 0) + i;
+      fw w[PN];
+#pragma unroll
+      for (int p = 0; p < PN; ++p) {
+        w[p] = *(const fw*)(part + (p < P ? p : P - 1) * (D * D + D) + e);
+        if (p >= P) w[p] = 0.f;
+      }
+#pragma unroll
+      for (int c = 0; c < W; ++c) {
+        if constexpr (PN == 1) x[c] = (double)w[0][c];
+        else if constexpr (PN == 2) x[c] = (double)w[0][c] + (double)w[1][c];
+        else x[c] = ((double)w[0][c] + (double)w[1][c]) + ((double)w[2][c] + (double)w[3][c]);
+      }
+    }
+  }
+};
+
+// Operands of a bf16 kernel, made in LDS by NTH threads: the T or N image's
+// matrix tiles (PARTS = 2: hi and lo parts, 1: hi parts), the z tile.  Small
+// grids wait for these loads: 8 or 16 bytes wide.
+template <int D, int PARTS, bool TRANSPOSED, int PN, int NTH>
+__device__ __forceinline__ void make_image(u32x4* dst, const MatrixSrc<D>& s) {
+  if constexpr (TRANSPOSED) {
+    constexpr int W = 2;  // eight rows' runs of two columns
+#pragma unroll 1
+    for (int u = threadIdx.x; u < D * D / (8 * W); u += NTH) {
+      const int c0 = W * (u % (D / W)), k0 = 8 * (u / (D / W));
+      double x[8][W];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) s.template get<PN, W>((k0 + j) * D + c0, false, x[j]);
+#pragma unroll
+      for (int c = 0; c < W; ++c) {
+        double y[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) y[j] = x[j][c];
+        int i, m;
+        image_row<D, DT_BF16>(c0 + c, i, m);
+        put_image8<D, DT_BF16, PARTS>((char*)dst, i, m, k0, y, true);
+      }
+    }
+  } else {
+    constexpr int W = PN == 0 ? 2 : 4;
+#pragma unroll 1
+    for (int u = threadIdx.x; u < D * D / 8; u += NTH) {
+      const int row = u / (D / 8), k0 = 8 * (u % (D / 8));
+      double x[8];
+#pragma unroll
+      for (int j = 0; j < 8; j += W) s.template get<PN, W>(row * D + k0 + j, false, x + j);
+      int i, m;
+      image_row<D, DT_BF16>(row, i, m);
+      put_image8<D, DT_BF16, PARTS>((char*)dst, i, m, k0, x, true);
+    }
+  }
+}
+template <int D, int PN>
+__device__ __forceinline__ void make_z_tile(u32x4* dst, const MatrixSrc<D>& s) {
+  if (threadIdx.x < 2 * D) {
+    const int k0 = 8 * (threadIdx.x >> 4);
+    double x[8];
+#pragma unroll
+    for (int j = 0; j < 8; j += 2) s.template get<PN, 2>(k0 + j, true, x + j);
+    put_image8<D, DT_BF16>((char*)dst, 0, threadIdx.x & 15, k0, x, true);
+  }
+}
+// f(PN) for the loads that P partials take
+template <class F>
+__device__ __forceinline__ void by_partials(int P, F&& f) {
+  if (P == 1) f(std::integral_constant<int, 1>{});
+  else if (P == 2) f(std::integral_constant<int, 2>{});
+  else f(std::integral_constant<int, 4>{});
+}
+
+// Whether the G workgroups of each head add up its P partials themselves
+// instead of a combine before them.  On a full chip the partials cost their
+// bytes G times over.  Apply and key pass against the same with a combine
+// each: 2,048 heads x 256 tokens, d = 128 (P = 1, G = 1 and 2) 161 + 179 us
+// and 126 + 198 + 399; 512 heads x 512, d = 64 (P = 2, G = 4) 40 + 43 and 30 +
+// 41 + 31; but 1,024 heads x 512, d = 32 (P = 4), the key pass with G = 4 42
+// and 32 + 8, and 512 heads x 1,024, d = 64 (P = 4, G = 4 and 8) 64 + 97 and
+// 38 + 70 + 42.  A small grid waits some 4 us for 100 KB and 6 us for a
+// combine: 4 heads x 1,024, d = 128 (P = 2) 23 + 14 us and 16 + 16 + 13, 4 x
+// 2,048 (P = 4) 28 + 20 and 17 + 15 + 13.
+inline bool fold_partials(int P, int G, int64_t heads, int D) {
+  if (P > 4) return false;
+  return P * G <= 8 || (P * (D * D + D) * 4 <= 144 * 1024 && heads * G <= 512);
+}
+
 struct FwdArgs {
   int64_t B, H, N;
   int D, in_dt, out_dt;
@@ -184,6 +294,7 @@ struct FwdArgs {
   float* part;         // [BH][P][D*D + D]: S rows, then z
   double* S64;         // [BH][D][D]
   double* z64;         // [BH][D]
+  bool want_summary;   // S64, z64 are results
   void* img;           // [BH][2 images]
   // noise-gated mix (null `other`: plain output): o = g_b A + (1 - g_b) other,
   // g_b = sigma_data / (sigma_data + sigma[b])
@@ -202,7 +313,7 @@ struct BwdArgs {
   const double *S64, *z64;
   int P, Tw, Ta;       // Ta: tokens per workgroup of the two-pass query kernel
   int Gk;              // key-backward workgroups per head (they take its token blocks in turn)
-  void* img;           // images of S
+  void* img;           // images of S (fp32 inputs at d <= 32, d = 16)
   float* part;         // partials of dS, dz
   float2* stash;       // [BH][N] per query token: (1/den, -(dO . O))
   double* dS64;

@@ -182,6 +182,30 @@ def test_backward_forms(layout, d, N):
         assert torch.equal(x[:, H - 1:], y)
 
 
+# up to four partials are added up by the workgroups that need them, or by a
+# pass before where many workgroups would read them: the same bits
+@pytest.mark.parametrize("d,heads", [(16, 15600), (32, 4000), (64, 1040), (128, 270)])
+@pytest.mark.parametrize("partials", [1, 3, 4])
+def test_partials_added_up_by_their_readers(partials, d, heads):
+    dev = require_gpu()
+    N = 4 * d * partials
+    gen = torch.Generator(device=dev).manual_seed(d + partials)
+    q, k, v, g = (torch.randn((1, heads, N, d), generator=gen, device=dev).bfloat16() for _ in range(4))
+    o, S, z = la.forward(q, k, v, return_summary=True)
+    got = la.backward(q, k, v, S, z, g)
+    last = [x[:, heads - 1:] for x in (q, k, v)]
+    o1, S1, z1 = la.forward(*last, return_summary=True)
+    got1 = la.backward(*last, S1, z1, g[:, heads - 1:])
+    o2 = la.apply(last[0], S1, z1)
+    torch.cuda.synchronize()
+    for x, y in zip((o, S, z, o) + tuple(got), (o1, S1, z1, o2) + tuple(got1)):
+        assert torch.equal(x[:, heads - 1:], y)
+    host = [x.float().cpu().numpy() for x in last + [g[:, heads - 1:]]]
+    assert normwise(as64(o1), oracle.forward(*host[:3])) < TOL["bf16"]
+    for x, r in zip(got1, oracle.backward(*host)):
+        assert normwise(as64(x), r) < TOL["bf16"]
+
+
 # the tiled step where its kernels change: footprints of 512 positions and
 # one more (offsets kept in LDS or not), cells longer than the window table,
 # a cell's last 16-token tile, one position per cell row
