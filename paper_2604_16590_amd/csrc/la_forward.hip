@@ -71,27 +71,27 @@ __device__ __forceinline__ void summary_load(const char* kh, const char* vh, uin
   }
 }
 
-// SUM_WAVE: one dimension of waves in (partial, (b, h)) order, (b, h)
-// fastest: wave w takes partial w / BH of (b, h) = w % BH, so a block's four
-// waves are four heads over the same tokens (with heads interleaved in a
-// token row, BNHD, one compute unit then reads adjacent slices of the same
-// rows: the summary at d = 64, 16 heads, went from 1.55 to 1.32 ms; BHND is
-// unaffected).  Which waves share a block does not change any partial's
-// arithmetic.
-// SUM_TEAM: one workgroup per (partial, (b, h)), in the same order; its four
-// waves take the partial's steps in turn and add their sums in LDS, so a
-// short sequence is four times as many waves of a quarter of the steps for
-// the same partials in memory (one head of 4,096 fp32 tokens at d = 64:
-// 45 -> 16 us; 64 heads of 16,384 bf16 tokens at d = 64: 54 -> 50 us).
-// Each XCD takes a contiguous share of the items (workgroups go to the
-// eight in turn).
+// A partial's tokens are summed in runs of Tq (summary_runs), from zero each,
+// and the runs' sums added in order in FP32, so the same bits come of two
+// forms:
+// NW = 1: a wave to a partial takes its runs one after the other and keeps
+// the sum so far in LDS.  One dimension of waves in (partial, (b, h)) order,
+// (b, h) fastest: wave w takes partial w / BH of (b, h) = w % BH, so a
+// block's four waves are four heads over the same tokens (with heads
+// interleaved in a token row, BNHD, one compute unit then reads adjacent
+// slices of the same rows: the summary at d = 64, 16 heads, went from 1.55 to
+// 1.32 ms; BHND is unaffected).
+// NW > 1: one workgroup per (partial, (b, h)), in the same order, a wave to a
+// run.  A few heads are NW times as many waves for the same partials in
+// memory (a head of 1,700,000 tokens at d = 32: 86 us, 417 with a wave to a
+// partial; two of 300,000 at d = 64: 51, 175; one of 4,096 fp32 tokens at
+// d = 64, when fp32 took this kernel: 16, 45).  Each XCD takes a contiguous share of the items (workgroups go
+// to the eight in turn).
 // (fp32 inputs at d >= 32 take summary_split_kernel.)
-enum { SUM_WAVE = 0, SUM_TEAM = 1 };
-
-template <int DT, int D, int MODE, int FORM>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SummaryCfg<DT, D, MODE>::WAVES_PER_SIMD))) void summary_kernel(
+template <int DT, int D, int MODE, int NW>
+__global__ __launch_bounds__(NW == 1 ? 256 : 64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 16 ? 4 : SummaryCfg<DT, D, MODE>::WAVES_PER_SIMD))) void summary_kernel(
     const void* __restrict__ k, const void* __restrict__ v, int64_t sb,
-    int64_t sh, int64_t sn, int H, int64_t N, int P, int Tw,
+    int64_t sh, int64_t sn, int H, int64_t N, int P, int Tw, int Tq,
     const float2* __restrict__ stash, float* __restrict__ part, int BH) {
   using C = SummaryCfg<DT, D, MODE>;
   constexpr int F = C::F;
@@ -99,14 +99,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SummaryCfg<
   const int lane = threadIdx.x & 63, wave = wave_index();
   const int g = lane >> 4, m = lane & 15;
   int64_t item = (int64_t)blockIdx.x * 4 + wave;
-  if constexpr (FORM == SUM_TEAM)
-    item = (int64_t)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  if constexpr (NW > 1) item = (int64_t)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
   const int p = (int)(item / BH);
   if (p >= P) return;  // uniform across the waves that share p
   const int bh = (int)(item % BH);
   const int64_t b = bh / H, h = bh % H;
-  const int64_t t_begin = (int64_t)p * Tw;
-  const int64_t t_end = min(N, t_begin + (int64_t)Tw);
+  int64_t t_begin = (int64_t)p * Tw;
+  int64_t t_end = min(N, t_begin + (int64_t)Tw);
+  if constexpr (NW > 1) {
+    // a wave past the partial's end runs one step of masked rows, which
+    // adds nothing
+    t_begin += (int64_t)wave * Tq;
+    t_end = min(t_end, t_begin + (int64_t)Tq);
+  }
   const int64_t head = (b * sb + h * sh) * C::ES;
   // lane m reads features [F*m, +F) of rows R*g + r (the host bounds 32 rows
   // of the token stride to 2^24 bytes, so the lane offset fits 32 bits)
@@ -117,13 +122,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SummaryCfg<
   const float2* tstash = MODE == MODE_BWD ? stash + (int64_t)bh * N : nullptr;
 
   f32x4 acc[F][F];
+  float zacc[F];
 #pragma unroll
   for (int i = 0; i < F; ++i)
 #pragma unroll
     for (int j = 0; j < F; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float zacc[F];
 #pragma unroll
   for (int i = 0; i < F; ++i) zacc[i] = 0.f;
+  // the sum of the runs before this one (NW = 1)
+  constexpr bool KEEP = NW == 1 && (D == 32 || D == 64);
+  __shared__ f32x4 kept[KEEP ? 4 : 1][KEEP ? F * F : 1][64];
+  float zkept[F];
+  bool first = true;
+  auto add_kept = [&] {
+#pragma unroll
+    for (int i = 0; i < F; ++i) {
+      zacc[i] = sum_groups(zacc[i]);
+      if (!first) zacc[i] = zkept[i] + zacc[i];
+#pragma unroll
+      for (int j = 0; j < F; ++j)
+        if (!first) acc[i][j] = kept[wave][i * F + j][lane] + acc[i][j];
+    }
+  };
 
   // two register sets in turn: while one step computes, the next one's
   // loads are in flight in the other set (no copies between them)
@@ -131,33 +151,47 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SummaryCfg<
   auto load = [&](int64_t t0, SummaryRegs<DT, D, MODE>& x) {
     summary_load<DT, D, MODE>(kh, vh, off, tstash, row_bytes, t0, g, m, t_end, x);
   };
-  // a team's wave past the partial's end runs one step of masked rows,
-  // which adds nothing
-  constexpr int STRIDE = FORM == SUM_TEAM ? 4 * C::STEP : C::STEP;
-  int64_t t0 = t_begin + (FORM == SUM_TEAM ? wave * C::STEP : 0);
+  int64_t t0 = t_begin;
+  int left = Tq;  // tokens of the run, a multiple of two steps (NW = 1)
   load(t0, ra);
   while (true) {
-    const int64_t t1 = t0 + STRIDE;
+    const int64_t t1 = t0 + C::STEP;
     if (t1 < t_end) load(t1, rb);
     summary_step<DT, D, MODE>(ra, acc, zacc);
     if (t1 >= t_end) break;
-    const int64_t t2 = t1 + STRIDE;
+    const int64_t t2 = t1 + C::STEP;
     if (t2 < t_end) load(t2, ra);
     summary_step<DT, D, MODE>(rb, acc, zacc);
     if (t2 >= t_end) break;
     t0 = t2;
+    if constexpr (KEEP) {
+      left -= 2 * C::STEP;
+      if (left == 0) {
+        add_kept();
+#pragma unroll
+        for (int i = 0; i < F; ++i) {
+          zkept[i] = zacc[i];
+          zacc[i] = 0.f;
+#pragma unroll
+          for (int j = 0; j < F; ++j) {
+            kept[wave][i * F + j][lane] = acc[i][j];
+            acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+          }
+        }
+        first = false;
+        left = Tq;
+      }
+    }
   }
 
   float* out = part + ((int64_t)bh * P + p) * E;
-  if constexpr (FORM == SUM_TEAM) {
-    // the waves' sums meet in LDS, RT tiles at a time, and are added in
-    // FP64 as (w0 + w1) + (w2 + w3): one more FP32 rounding a partial
-    constexpr int T = F * F, RT = T < 16 ? T : 16;
-    __shared__ f32x4 red[4][RT][64];
-    __shared__ float zred[4][D];
-    auto sum4 = [](float a, float b, float c, float e) {
-      return (float)(((double)a + (double)b) + ((double)c + (double)e));
-    };
+  if constexpr (NW > 1) {
+    // the runs' sums meet in LDS, RT tiles at a time
+    constexpr int T = F * F, RT = T < 64 / NW ? T : 64 / NW;
+    static_assert(RT % F == 0);
+    __shared__ f32x4 red[NW][RT][64];
+    __shared__ float zred[NW][D];
+    const int runs = (int)((min(N - (int64_t)p * Tw, (int64_t)Tw) + Tq - 1) / Tq);
 #pragma unroll
     for (int i = 0; i < F; ++i) {
       const float zs = sum_groups(zacc[i]);
@@ -169,25 +203,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SummaryCfg<
 #pragma unroll
       for (int t = 0; t < RT; ++t) red[wave][t][lane] = acc[(r0 + t) / F][(r0 + t) % F];
       __syncthreads();
-      // wave w takes rows 4g + w of the round's tiles
-      for (int t = 0; t < RT; t += F) {
+      // a wave takes rows 4g + r of a tile row in turn
+      for (int u = wave; u < RT / F * 4; u += NW) {
+        const int t = u / 4 * F, r = u % 4;
+        float x[F];
+#pragma unroll
+        for (int j = 0; j < F; ++j) x[j] = red[0][t + j][lane][r];
+        for (int w = 1; w < runs; ++w)
+#pragma unroll
+          for (int j = 0; j < F; ++j) x[j] += red[w][t + j][lane][r];
         uint32_t w[F];
 #pragma unroll
-        for (int j = 0; j < F; ++j)
-          w[j] = __float_as_uint(sum4(red[0][t + j][lane][wave], red[1][t + j][lane][wave],
-                                      red[2][t + j][lane][wave], red[3][t + j][lane][wave]));
-        store_words<4 * F>(out + (F * (4 * g + wave) + (r0 + t) / F) * D + F * m, w);
+        for (int j = 0; j < F; ++j) w[j] = __float_as_uint(x[j]);
+        store_words<4 * F>(out + (F * (4 * g + r) + (r0 + t) / F) * D + F * m, w);
       }
     }
     if (threadIdx.x < D) {
-      const int f = threadIdx.x;
-      out[D * D + f] = sum4(zred[0][f], zred[1][f], zred[2][f], zred[3][f]);
+      float x = zred[0][threadIdx.x];
+      for (int w = 1; w < runs; ++w) x += zred[w][threadIdx.x];
+      out[D * D + threadIdx.x] = x;
     }
     return;
   }
 
-  // this wave's share of the partial: rows of S, F consecutive values a
-  // lane, then z
+  // this wave's partial: rows of S, F consecutive values a lane, then z
+  if constexpr (KEEP) {
+    add_kept();
+  } else {
+#pragma unroll
+    for (int i = 0; i < F; ++i) zacc[i] = sum_groups(zacc[i]);
+  }
 #pragma unroll
   for (int i = 0; i < F; ++i)
 #pragma unroll
@@ -198,10 +243,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SummaryCfg<
       store_words<4 * F>(out + (F * (4 * g + r) + i) * D + F * m, w);
     }
 #pragma unroll
-  for (int i = 0; i < F; ++i) {
-    const float zs = sum_groups(zacc[i]);
-    if (g == 0) out[D * D + F * m + i] = zs;
-  }
+  for (int i = 0; i < F; ++i)
+    if (g == 0) out[D * D + F * m + i] = zacc[i];
 }
 
 // ---------------------------------------------------------------------------
@@ -782,20 +825,51 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
 // ---------------------------------------------------------------------------
 // Host-side launchers
 // ---------------------------------------------------------------------------
+// Tokens of a summary's runs: four to a partial where the teams take them
+// (d >= 64, short sequences), else up to eight (d <= 32: sixteen) of at least
+// 256 (128) tokens, so that a wave that takes them all adds up every eight
+// (four) steps; at d = 128, where a wave's sum fills 64 KB, one.
+static int summary_run(int D, int Tw, bool team) {
+  if (team) return (Tw / 4 + 31) / 32 * 32;
+  const int most = D >= 128 ? 1 : D == 64 ? 8 : 16;
+  const int runs = std::max(1, std::min(most, Tw / (D == 64 ? 256 : 128)));
+  return ((Tw + runs - 1) / runs + 63) / 64 * 64;
+}
+
 template <int DT, int D, int MODE>
 static void launch_summary_t(const void* k, const void* v, int64_t sb, int64_t sh, int64_t sn,
                              int64_t BH, int64_t H, int64_t N, int P, int Tw, bool team,
                              const float2* stash, float* part, hipStream_t stream) {
+  const int64_t items = P * BH;
+  const dim3 one((unsigned)((items + 7) / 8 * 8));
   if constexpr (DT == DT_FP32 && D >= 32) {
-    summary_split_kernel<D, MODE><<<dim3((unsigned)((P * BH + 7) / 8 * 8)), 64 * SplitCfg<D>::NW, 0, stream>>>(
+    summary_split_kernel<D, MODE><<<one, 64 * SplitCfg<D>::NW, 0, stream>>>(
         k, v, sb, sh, sn, (int)H, N, P, Tw, stash, part, (int)BH);
-  } else if (D >= 64 && MODE == MODE_FWD && team) {
-    if constexpr (D >= 64 && MODE == MODE_FWD)
-      summary_kernel<DT, D, MODE, SUM_TEAM><<<dim3((unsigned)((P * BH + 7) / 8 * 8)), 256, 0, stream>>>(
-          k, v, sb, sh, sn, (int)H, N, P, Tw, stash, part, (int)BH);
   } else {
-    summary_kernel<DT, D, MODE, SUM_WAVE><<<dim3((unsigned)((P * BH + 3) / 4)), 256, 0, stream>>>(
-        k, v, sb, sh, sn, (int)H, N, P, Tw, stash, part, (int)BH);
+#define LA_SUM(NW, GRID)                                                             \
+  summary_kernel<DT, D, MODE, NW><<<GRID, NW == 1 ? 256 : 64 * NW, 0, stream>>>(      \
+      k, v, sb, sh, sn, (int)H, N, P, Tw, Tq, stash, part, (int)BH)
+    const int Tq = summary_run(D, Tw, team);
+    const int runs = (Tw + Tq - 1) / Tq;
+    // A wave to a whole partial where those fill the chip, d = 64: from 832
+    // partials (12 heads of 50,000 tokens in 64 each: 40 us by teams, 44; 14:
+    // 50, 44); d = 32: from 2,048 unless heads share cache lines (64 heads of
+    // 30,001 tokens: 63 us by teams, 60; as views of [B, N, H, d] 76 and 82);
+    // d = 16 never (128 heads of 60,000: 164 us, 174).
+    const bool whole = D >= 32 && items >= (D == 32 ? 2048 : 832) &&
+                       !(D == 32 && lines_shared(sh * SummaryCfg<DT, D, MODE>::ES, H));
+    if (runs > 1 && (team || !whole)) {
+      if (runs <= 4) {
+        LA_SUM(4, one);
+      } else if (runs <= 8) {
+        if constexpr (D <= 64) LA_SUM(8, one);
+      } else {
+        if constexpr (D <= 32) LA_SUM(16, one);
+      }
+    } else {
+      LA_SUM(1, dim3((unsigned)((items + 3) / 4)));
+    }
+#undef LA_SUM
   }
 }
 
@@ -810,8 +884,10 @@ static void launch_summary_d(int mode, int dt, const void* k, const void* v, int
   launch_summary_t<DTI, D, M>(k, v, sb, sh, sn, BH, H, N, P, Tw, team, stash, part, stream)
   if (mode == MODE_FWD) {
     if (dt == DT_BF16) LA_SUM(DT_BF16, MODE_FWD); else LA_SUM(DT_FP32, MODE_FWD);
-  } else {
-    if (dt == DT_BF16) LA_SUM(DT_BF16, MODE_BWD); else LA_SUM(DT_FP32, MODE_BWD);
+  } else if (dt == DT_FP32) {
+    LA_SUM(DT_FP32, MODE_BWD);
+  } else if constexpr (D == 16) {  // (wider bf16 heads: la_backward.hip's fused pass)
+    LA_SUM(DT_BF16, MODE_BWD);
   }
 #undef LA_SUM
 }

@@ -47,6 +47,47 @@ def test_summary_forms(d, dtype, N):
     assert np.isfinite(as64(o)).all()
 
 
+# a wave to a partial's run or to the whole partial, run after run: the same
+# bits from one head, from many, and from views in which heads share cache
+# lines; two runs of a partial and its last partial's one, whole and ragged
+@pytest.mark.parametrize("d,heads,N", [
+    (16, 8, 4097), (16, 8, 33001), (16, 4, 300000), (32, 130, 4097), (32, 40, 33001), (32, 36, 64 * 2048),
+    (64, 16, 32769), (64, 16, 40001), (64, 14, 64 * 2048 + 65)])
+def test_summary_runs(d, heads, N):
+    dev = require_gpu()
+    gen = torch.Generator(device=dev).manual_seed(N)
+    q, k, v = (torch.randn((1, heads, N, d), generator=gen, device=dev).bfloat16() for _ in range(3))
+    views = [x.permute(0, 2, 1, 3).contiguous().permute(0, 2, 1, 3) for x in (q, k, v)]
+    last = [x[:, heads - 1:] for x in (q, k, v)]
+    o, S, z = la.forward(q, k, v, return_summary=True)
+    ov, Sv, zv = la.forward(*views, return_summary=True)
+    o1, S1, z1 = la.forward(*last, return_summary=True)
+    torch.cuda.synchronize()
+    assert torch.equal(S, Sv) and torch.equal(z, zv) and torch.equal(o, ov)
+    assert torch.equal(S[:, heads - 1:], S1) and torch.equal(z[:, heads - 1:], z1) and torch.equal(o[:, heads - 1:], o1)
+    host = [x.float().cpu().numpy() for x in last]
+    o_ref, S_ref, z_ref = oracle.forward(*host, want_summary=True)
+    assert normwise(as64(o1), o_ref) < TOL["bf16"]
+    assert normwise(S1.cpu().numpy(), S_ref) < 4e-3
+    assert normwise(z1.cpu().numpy()[..., None], z_ref[..., None]) < 4e-3
+
+
+@pytest.mark.parametrize("N", [257, 4097, 20001, 200001])
+def test_summary_runs_fp32(N):
+    # d = 16, forward and the backward's reduction
+    dev = require_gpu()
+    host = make_inputs((1, 2, N, 16), "fp32", seed=N, streams=(0, 1, 2, 3))
+    q, k, v, g = (to_device(x, dev) for x in host)
+    o, S, z = la.forward(q, k, v, return_summary=True)
+    got = la.backward(q, k, v, S, z, g)
+    torch.cuda.synchronize()
+    o_ref, S_ref, z_ref = oracle.forward(*host[:3], want_summary=True)
+    assert normwise(as64(o), o_ref) < TOL["fp32"]
+    assert normwise(S.cpu().numpy(), S_ref) < 1e-5 and normwise(z.cpu().numpy()[..., None], z_ref[..., None]) < 1e-6
+    for x, r in zip(got, oracle.backward(*host)):
+        assert normwise(as64(x), r) < TOL["fp32"]
+
+
 @pytest.mark.parametrize("d", [16, 32, 64, 128])
 @pytest.mark.parametrize("kind", ["tiny_v", "tiny_k", "huge_v", "inf_v", "nan_v", "inf_k", "nan_k", "zeros"])
 def test_fp32_extremes(kind, d):
