@@ -138,18 +138,28 @@ int64_t partial_room(int64_t N, int d, int P) {
   return std::max<int64_t>(P, std::min(max_partials(d), ceil_div(N, d >= 128 ? 2048 : 512)));
 }
 
-// Apply workgroups per head: about kApplyGrid in the whole grid (a few per
-// compute unit), at most one per token block.  Per-token work, so this
-// changes no bits and may depend on the batch size.
-int apply_groups(int64_t N, int64_t BH) {
+// Apply workgroups per head: at most one per token block.  Per-token work, so
+// this changes no bits and may depend on the batch size.
+int apply_groups(int64_t N, int64_t BH, int d) {
   const int64_t blk = 128;  // tokens per block
+  if (d >= 128) {
+    // A workgroup first makes or copies 72 KB of operands, as much traffic as
+    // 270 tokens, and two share a compute unit: one round of 512 workgroups
+    // (4 x 16 heads of 4,096: 44 us, 81 with 2,048; 16 of 43,237: 92, 126),
+    // more where each still has 8,192 tokens (8 heads of 2,097,152 as views of
+    // [B, N, H, d]: 1.72 ms, 1.95 in one round); beyond 128 heads up to 2,048
+    // of at least 2,048 tokens, so that the last round is not half empty.
+    const int64_t ga = BH <= 128 ? std::max(512 / BH, std::min(ceil_div(4096, BH), N / 8192))
+                                 : std::min(ceil_div(2048, BH), N / 2048);
+    return (int)std::max<int64_t>(1, std::min(ceil_div(N, blk), ga));
+  }
   const int64_t grid = 4096;
   int64_t ga = std::min(ceil_div(N, blk), ceil_div(grid, BH));
-  // while the grid keeps 2048 workgroups or more, at least four blocks per
-  // workgroup: each workgroup stages the operand images first, and at
-  // 16,384 tokens x 64 heads (d = 64) 32 workgroups per head took 58 us
-  // against 60 us for 64 (16: 60 us)
-  ga = std::min(ga, std::max(ceil_div(N, 4 * blk), ceil_div(2048, BH)));
+  // while the grid keeps 1,024 workgroups or more (four to a compute unit), at
+  // least four blocks per workgroup: each stages the operands first (d = 64:
+  // 4 x 16 heads of 4,096 tokens take 23 us with 16 workgroups a head and 29
+  // with 32; of 16,384, 58 us with 32 and 60 with 64 or 16)
+  ga = std::min(ga, std::max(ceil_div(N, 4 * blk), ceil_div(1024, BH)));
   return (int)std::max<int64_t>(1, ga);
 }
 
@@ -205,11 +215,20 @@ Layout layout_for(const la_attn_desc* d, int pass) {
 
 // The gate's arguments (the attention's own are checked by the caller).
 // Key-backward workgroups per head, as apply_groups (fp32 takes one tile per
-// wave step).
-int key_groups(int64_t N, int64_t BH, int dt) {
+// wave step; at d >= 64 it has its own grid).  A bf16 workgroup stages 64 KB
+// of operands at d = 128 and 16 at d = 64: at least 1,024 (512) tokens each
+// while the grid keeps 1,024 (2,048) workgroups: 4 x 16 heads of 4,096 tokens
+// at d = 128 take 68 us, 80 with 128 tokens each, 8 x 16 of 16,384 430 and
+// 495 (256 tokens); at d = 64 8 x 16 of 16,384 take 215 us, 230 (256).
+int key_groups(int64_t N, int64_t BH, int d, int dt) {
   const int64_t blk = dt == LA_FP32 ? 64 : 128;  // tokens per block (4 waves x 16 x TT)
   int64_t grid = 8192;
-  return (int)std::max<int64_t>(1, std::min(ceil_div(N, blk), ceil_div(grid, BH)));
+  int64_t g = std::min(ceil_div(N, blk), ceil_div(grid, BH));
+  if (d >= 64) {
+    const int64_t tokens = d >= 128 ? 1024 : 512, least = d >= 128 ? 1024 : 2048;
+    g = std::min(g, std::max(ceil_div(N, tokens), ceil_div(least, BH)));
+  }
+  return (int)std::max<int64_t>(1, g);
 }
 
 la_status check_gate(const void* other, const double* sigma, double sigma_data) {
@@ -241,7 +260,7 @@ la_status forward_impl(const la_attn_desc* desc, const void* q, const void* k, c
   a.q = q; a.k = k; a.v = v; a.o = o;
   a.P = t.P; a.Tw = t.Tw;
   a.team = team_summary(desc->N, (int)desc->d, desc->in_dtype);
-  a.Ga = apply_groups(desc->N, desc->B * desc->H);
+  a.Ga = apply_groups(desc->N, desc->B * desc->H, (int)desc->d);
   a.part = (float*)(w + L.part);
   a.S64 = s_out ? s_out : (double*)(w + L.S64);
   a.z64 = z_out ? z_out : (double*)(w + L.z64);
@@ -271,7 +290,7 @@ la_status apply_impl(const la_attn_desc* desc, const void* q, const double* s, c
   a.sb = desc->in_sb; a.sh = desc->in_sh; a.sn = desc->in_sn;
   a.osb = desc->out_sb; a.osh = desc->out_sh; a.osn = desc->out_sn;
   a.q = q; a.o = o;
-  a.Ga = apply_groups(desc->N, desc->B * desc->H);
+  a.Ga = apply_groups(desc->N, desc->B * desc->H, (int)desc->d);
   a.S64 = const_cast<double*>(s);
   a.z64 = const_cast<double*>(z);
   a.img = (char*)ws + L.img;
@@ -379,7 +398,7 @@ la_status la_backward(const la_attn_desc* desc, const void* q, const void* k,
   a.dq = dq; a.dk = dk; a.dv = dv;
   a.S64 = s; a.z64 = z;
   a.P = t.P; a.Tw = t.Tw; a.Ta = t.Tk;
-  a.Gk = key_groups(desc->N, desc->B * desc->H, desc->in_dtype);
+  a.Gk = key_groups(desc->N, desc->B * desc->H, (int)desc->d, desc->in_dtype);
   a.img = w + L.img;
   a.part = (float*)(w + L.part);
   a.stash = (float2*)(w + L.stash);

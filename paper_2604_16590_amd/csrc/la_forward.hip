@@ -828,7 +828,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
 // Tokens of a summary's runs: four to a partial where the teams take them
 // (d >= 64, short sequences), else up to eight (d <= 32: sixteen) of at least
 // 256 (128) tokens, so that a wave that takes them all adds up every eight
-// (four) steps; at d = 128, where a wave's sum fills 64 KB, one.
+// (four) steps; at d = 128, where a wave's sum fills 64 KB, one.  (Kept in
+// memory between the runs, or in a launch for each, it cost 8 to 25 % of the
+// summary of eight heads and more.)
 static int summary_run(int D, int Tw, bool team) {
   if (team) return (Tw / 4 + 31) / 32 * 32;
   const int most = D >= 128 ? 1 : D == 64 ? 8 : 16;
