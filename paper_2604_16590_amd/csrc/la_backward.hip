@@ -203,7 +203,7 @@ template <int DT, int OT, int D>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void bwd_query_kernel(
     const void* __restrict__ q, const void* __restrict__ dout, int64_t sb, int64_t sh,
     int64_t sn, void* __restrict__ dq, int64_t osb, int64_t osh, int64_t osn, int H,
-    int64_t N, int Ta, const void* __restrict__ img, const double* __restrict__ z64,
+    int64_t N, int Ta, const double* __restrict__ S64, const double* __restrict__ z64,
     float2* __restrict__ stash, int G, int BH, bool shared_lines) {
   using C = RowCfg<DT, D>;
   using IC = ImageCfg<D>;
@@ -220,9 +220,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void b
   const int bh = hp.bh;
   const int64_t b = bh / H, h = bh % H;
   {
-    const char* head = (const char*)img + (int64_t)bh * IC::head_bytes(DT);
-    stage_image(simg, (const u32x4*)(head + IC::img_bytes(DT)), IMG_WORDS, false);
-    stage_image(simg + IMG_WORDS, (const u32x4*)(head + IC::mat_bytes(DT)), Z_WORDS, false);
+    const MatrixSrc<D> src{S64 + (int64_t)bh * D * D, z64 + (int64_t)bh * D, nullptr, 0};
+    make_image<DT, D, 2, false, 0, 256>(simg, src);
+    make_z_tile<DT, D, 0>(simg + IMG_WORDS, src);
   }
   const int lane = threadIdx.x & 63, wave = wave_index();
   const int g = lane >> 4, n = lane & 15;
@@ -385,8 +385,8 @@ void bwd_qds_kernel(const void* __restrict__ q, const void* __restrict__ dout, i
   const int64_t b = bh / H, h = bh % H;
   {
     const MatrixSrc<D> src{S64 + (int64_t)bh * D * D, z64 + (int64_t)bh * D, nullptr, 0};
-    make_image<D, 2, false, 0, 256>(simg, src);
-    make_z_tile<D, 0>(simg + IMG_WORDS, src);
+    make_image<DT_BF16, D, 2, false, 0, 256>(simg, src);
+    make_z_tile<DT_BF16, D, 0>(simg + IMG_WORDS, src);
     for (int c = threadIdx.x; c < D; c += 256) zf[c] = (float)z64[(int64_t)bh * D + c];
   }
   __syncthreads();
@@ -595,7 +595,7 @@ void bwd_qds4_kernel(const void* __restrict__ q, const void* __restrict__ dout, 
   constexpr int D = 128;
   using IC = ImageCfg<D>;
   using RN = Run<D, DT_BF16>;
-  constexpr int Q4 = D / 4, NT = D / 16, NB = D / 16, NS = IC::NS;
+  constexpr int NT = D / 16, NS = IC::NS;
   constexpr int RW = D / 8, NCH = RN::NCH, CH = RN::CH;
   constexpr int OES = OT == DT_BF16 ? 2 : 4;
   constexpr int OCB = CH * OES;
@@ -625,8 +625,8 @@ void bwd_qds4_kernel(const void* __restrict__ q, const void* __restrict__ dout, 
   const int64_t b = bh / H, h = bh % H;
   {
     const MatrixSrc<D> src{S64 + (int64_t)bh * D * D, z64 + (int64_t)bh * D, nullptr, 0};
-    make_image<D, 1, false, 0, 64 * NW>(simg, src);
-    make_z_tile<D, 0>(simg + IMG_WORDS, src);
+    make_image<DT_BF16, D, 1, false, 0, 64 * NW>(simg, src);
+    make_z_tile<DT_BF16, D, 0>(simg + IMG_WORDS, src);
     for (int c = threadIdx.x; c < D; c += 64 * NW) zf[c] = (float)z64[(int64_t)bh * D + c];
   }
   __syncthreads();
@@ -885,18 +885,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void b
   // FP64 for fp32 inputs
   using DzT = typename std::conditional<DT == DT_BF16, float, double>::type;
   __shared__ DzT dzl[D];
-  if (DT != DT_BF16 || !part) {
+  if (!part) {
     const u32x4* head = (const u32x4*)((const char*)dimg + (int64_t)bh * IC::head_bytes(DT));
     stage_image(timg, head, ONE, DT == DT_BF16);
     stage_image(nimg, head + IC::img_bytes(DT) / 16, ONE, DT == DT_BF16);
     if (threadIdx.x < D) dzl[threadIdx.x] = (DzT)dz64[(int64_t)bh * D + threadIdx.x];
-  } else if constexpr (DT == DT_BF16) {
+  } else {
     // few partials of dS, dz: added up here
     const MatrixSrc<D> src{nullptr, nullptr, part + (int64_t)bh * P * (D * D + D), P};
     by_partials(P, [&](auto pn) {
       constexpr int PN = decltype(pn)::value;
-      make_image<D, 1, true, PN, 256>(timg, src);
-      make_image<D, 1, false, PN, 256>(nimg, src);
+      make_image<DT, D, 1, true, PN, 256>(timg, src);
+      make_image<DT, D, 1, false, PN, 256>(nimg, src);
       if (threadIdx.x < D) {
         double x;
         src.template get<PN, 1>(threadIdx.x, true, &x);
@@ -1027,7 +1027,7 @@ static hipError_t launch_rows(const BwdArgs& a) {
   const int BH = (int)(a.B * a.H);
   const bool shared = lines_shared(a.sh * (DT == DT_BF16 ? 2 : 4), a.H);
   // few partials of dS: the key pass's workgroups add them up themselves
-  const bool fold = DT == DT_BF16 && fold_partials(a.P, a.Gk, BH, D);
+  const bool fold = fold_partials(a.P, a.Gk, BH, D);
   if constexpr (DT == DT_BF16 && D == 128) {
     // one pass, four waves sharing each partial
     ProfScope prof("bwd_query_ds", a.stream);
@@ -1052,7 +1052,7 @@ static hipError_t launch_rows(const BwdArgs& a) {
       ProfScope prof("bwd_query", a.stream);
       const int64_t G = (a.N + a.Ta - 1) / a.Ta;
       bwd_query_kernel<DT, OT, D><<<row_grid(G, BH, shared), 256, 0, a.stream>>>(
-          a.q, a.dout, a.sb, a.sh, a.sn, a.dq, a.osb, a.osh, a.osn, (int)a.H, a.N, a.Ta, a.img,
+          a.q, a.dout, a.sb, a.sh, a.sn, a.dq, a.osb, a.osh, a.osn, (int)a.H, a.N, a.Ta, a.S64,
           a.z64, a.stash, (int)G, BH, shared);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -1072,11 +1072,6 @@ static hipError_t launch_rows(const BwdArgs& a) {
 template <int D>
 static hipError_t launch_backward_d(const BwdArgs& a) {
   if (fp32_rows(a.in_dt, D)) return launch_backward_fp32(a);
-  if (a.in_dt != DT_BF16 || D < 32) {  // the two-pass query kernel's operands
-    const hipError_t e =
-        launch_images(a.S64, a.z64, a.img, a.in_dt, a.B * a.H, D, IMG_Z | IMG_N | IMG_LO, a.stream);
-    if (e != hipSuccess) return e;
-  }
   if (a.in_dt == DT_BF16 && a.out_dt == DT_BF16) return launch_rows<DT_BF16, DT_BF16, D>(a);
   if (a.in_dt == DT_BF16) return launch_rows<DT_BF16, DT_FP32, D>(a);
   if constexpr (!fp32_rows(DT_FP32, D)) {

@@ -484,51 +484,44 @@ __global__ __launch_bounds__(64 * SplitCfg<D>::NW) __attribute__((amdgpu_waves_p
 // words of both images (eight contraction indices each), so every store is
 // one: the halfword stores this replaces took most of the time (1,024 heads
 // of 4 partials at d = 64: 94 -> 37 us; 64 heads of 8: 14 -> 7.5 us).  The
-// last workgroup of a head does the same for the vector.  T = double: M
-// and v are given, only the operands are written.
+// last workgroup of a head does the same for the vector.
 // ---------------------------------------------------------------------------
-template <int D, int IDT, typename T>
+template <int D, int IDT>
 __global__ __launch_bounds__(8 * D) void combine_kernel(
-    const T* __restrict__ msrc, const T* __restrict__ vsrc, int64_t mstride, int64_t vstride, int P,
+    const float* __restrict__ part, int P,
     double* __restrict__ M64, double* __restrict__ v64, void* __restrict__ img, int what) {
   using IC = ImageCfg<D>;
-  constexpr bool GIVEN = sizeof(T) == 8;
-  __shared__ double qs[GIVEN ? 1 : 4][8][D];
+  constexpr int E = D * D + D;
+  __shared__ double qs[4][8][D];
   __shared__ double sum[8][D];
   const int bh = blockIdx.y, t = threadIdx.x;
   const bool vec = blockIdx.x == D / 8;
   const int rows = vec ? 1 : 8, row0 = 8 * blockIdx.x;
-  const T* src = vec ? vsrc + (int64_t)bh * P * vstride
-                     : msrc + (int64_t)bh * P * mstride + (int64_t)row0 * D;
-  const int64_t stride = vec ? vstride : mstride;
-  if constexpr (GIVEN) {
-    for (int u = t; u < rows * D; u += 8 * D) (&sum[0][0])[u] = src[u];
-  } else {
-    // slice w, element quad u of the rows; eight loads at a time in flight
-    // (the last repeated past the end), added in order
-    const int w = t / (2 * D), u = 4 * (t % (2 * D));
-    const int pq = (P + 3) / 4, p0 = min(P, w * pq), p1 = min(P, p0 + pq);
-    if (u < rows * D) {
-      double q[4] = {0.0, 0.0, 0.0, 0.0};
-      for (int p = p0; p < p1; p += 8) {
-        f32x4 x[8];
+  const float* src = part + (int64_t)bh * P * E + (vec ? D * D : row0 * D);
+  // slice w, element quad u of the rows; eight loads at a time in flight
+  // (the last repeated past the end), added in order
+  const int w = t / (2 * D), u = 4 * (t % (2 * D));
+  const int pq = (P + 3) / 4, p0 = min(P, w * pq), p1 = min(P, p0 + pq);
+  if (u < rows * D) {
+    double q[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int p = p0; p < p1; p += 8) {
+      f32x4 x[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) x[k] = *(const f32x4*)(src + (int64_t)min(p + k, p1 - 1) * stride + u);
+      for (int k = 0; k < 8; ++k) x[k] = *(const f32x4*)(src + (int64_t)min(p + k, p1 - 1) * E + u);
 #pragma unroll
-        for (int k = 0; k < 8; ++k)
+      for (int k = 0; k < 8; ++k)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) q[r] += p + k < p1 ? (double)x[k][r] : 0.0;
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) (&qs[w][0][0])[u + r] = q[r];
+        for (int r = 0; r < 4; ++r) q[r] += p + k < p1 ? (double)x[k][r] : 0.0;
     }
-    __syncthreads();
-    if (t < rows * D) {
-      const double s = ((&qs[0][0][0])[t] + (&qs[1][0][0])[t]) + ((&qs[2][0][0])[t] + (&qs[3][0][0])[t]);
-      (&sum[0][0])[t] = s;
-      if (vec) v64[(int64_t)bh * D + t] = s;
-      else M64[((int64_t)bh * D + row0) * D + t] = s;
-    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) (&qs[w][0][0])[u + r] = q[r];
+  }
+  __syncthreads();
+  if (t < rows * D) {
+    const double s = ((&qs[0][0][0])[t] + (&qs[1][0][0])[t]) + ((&qs[2][0][0])[t] + (&qs[3][0][0])[t]);
+    (&sum[0][0])[t] = s;
+    if (vec) v64[(int64_t)bh * D + t] = s;
+    else M64[((int64_t)bh * D + row0) * D + t] = s;
   }
   __syncthreads();
   char* head = (char*)img + (int64_t)bh * IC::head_bytes(IDT);
@@ -592,8 +585,7 @@ struct ApplyCfg {
 // queries, a step ahead, where registers allow (bf16 in and out).  `other`
 // may be `o` itself: each lane reads its elements before it writes them.
 //
-// img: the operands as the combine left them; null (bf16): each workgroup
-// makes them from src, and where that holds partial sums the first of a head
+// img: the operands as the combine left them; null: each workgroup makes them from src, and where that holds partial sums the first of a head
 // writes their FP64 sum if it is a result.
 struct ApplySrc {
   const double *M, *v;     // FP64 summary, or
@@ -781,21 +773,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
   // (the first of the head's two, S^T operands) into LDS
   QRegs qa, qb;
   if (nk > 0) load_q(tok(0), qa);
-  if (DT != DT_BF16 || img) {
+  if (img) {
     const u32x4* from = (const u32x4*)((const char*)img + (int64_t)bh * IC::head_bytes(DT));
     for (int w = threadIdx.x; w < IMG_WORDS; w += 256) simg[w] = from[w];
-  } else if constexpr (DT == DT_BF16) {
+  } else {
     const MatrixSrc<D> s{src.M ? src.M + (int64_t)bh * D * D : nullptr,
                          src.v ? src.v + (int64_t)bh * D : nullptr,
                          src.part ? src.part + (int64_t)bh * src.P * (D * D + D) : nullptr, src.P};
     if (!src.part) {
-      make_image<D, 2, true, 0, 256>(simg, s);
-      make_z_tile<D, 0>(simg + IC::mat_bytes(DT) / 16, s);
+      make_image<DT, D, 2, true, 0, 256>(simg, s);
+      make_z_tile<DT, D, 0>(simg + IC::mat_bytes(DT) / 16, s);
     } else {
       by_partials(src.P, [&](auto pn) {
         constexpr int PN = decltype(pn)::value;
-        make_image<D, 2, true, PN, 256>(simg, s);
-        make_z_tile<D, PN>(simg + IC::mat_bytes(DT) / 16, s);
+        make_image<DT, D, 2, true, PN, 256>(simg, s);
+        make_z_tile<DT, D, PN>(simg + IC::mat_bytes(DT) / 16, s);
         if (src.M_out && blockIdx.x == 0) {
           double x[2];
           for (int u = threadIdx.x; u < (D * D + D) / 2; u += 256) {
@@ -913,9 +905,9 @@ static void launch_combine_d(const float* part, int P, double* M64, double* v64,
   const dim3 grid(D / 8 + 1, (unsigned)BH);
   constexpr int E = D * D + D;
   if (img_dt == DT_BF16)
-    combine_kernel<D, DT_BF16, float><<<grid, 8 * D, 0, stream>>>(part, part + D * D, E, E, P, M64, v64, img, what);
+    combine_kernel<D, DT_BF16><<<grid, 8 * D, 0, stream>>>(part, P, M64, v64, img, what);
   else
-    combine_kernel<D, DT_FP32, float><<<grid, 8 * D, 0, stream>>>(part, part + D * D, E, E, P, M64, v64, img, what);
+    combine_kernel<D, DT_FP32><<<grid, 8 * D, 0, stream>>>(part, P, M64, v64, img, what);
 }
 
 hipError_t launch_combine(const float* part, int P, double* M64, double* v64, void* img,
@@ -940,7 +932,7 @@ static hipError_t launch_forward_d(const FwdArgs& a) {
   launch_summary_d<D>(MODE_FWD, a.in_dt, a.k, a.v, a.sb, a.sh, a.sn, a.B, a.H, a.N, a.P, a.Tw,
                       a.team, nullptr, a.part, a.stream);
   // few partials: the apply's workgroups add them up themselves
-  if (a.in_dt == DT_BF16 && fold_partials(a.P, a.Ga, BH, D))
+  if (!fp32_rows(a.in_dt, D) && fold_partials(a.P, a.Ga, BH, D))
     return launch_apply_only<D>(a, nullptr, ApplySrc{nullptr, nullptr, a.part, a.P,
                                                      a.want_summary ? a.S64 : nullptr, a.z64});
   {
@@ -991,12 +983,7 @@ hipError_t launch_forward(const FwdArgs& a) {
 template <int D>
 static hipError_t launch_apply_d(const FwdArgs& a) {
   if (fp32_rows(a.in_dt, D)) return launch_apply_fp32(a);
-  if (a.in_dt == DT_BF16)
-    return launch_apply_only<D>(a, nullptr, ApplySrc{a.S64, a.z64, nullptr, 0, nullptr, nullptr});
-  const hipError_t e =
-      launch_images(a.S64, a.z64, a.img, a.in_dt, a.B * a.H, D, IMG_T | IMG_Z, a.stream);
-  if (e != hipSuccess) return e;
-  return launch_apply_only<D>(a, a.img, ApplySrc{});
+  return launch_apply_only<D>(a, nullptr, ApplySrc{a.S64, a.z64, nullptr, 0, nullptr, nullptr});
 }
 
 hipError_t launch_apply(const FwdArgs& a) {
@@ -1007,29 +994,6 @@ hipError_t launch_apply(const FwdArgs& a) {
     case 128: return launch_apply_d<128>(a);
   }
   return hipErrorInvalidValue;
-}
-
-template <int D>
-static void launch_images_d(const double* M64, const double* v64, void* img, int img_dt, int64_t BH,
-                            int what, hipStream_t stream) {
-  const dim3 grid(D / 8 + 1, (unsigned)BH);
-  if (img_dt == DT_BF16)
-    combine_kernel<D, DT_BF16, double><<<grid, 8 * D, 0, stream>>>(M64, v64, D * D, D, 1, nullptr, nullptr, img, what);
-  else
-    combine_kernel<D, DT_FP32, double><<<grid, 8 * D, 0, stream>>>(M64, v64, D * D, D, 1, nullptr, nullptr, img, what);
-}
-
-hipError_t launch_images(const double* M64, const double* v64, void* img, int img_dt, int64_t BH,
-                         int D, int what, hipStream_t stream) {
-  ProfScope prof("images", stream);
-  switch (D) {
-    case 16: launch_images_d<16>(M64, v64, img, img_dt, BH, what, stream); break;
-    case 32: launch_images_d<32>(M64, v64, img, img_dt, BH, what, stream); break;
-    case 64: launch_images_d<64>(M64, v64, img, img_dt, BH, what, stream); break;
-    case 128: launch_images_d<128>(M64, v64, img, img_dt, BH, what, stream); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
 }
 
 }  // namespace la

@@ -212,10 +212,10 @@ struct MatrixSrc {
   }
 };
 
-// Operands of a bf16 kernel, made in LDS by NTH threads: the T or N image's
-// matrix tiles (PARTS = 2: hi and lo parts, 1: hi parts), the z tile.  Small
+// A kernel's operands, made in LDS by NTH threads: the T or N image's matrix
+// tiles (bf16, PARTS = 2: hi and lo parts, 1: hi parts), the z tile.  Small
 // grids wait for these loads: 8 or 16 bytes wide.
-template <int D, int PARTS, bool TRANSPOSED, int PN, int NTH>
+template <int DT, int D, int PARTS, bool TRANSPOSED, int PN, int NTH>
 __device__ __forceinline__ void make_image(u32x4* dst, const MatrixSrc<D>& s) {
   if constexpr (TRANSPOSED) {
     constexpr int W = 2;  // eight rows' runs of two columns
@@ -231,8 +231,8 @@ __device__ __forceinline__ void make_image(u32x4* dst, const MatrixSrc<D>& s) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) y[j] = x[j][c];
         int i, m;
-        image_row<D, DT_BF16>(c0 + c, i, m);
-        put_image8<D, DT_BF16, PARTS>((char*)dst, i, m, k0, y, true);
+        image_row<D, DT>(c0 + c, i, m);
+        put_image8<D, DT, PARTS>((char*)dst, i, m, k0, y, true);
       }
     }
   } else {
@@ -244,19 +244,19 @@ __device__ __forceinline__ void make_image(u32x4* dst, const MatrixSrc<D>& s) {
 #pragma unroll
       for (int j = 0; j < 8; j += W) s.template get<PN, W>(row * D + k0 + j, false, x + j);
       int i, m;
-      image_row<D, DT_BF16>(row, i, m);
-      put_image8<D, DT_BF16, PARTS>((char*)dst, i, m, k0, x, true);
+      image_row<D, DT>(row, i, m);
+      put_image8<D, DT, PARTS>((char*)dst, i, m, k0, x, true);
     }
   }
 }
-template <int D, int PN>
+template <int DT, int D, int PN>
 __device__ __forceinline__ void make_z_tile(u32x4* dst, const MatrixSrc<D>& s) {
   if (threadIdx.x < 2 * D) {
     const int k0 = 8 * (threadIdx.x >> 4);
     double x[8];
 #pragma unroll
     for (int j = 0; j < 8; j += 2) s.template get<PN, 2>(k0 + j, true, x + j);
-    put_image8<D, DT_BF16>((char*)dst, 0, threadIdx.x & 15, k0, x, true);
+    put_image8<D, DT>((char*)dst, 0, threadIdx.x & 15, k0, x, true);
   }
 }
 // f(PN) for the loads that P partials take
@@ -345,8 +345,5 @@ hipError_t launch_backward(const BwdArgs& a);
 constexpr bool fp32_rows(int dt, int D) { return dt == DT_FP32 && D >= 64; }
 hipError_t launch_apply_fp32(const FwdArgs& a);
 hipError_t launch_backward_fp32(const BwdArgs& a);
-// The operands `what` of a given M and v.
-hipError_t launch_images(const double* M64, const double* v64, void* img, int img_dt, int64_t BH,
-                         int D, int what, hipStream_t stream);
 
 }  // namespace la
