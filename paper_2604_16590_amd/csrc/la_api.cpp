@@ -58,7 +58,6 @@ la_status check_desc(const la_attn_desc* d) {
 struct Tiling {
   int P;   // partial sums per (b, h)
   int Tw;  // tokens per partial (a multiple of 64, at most max_fp32_run)
-  int Tk;  // tokens per workgroup of the key (and two-pass query) backward
 };
 
 // The longest token range any kernel sums in FP32: each partial sum covers
@@ -125,9 +124,6 @@ Tiling choose_tiling(int64_t N, int d, int dt, bool backward) {
   Tiling t;
   t.P = (int)P;
   t.Tw = (int)Tw;
-  // per-token kernels: no cross-token sums, so these ranges change no bits
-  // (measured: the key backward is fastest at 2048 tokens per workgroup)
-  t.Tk = (int)std::min<int64_t>(2048, ceil_div(N, 64) * 64);
   return t;
 }
 
@@ -213,7 +209,16 @@ Layout layout_for(const la_attn_desc* d, int pass) {
   return L;
 }
 
-// The gate's arguments (the attention's own are checked by the caller).
+// Tokens per workgroup of the two-pass query backward (d = 16, fp32 d = 32):
+// per-token work as the apply's, up to 2,048 once the grid has 1,024
+// workgroups (2 heads of 8,699 fp32 tokens at d = 32: 10 us, 41 with ten
+// workgroups; 1,024 of 1,000 bf16 tokens, d = 16, 23 us, 28 with four each).
+int query_tokens(int64_t N, int64_t BH, int dt) {
+  const int64_t blk = dt == LA_FP32 ? 64 : 128;  // tokens per block (4 waves x 16 x TT)
+  const int64_t g = std::min(ceil_div(N, blk), std::max(ceil_div(N, 2048), ceil_div(1024, BH)));
+  return (int)(ceil_div(ceil_div(N, g), blk) * blk);
+}
+
 // Key-backward workgroups per head, as apply_groups (fp32 takes one tile per
 // wave step; at d >= 64 it has its own grid).  A bf16 workgroup stages 64 KB
 // of operands at d = 128 and 16 at d = 64: at least 1,024 (512) tokens each
@@ -231,6 +236,7 @@ int key_groups(int64_t N, int64_t BH, int d, int dt) {
   return (int)std::max<int64_t>(1, g);
 }
 
+// The gate's arguments (the attention's own are checked by the caller).
 la_status check_gate(const void* other, const double* sigma, double sigma_data) {
   if (!other || !sigma) return LA_ERR_INVALID_ARG;
   if (!aligned16(other) || ((uintptr_t)sigma & 7u)) return LA_ERR_INVALID_ARG;
@@ -397,7 +403,7 @@ la_status la_backward(const la_attn_desc* desc, const void* q, const void* k,
   a.q = q; a.k = k; a.v = v; a.dout = dout;
   a.dq = dq; a.dk = dk; a.dv = dv;
   a.S64 = s; a.z64 = z;
-  a.P = t.P; a.Tw = t.Tw; a.Ta = t.Tk;
+  a.P = t.P; a.Tw = t.Tw; a.Ta = query_tokens(desc->N, desc->B * desc->H, desc->in_dtype);
   a.Gk = key_groups(desc->N, desc->B * desc->H, (int)desc->d, desc->in_dtype);
   a.img = w + L.img;
   a.part = (float*)(w + L.part);
