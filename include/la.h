@@ -104,14 +104,16 @@ la_status la_version(int32_t* major, int32_t* minor);
  * per-tile partial sums of the token reduction.  Each partial sums at most
  * 16,384 tokens (bf16 inputs; 4,096 for fp32) in FP32 before the partials
  * are added in FP64, so the FP32 part of every sum over tokens is bounded
- * whatever N is; the partial count is 128 (d = 128) or 64 (d < 128) until
+ * whatever N is; there are at most 128 partials (d = 128) or 64 (d < 128) until
  * that bound is reached (2,097,152 or 1,048,576 bf16 tokens per head) and
  * grows with N beyond it, by (d*d + d) * 4 bytes per 16,384 tokens per
  * head (0.8 % of the bytes of K and V at d = 128).  Where the backward runs
  * its query pass and its dS reduction separately (fp32 inputs, and
  * d = 16) it adds 8 bytes per (b, h, token) for the per-query pair
  * (1/den, dden) passed between them; bf16 at d >= 32 runs them as one pass
- * and needs no such buffer.
+ * and needs no such buffer.  With a somewhat smaller workspace, down to one
+ * partial for 2,048 (d = 128) or 512 tokens, a pass runs in parts of its
+ * heads, with the same results; below, LA_ERR_OOM.
  */
 la_status la_workspace_size(const la_attn_desc* desc, int32_t pass, size_t* bytes);
 
@@ -135,8 +137,8 @@ la_status la_forward(const la_attn_desc* desc, const void* q, const void* k,
  * until the process ends, so the call itself allocates nothing.  Arguments
  * and results are those of la_forward (same kernels, so the same bits);
  * the array of the CURRENT device is used, and `stream` must belong to that
- * device.  LA_ERR_OOM when la_workspace_size(desc, 0) exceeds the array
- * (bf16 inputs: 8 heads at d = 128 fit up to 4,079,616 tokens each,
+ * device.  A problem whose workspace exceeds the array runs in parts of its
+ * heads; LA_ERR_OOM beyond that (bf16 inputs: 8 heads at d = 128 fit up to 4,079,616 tokens each,
  * 64 heads at d = 64 up to 1,982,464; fp32 inputs, 8 heads at d = 128: up
  * to 1,019,904).  All calls on one device share its
  * array: calls whose work overlaps on the device (different streams, or

@@ -175,7 +175,7 @@ struct Layout {
 };
 
 // Forward: [part][S64][z64][img].  Apply: [img].
-// Backward: [img][part][stash][dS64][dz64][dimg]; the stash holds two floats
+// Backward: [part][stash][dS64][dz64][dimg]; the stash holds two floats
 // per query token (1/den, -(dO . O)) between the query kernel and the dS
 // reduction, the only part of any workspace that grows with N.  bf16 at
 // d >= 32 fuses the two passes and needs no stash.
@@ -197,7 +197,6 @@ Layout layout_for(const la_attn_desc* d, int pass) {
     L.z64 = off; off += vec;
     L.img = off; off += img;
   } else {
-    L.img = off; off += img;
     L.part = off; off += part;
     L.stash = off;
     if (!fused_backward((int)D, d->in_dtype)) off += align_up((size_t)BH * d->N * 2 * sizeof(float));
@@ -207,6 +206,77 @@ Layout layout_for(const la_attn_desc* d, int pass) {
   }
   L.total = off;
   return L;
+}
+
+}  // namespace
+
+// The workspace that a pass has always taken: two operand images of S (and dS)
+// and a partial for 2,048 (d = 128) or 512 tokens.  Short sequences are cut
+// finer now, up to 3.3 times this (fp32, d = 128); with less than they want,
+// but this much, a problem runs in parts of its heads.
+namespace la {
+size_t least_workspace(const la_attn_desc* d, int pass) {
+  const int64_t BH = d->B * d->H, D = d->d;
+  int64_t P = std::max(std::min(max_partials((int)D), ceil_div(d->N, D >= 128 ? 2048 : 512)),
+                       ceil_div(d->N, max_fp32_run(d->in_dtype)));
+  P = ceil_div(d->N, ceil_div(ceil_div(d->N, P), 64) * 64);
+  const size_t part = align_up((size_t)BH * P * (D * D + D) * sizeof(float));
+  const size_t sums = align_up((size_t)BH * D * D * sizeof(double)) + align_up((size_t)BH * D * sizeof(double));
+  const size_t img = align_up((size_t)BH * head_image_bytes((int)D, d->in_dtype));
+  if (pass == 2) return img;
+  if (pass == 0) return part + sums + img;
+  const size_t stash =
+      fused_backward((int)D, d->in_dtype) ? 0 : align_up((size_t)BH * d->N * 2 * sizeof(float));
+  return part + stash + sums + 2 * img;
+}
+}  // namespace la
+
+namespace {
+
+// The largest number of batch elements, or of heads of one, whose workspace
+// fits ws_bytes (0: not even one head's).
+struct Part {
+  int64_t B, H;
+};
+Part part_for(const la_attn_desc* d, int pass, size_t ws_bytes) {
+  la_attn_desc p = *d;
+  auto most = [&](int64_t& n) {  // the total is monotonic in n
+    int64_t lo = 0, hi = n;
+    while (lo < hi) {
+      n = (lo + hi + 1) / 2;
+      if (layout_for(&p, pass).total <= ws_bytes) lo = n; else hi = n - 1;
+    }
+    return lo;
+  };
+  if (const int64_t b = most(p.B)) return {b, d->H};
+  p.B = 1;
+  return {1, most(p.H)};
+}
+
+// Calls f(part's descriptor, its first b, its first h) for parts of the
+// problem that fit ws_bytes, one after the other.  A head's result does not
+// depend on the others in a call, so the bits are those of one call.
+template <class F>
+la_status in_parts(const la_attn_desc* desc, int pass, size_t ws_bytes, F&& f) {
+  const Part most = part_for(desc, pass, ws_bytes);
+  if (ws_bytes < la::least_workspace(desc, pass) || !most.H) return LA_ERR_OOM;
+  for (int64_t b = 0; b < desc->B; b += most.B)
+    for (int64_t h = 0; h < desc->H; h += most.H) {
+      la_attn_desc p = *desc;
+      p.B = std::min(most.B, desc->B - b);
+      p.H = std::min(most.H, desc->H - h);
+      const la_status st = f(&p, b, h);
+      if (st != LA_OK) return st;
+    }
+  return LA_OK;
+}
+
+// Byte offsets of element (b, h, 0, 0) of the tensors in in_s*, out_s*.
+int64_t in_offset(const la_attn_desc* d, int64_t b, int64_t h) {
+  return (b * d->in_sb + h * d->in_sh) * elem_size(d->in_dtype);
+}
+int64_t out_offset(const la_attn_desc* d, int64_t b, int64_t h) {
+  return (b * d->out_sb + h * d->out_sh) * elem_size(d->out_dtype);
 }
 
 // Tokens per workgroup of the two-pass query backward (d = 16, fp32 d = 32):
@@ -255,7 +325,15 @@ la_status forward_impl(const la_attn_desc* desc, const void* q, const void* k, c
   if (((uintptr_t)ws % kAlign) != 0) return LA_ERR_INVALID_ARG;
   if (((uintptr_t)s_out & 7u) || ((uintptr_t)z_out & 7u)) return LA_ERR_INVALID_ARG;
   const Layout L = layout_for(desc, 0);
-  if (ws_bytes < L.total) return LA_ERR_OOM;
+  if (ws_bytes < L.total)
+    return in_parts(desc, 0, ws_bytes, [&](const la_attn_desc* p, int64_t b, int64_t h) {
+      const int64_t i = in_offset(desc, b, h), j = out_offset(desc, b, h);
+      const int64_t bh = b * desc->H + h, d = desc->d;
+      return forward_impl(p, (const char*)q + i, (const char*)k + i, (const char*)v + i, (char*)o + j,
+                          s_out ? s_out + bh * d * d : nullptr, z_out ? z_out + bh * d : nullptr, ws,
+                          ws_bytes, stream, other ? (const char*)other + j : nullptr,
+                          sigma ? sigma + b : nullptr, sigma_data);
+    });
   const Tiling t = choose_tiling(desc->N, (int)desc->d, desc->in_dtype, false);
   char* w = (char*)ws;
   la::FwdArgs a{};
@@ -392,7 +470,14 @@ la_status la_backward(const la_attn_desc* desc, const void* q, const void* k,
   if (((uintptr_t)s & 7u) || ((uintptr_t)z & 7u)) return LA_ERR_INVALID_ARG;
   if (((uintptr_t)ws % kAlign) != 0) return LA_ERR_INVALID_ARG;
   const Layout L = layout_for(desc, 1);
-  if (ws_bytes < L.total) return LA_ERR_OOM;
+  if (ws_bytes < L.total)
+    return in_parts(desc, 1, ws_bytes, [&](const la_attn_desc* p, int64_t b, int64_t h) {
+      const int64_t i = in_offset(desc, b, h), j = out_offset(desc, b, h);
+      const int64_t bh = b * desc->H + h, d = desc->d;
+      return la_backward(p, (const char*)q + i, (const char*)k + i, (const char*)v + i, s + bh * d * d,
+                         z + bh * d, (const char*)dout + i, (char*)dq + j, (char*)dk + j, (char*)dv + j,
+                         ws, ws_bytes, stream);
+    });
   const Tiling t = choose_tiling(desc->N, (int)desc->d, desc->in_dtype, true);
   char* w = (char*)ws;
   la::BwdArgs a{};
@@ -405,7 +490,6 @@ la_status la_backward(const la_attn_desc* desc, const void* q, const void* k,
   a.S64 = s; a.z64 = z;
   a.P = t.P; a.Tw = t.Tw; a.Ta = query_tokens(desc->N, desc->B * desc->H, desc->in_dtype);
   a.Gk = key_groups(desc->N, desc->B * desc->H, (int)desc->d, desc->in_dtype);
-  a.img = w + L.img;
   a.part = (float*)(w + L.part);
   a.stash = (float2*)(w + L.stash);
   a.dS64 = (double*)(w + L.dS64);

@@ -71,7 +71,7 @@ __device__ __forceinline__ void summary_load(const char* kh, const char* vh, uin
   }
 }
 
-// A partial's tokens are summed in runs of Tq (summary_runs), from zero each,
+// A partial's tokens are summed in runs of Tq (summary_run), from zero each,
 // and the runs' sums added in order in FP32, so the same bits come of two
 // forms:
 // NW = 1: a wave to a partial takes its runs one after the other and keeps
@@ -84,9 +84,8 @@ __device__ __forceinline__ void summary_load(const char* kh, const char* vh, uin
 // NW > 1: one workgroup per (partial, (b, h)), in the same order, a wave to a
 // run.  A few heads are NW times as many waves for the same partials in
 // memory (a head of 1,700,000 tokens at d = 32: 86 us, 417 with a wave to a
-// partial; two of 300,000 at d = 64: 51, 175; one of 4,096 fp32 tokens at
-// d = 64, when fp32 took this kernel: 16, 45).  Each XCD takes a contiguous share of the items (workgroups go
-// to the eight in turn).
+// partial; two of 300,000 at d = 64: 51, 175).  Each XCD takes a contiguous
+// share of the items (workgroups go to the eight in turn).
 // (fp32 inputs at d >= 32 take summary_split_kernel.)
 template <int DT, int D, int MODE, int NW>
 __global__ __launch_bounds__(NW == 1 ? 256 : 64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 16 ? 4 : SummaryCfg<DT, D, MODE>::WAVES_PER_SIMD))) void summary_kernel(

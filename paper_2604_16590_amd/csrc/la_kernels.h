@@ -1,6 +1,7 @@
 // la_kernels.h -- launch arguments, operand-image layout and launcher
 // declarations of the gfx950 kernels (internal to liblinattn).
 #pragma once
+#include "../../include/la.h"
 #include "la_device.h"
 
 namespace la {
@@ -313,7 +314,6 @@ struct BwdArgs {
   const double *S64, *z64;
   int P, Tw, Ta;       // Ta: tokens per workgroup of the two-pass query kernel
   int Gk;              // key-backward workgroups per head (they take its token blocks in turn)
-  void* img;           // images of S (fp32 inputs at d <= 32, d = 16)
   float* part;         // partials of dS, dz
   float2* stash;       // [BH][N] per query token: (1/den, -(dO . O))
   double* dS64;
@@ -328,7 +328,7 @@ enum { MODE_FWD = 0, MODE_BWD = 1 };
 int32_t record_hip_error(int32_t e);
 
 hipError_t launch_forward(const FwdArgs& a);
-// Apply only: images of a given S (into a.img), then the apply kernel.
+// Apply only, of a given S and z.
 hipError_t launch_apply(const FwdArgs& a);
 // Token-reduction kernel: forward summary (MODE_FWD) or the dS/dz sums of
 // the backward (MODE_BWD, k = Q, v = dO, stash = per-token (1/den, -(dO . O))).
@@ -345,5 +345,8 @@ hipError_t launch_backward(const BwdArgs& a);
 constexpr bool fp32_rows(int dt, int D) { return dt == DT_FP32 && D >= 64; }
 hipError_t launch_apply_fp32(const FwdArgs& a);
 hipError_t launch_backward_fp32(const BwdArgs& a);
+
+// The least workspace, in bytes, with which a pass (as la_workspace_size's) runs.
+size_t least_workspace(const la_attn_desc* d, int pass);
 
 }  // namespace la

@@ -55,7 +55,7 @@ extern "C" la_status la_forward_noalloc(const la_attn_desc* desc, const void* q,
   size_t need = 0;
   la_status st = la_workspace_size(desc, 0, &need);
   if (st != LA_OK) return st;
-  if (need > kScratchBytes) return LA_ERR_OOM;  // beyond the fixed array
+  if (la::least_workspace(desc, 0) > kScratchBytes) return LA_ERR_OOM;  // beyond the fixed array
   void* ws = nullptr;
   st = scratch_for_current_device(&ws);
   if (st != LA_OK) return st;

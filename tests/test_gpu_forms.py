@@ -265,3 +265,53 @@ def test_tiled_forms(dims, core, halo, H, d):
     flat = tuple(dims) + (H * d,)
     ref = oracle_tiled(*(x.reshape(flat) for x in (q, k, v)), dims, core, halo, H, d)
     assert normwise(as64(o).reshape(1, 1, -1), ref.reshape(1, 1, -1)) < TOL["bf16"]
+
+
+# a workspace smaller than la_workspace_size: parts of the heads, one after the
+# other, with the same bits and nothing written beyond it
+@pytest.mark.parametrize("layout", ["bhnd", "bnhd"])
+@pytest.mark.parametrize("d,dtype,N", [(128, "fp32", 3849), (16, "bf16", 963)])
+@pytest.mark.parametrize("B,H,room", [(1, 3, (1, 1)), (1, 5, (1, 2)), (3, 2, (2, 2)), (3, 2, (1, 2))])
+def test_small_workspace(B, H, room, d, dtype, N, layout):
+    import ctypes
+    from paper_2604_16590_amd import _binding as BB
+    dev = require_gpu()
+    host = make_inputs((B, H, N, d), dtype, seed=9, streams=(0, 1, 2, 3))
+    q, k, v, g = (to_device(x, dev) for x in host)
+    if layout == "bnhd":
+        q, k, v, g = (x.permute(0, 2, 1, 3).contiguous().permute(0, 2, 1, 3) for x in (q, k, v, g))
+    sigma = torch.linspace(0.1, 2.0, B, dtype=torch.float64, device=dev)
+    want = la.forward_gated(q, k, v, g, sigma, out=torch.empty_like(q), return_summary=True)
+    grads = la.backward(q, k, v, want[1], want[2], g)
+    desc = BB.make_desc(q, want[0])
+    small = BB.AttnDesc(room[0], room[1], *[getattr(desc, f) for f, _ in BB.AttnDesc._fields_[2:]])
+    got = [torch.full_like(x, float("nan")) for x in want]
+    ggot = [torch.full_like(x, float("nan")) for x in grads]
+    gdesc = BB.make_desc(q, grads[0])
+    st = BB._stream(q.device)
+
+    def call(pass_, nbytes, ws):
+        if pass_ == 0:
+            return BB.lib().la_forward_gated(
+                ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), g.data_ptr(), sigma.data_ptr(),
+                0.5, got[0].data_ptr(), got[1].data_ptr(), got[2].data_ptr(), ws.data_ptr(), nbytes, st)
+        return BB.lib().la_backward(
+            ctypes.byref(gdesc), q.data_ptr(), k.data_ptr(), v.data_ptr(), want[1].data_ptr(), want[2].data_ptr(),
+            g.data_ptr(), *[x.data_ptr() for x in ggot], ws.data_ptr(), nbytes, st)
+
+    up = lambda n: -(-n // 256) * 256
+    parts = -(-N // (2048 if d == 128 else 512))  # the least: a partial for so many tokens
+    images = BB.workspace_size(desc, 2)
+    least = up(B * H * parts * (d * d + d) * 4) + up(B * H * d * d * 8) + up(B * H * d * 8) + images
+    stash = up(B * H * N * 8)
+    for pass_, low in ((0, least), (1, least + stash + images)):
+        nbytes = max(BB.workspace_size(small, pass_), low)
+        assert nbytes < BB.workspace_size(desc, pass_)
+        ws = torch.zeros(nbytes + 4096, dtype=torch.uint8, device=dev)
+        ws[nbytes:] = 0xA5
+        assert call(pass_, nbytes, ws) == 0
+        torch.cuda.synchronize()
+        assert bool((ws[nbytes:] == 0xA5).all())
+        assert call(pass_, low - 256, ws) == 3  # LA_ERR_OOM
+    for x, y in zip(tuple(want) + tuple(grads), got + ggot):
+        assert torch.equal(x, y)
