@@ -26,7 +26,6 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, 8 TB/s
 BF16_PEAK_TFLOPS = 2500.0      # dense MFMA bf16
-FP32_PEAK_TFLOPS = 157.3       # fp32 (matrix and vector)
 
 METRIC = "attn tokens/s fwd & fwd+bwd at 2M tok, BF16 vs FP32; serve p50/p99 ms"
 WORKLOAD = dict(B=1, H=8, N=2097152, d=128, grid=(256, 64, 128), std_qkv=0.5 ** 0.5)
@@ -81,7 +80,8 @@ def kernel_mma(dtype, d):
     Only the method's products count (operand re-layout products do not).
     bf16 applies S (and, in the query backward, S again) as two operands
     hi + lo, so those products count twice; the fused query backward at
-    d = 128 uses the hi part only.  fp32 applies S as one fp32 operand.
+    d = 128 uses the hi part only.  fp32 applies S as one fp32 operand; at
+    d >= 64 each of its products is six of bf16 parts.
     """
     two = 2 if dtype == "bf16" else 1
     return {"summary_fwd": 1, "apply": two, "bwd_query": two, "summary_bwd": 1,
@@ -164,7 +164,7 @@ def kernel_table(stats, steps, elems, esize):
 # the sources the long-context step's kernels and their launch choices are
 # built from (the counter figures go stale when any of these changes)
 STEP_SOURCES = ("la_api.cpp", "la_backward.hip", "la_device.h", "la_forward.hip",
-                "la_kernels.h", "la_profile.cpp", "la_profile.h", "la_summary.h")
+                "la_kernels.h", "la_profile.cpp", "la_profile.h", "la_split.h", "la_summary.h")
 
 
 # the sources of the fused tiled step's kernels
@@ -472,13 +472,12 @@ def cpu_baseline_other_workloads():
 # ---- profile summaries (host only) ----
 
 # attention kernels of the long-context step, by the demangled name's start
-PROFILE_KERNELS = (("la::summary_kernel<0, 128, 0>", "summary_fwd"),
+PROFILE_KERNELS = (("la::summary_kernel<0, 128, 0", "summary_fwd"),
                    ("la::combine_kernel<128, 0>", "combine"),
                    ("la::apply_kernel<0, 0, 128, false>", "apply"),
-                   ("la::image_kernel<128>", "images"),
                    ("la::bwd_qds4_kernel<0>", "bwd_query_ds"),
                    ("la::combine_kernel<128, 1>", "combine_bwd"),
-                   ("la::bwd_key_kernel<0, 0, 128, 3>", "bwd_key"))
+                   ("la::bwd_key_kernel<0, 0, 128", "bwd_key"))
 COPY_KERNEL = "stream_copy_swept_kernel"
 
 
@@ -655,7 +654,7 @@ def summarize_profiles(top, prof=None):
 # the fused tiled step's kernels (d = 64) and their algorithmic field
 # passes: K and V read by the column walks, Q read and O written by the
 # apply; the slot pass moves workspace only
-TILED_KERNELS = (("tile_cols_kernel<64>", "tile_cols", 2), ("tile_slot_kernel<64>", "tile_slots", 0),
+TILED_KERNELS = (("tile_cols_kernel<64", "tile_cols", 2), ("tile_slot_kernel<64>", "tile_slots", 0),
                  ("tile_apply_kernel<64>", "tile_apply", 2))
 
 
@@ -933,7 +932,7 @@ def main():
         fp32 = {"fwd_bwd_tokens_per_s": round(tokens / t32, 1), "fwd_tokens_per_s": round(tokens / t32f, 1),
                 "ms_per_step": round(t32 * 1e3, 3), "fwd_ms": round(t32f * 1e3, 3),
                 "kernels_ms": {k: v["avg_ms"] for k, v in k32.items()},
-                "mma_frac_of_fp32_peak": round(mma32 / t32 / 1e12 / FP32_PEAK_TFLOPS, 4)}
+                "mma_frac_of_bf16_peak": round(6 * mma32 / t32 / 1e12 / BF16_PEAK_TFLOPS, 4)}
         log("fp32 fwd+bwd %.3f ms" % (t32 * 1e3))
         del p32, xs
         torch.cuda.empty_cache()
