@@ -890,6 +890,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void b
     stage_image(timg, head, ONE, DT == DT_BF16);
     stage_image(nimg, head + IC::img_bytes(DT) / 16, ONE, DT == DT_BF16);
     if (threadIdx.x < D) dzl[threadIdx.x] = (DzT)dz64[(int64_t)bh * D + threadIdx.x];
+  } else if (D <= 32 && P > 4) {
+    __shared__ double sum[D <= 32 ? D * D + D : 1];
+    sum_partials<D <= 32 ? D : 16, 256>(sum, part + (int64_t)bh * P * (D * D + D), P);
+    const MatrixSrc<D> src{sum, sum + D * D, nullptr, 0};
+    make_image<DT, D, 1, true, 0, 256>(timg, src);
+    make_image<DT, D, 1, false, 0, 256>(nimg, src);
+    if (threadIdx.x < D) dzl[threadIdx.x] = (DzT)sum[D * D + threadIdx.x];
   } else {
     // few partials of dS, dz: added up here
     const MatrixSrc<D> src{nullptr, nullptr, part + (int64_t)bh * P * (D * D + D), P};

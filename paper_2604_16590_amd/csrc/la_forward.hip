@@ -584,7 +584,8 @@ struct ApplyCfg {
 // queries, a step ahead, where registers allow (bf16 in and out).  `other`
 // may be `o` itself: each lane reads its elements before it writes them.
 //
-// img: the operands as the combine left them; null: each workgroup makes them from src, and where that holds partial sums the first of a head
+// img: the operands as the combine left them; null: each workgroup makes
+// them from src, and where that holds partial sums the first of a head
 // writes their FP64 sum if it is a result.
 struct ApplySrc {
   const double *M, *v;     // FP64 summary, or
@@ -779,7 +780,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
     const MatrixSrc<D> s{src.M ? src.M + (int64_t)bh * D * D : nullptr,
                          src.v ? src.v + (int64_t)bh * D : nullptr,
                          src.part ? src.part + (int64_t)bh * src.P * (D * D + D) : nullptr, src.P};
-    if (!src.part) {
+    constexpr bool MANY = D <= 32;
+    __shared__ double sum[MANY ? D * D + D : 1];
+    if (MANY && src.part && src.P > 4) {
+      sum_partials<MANY ? D : 16, 256>(sum, s.part, src.P);
+      const MatrixSrc<D> t{sum, sum + D * D, nullptr, 0};
+      make_image<DT, D, 2, true, 0, 256>(simg, t);
+      make_z_tile<DT, D, 0>(simg + IC::mat_bytes(DT) / 16, t);
+      if (src.M_out && blockIdx.x == 0)
+        for (int u = threadIdx.x; u < D * D + D; u += 256) {
+          if (u < D * D) src.M_out[(int64_t)bh * D * D + u] = sum[u];
+          else src.v_out[(int64_t)bh * D + u - D * D] = sum[u];
+        }
+    } else if (!src.part) {
       make_image<DT, D, 2, true, 0, 256>(simg, s);
       make_z_tile<DT, D, 0>(simg + IC::mat_bytes(DT) / 16, s);
     } else {

@@ -268,6 +268,36 @@ __device__ __forceinline__ void by_partials(int P, F&& f) {
   else f(std::integral_constant<int, 4>{});
 }
 
+// The sum of 5 to 16 partials (d <= 32), in the combine's order: quarters of
+// them in order, then (q0 + q1) + (q2 + q3).  NTH threads put the matrix and
+// the vector behind it into `sum`, two elements each with all sixteen loads
+// in flight (no branch divides them); ends in a barrier.
+template <int D, int NTH>
+__device__ __forceinline__ void sum_partials(double* sum, const float* part, int P) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  constexpr int E = D * D + D;
+  const int pq = (P + 3) / 4;
+  for (int u = 2 * threadIdx.x; u < E; u += 2 * NTH) {
+    f32x2 x[4][4];
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) x[w][k] = *(const f32x2*)(part + min(w * pq + k, P - 1) * E + u);
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      double q[4];
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        q[w] = 0.0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) q[w] += k < pq && w * pq + k < P ? (double)x[w][k][r] : 0.0;
+      }
+      sum[u + r] = (q[0] + q[1]) + (q[2] + q[3]);
+    }
+  }
+  __syncthreads();
+}
+
 // Whether the G workgroups of each head add up its P partials themselves
 // instead of a combine before them.  On a full chip the partials cost their
 // bytes G times over.  Apply and key pass against the same with a combine
@@ -277,9 +307,11 @@ __device__ __forceinline__ void by_partials(int P, F&& f) {
 // and 32 + 8, and 512 heads x 1,024, d = 64 (P = 4, G = 4 and 8) 64 + 97 and
 // 38 + 70 + 42.  A small grid waits some 4 us for 100 KB and 6 us for a
 // combine: 4 heads x 1,024, d = 128 (P = 2) 23 + 14 us and 16 + 16 + 13, 4 x
-// 2,048 (P = 4) 28 + 20 and 17 + 15 + 13.
+// 2,048 (P = 4) 28 + 20 and 17 + 15 + 13; at d <= 32 up to sixteen partials (2 x
+// 8 heads x 4,000, d = 32: 46 us for the pass, 59; with 64 partials of two
+// heads x 30,001, d = 16, 58 and 54).
 inline bool fold_partials(int P, int G, int64_t heads, int D) {
-  if (P > 4) return false;
+  if (P > 4) return D <= 32 && P <= 16 && heads * G <= 512;
   return P * G <= 8 || (P * (D * D + D) * 4 <= 144 * 1024 && heads * G <= 512);
 }
 

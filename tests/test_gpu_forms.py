@@ -223,11 +223,12 @@ def test_backward_forms(layout, d, N):
         assert torch.equal(x[:, H - 1:], y)
 
 
-# up to four partials are added up by the workgroups that need them (one
-# head), or by a pass before where many workgroups would read them: the same
-# bits
-@pytest.mark.parametrize("d,heads", [(16, 1100), (32, 300), (64, 130), (128, 66)])
-@pytest.mark.parametrize("partials", [1, 2, 3, 4])
+# up to four partials (d <= 32: sixteen) are added up by the workgroups that
+# need them (one head), or by a pass before where many workgroups would read
+# them: the same bits
+@pytest.mark.parametrize("d,heads,partials", [
+    (d, h, p) for d, h in ((16, 1100), (32, 300), (64, 130), (128, 66)) for p in (1, 2, 3, 4)] + [
+    (d, 300, p) for d in (16, 32) for p in (5, 7, 12, 16)])
 def test_partials_added_up_by_their_readers(partials, d, heads):
     dev = require_gpu()
     N = 4 * d * partials
