@@ -412,9 +412,10 @@ void bwd_qds_kernel(const void* __restrict__ q, const void* __restrict__ dout, i
   auto at = [](int r, int c) { return (r * RC + (c ^ (2 * ((r >> (D == 64 ? 1 : 2)) & (RC / 2 - 1))))) * 16; };
 
   typedef uint32_t Regs[TT][2][RW];  // Q run, G run of the step's tiles
-  // Rows past the head's end read its last token again (finite values, no
-  // branch around the loads); the step gives such tokens a zero scale, so
-  // they add nothing to dS or dz and their dQ rows are not stored.
+  // Rows past the head's end read its last token again (no branch around
+  // the loads).  The step takes their G as zeros (the token read again may
+  // hold infinities, and 0 x inf is NaN) and gives them a zero scale and
+  // G . O, so they add nothing to dS or dz; their dQ rows are not stored.
   auto load = [&](int k, Regs& x) {
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) {
@@ -457,6 +458,8 @@ void bwd_qds_kernel(const void* __restrict__ q, const void* __restrict__ dout, i
     for (int tt = 0; tt < TT; ++tt) {
       phi_words<DT_BF16, D>(x[tt][0], pq[tt]);
       raw_words<DT_BF16, D>(x[tt][1], pg[tt]);
+#pragma unroll
+      for (int w = 0; w < RW; ++w) pg[tt][w] = t0 + 16 * tt + n < N ? pg[tt][w] : 0;
       // chunk w of the lane's run is the row's 16-byte chunk 4w + g
 #pragma unroll
       for (int w = 0; w < NCH; ++w)
@@ -489,7 +492,7 @@ void bwd_qds_kernel(const void* __restrict__ q, const void* __restrict__ dout, i
       const double rden = 1.0 / (double)dacc[tt][0][0];
       const bool ok = t0 + 16 * tt + n < N;
       const float rd = ok ? (float)rden : 0.f;  // zero past the end: no dS, dz share
-      const float go = gn * rd;                 // G . O
+      const float go = ok ? gn * rd : 0.f;      // G . O
       const float dd = -go * rd;
       // dQ chunk by chunk (few live registers): run positions [CH*w, +CH);
       // phi(q)/den rows into LDS
@@ -647,9 +650,11 @@ void bwd_qds4_kernel(const void* __restrict__ q, const void* __restrict__ dout, 
   const uint32_t ooff = (uint32_t)n * (uint32_t)orow_bytes + (uint32_t)(g * OCB);
 
   typedef uint32_t Regs[2][RW];  // Q run, G run of this wave's tile
-  // Rows past the head's end read its last token again (finite values, no
-  // zero fill); the step gives such tokens a zero scale, so they add
-  // nothing to dS or dz and their dQ rows are not stored.
+  // Rows past the head's end read its last token again; the step gives
+  // such tokens a zero scale and G . O and clears their rows of G in LDS (as
+  // bwd_qds_kernel's; a branch there, because selecting the words took
+  // registers the step does not have: 2.50 ms, 2.52), and their dQ rows are
+  // not stored.
   auto load = [&](int k, Regs& x) {
     const int64_t tb = min(block_token(k) + 16 * wave, N - 1);  // wave-uniform
     const int last = (int)min((int64_t)15, N - 1 - tb);
@@ -728,7 +733,7 @@ void bwd_qds4_kernel(const void* __restrict__ q, const void* __restrict__ dout, 
 #pragma unroll
       for (int r = 0; r < 4; ++r) gn += run_val<DT_BF16>(pq, 4 * i + r) * acc[i][r];
     gn = sum_groups(gn);
-    const float go = gn * rd;
+    const float go = ok ? gn * rd : 0.f;
     // dz = sum_i dden_i phi(q_i) = sum_i (phi(q_i)/den_i)(-G_i . O_i): one
     // more column block of the dS product, whose B operand holds -G.O of
     // each token as a bf16 pair hi + lo in columns 0 and 1 (made
@@ -773,6 +778,11 @@ void bwd_qds4_kernel(const void* __restrict__ q, const void* __restrict__ dout, 
         wa[kk] = pack_bf16(bf16lo(x) * rd, bf16hi(x) * rd);
       }
       rowq[wave][tile_slot(n, 4 * w + g)] = u32x4{wa[0], wa[1], wa[2], wa[3]};
+    }
+    if (tb + 16 > N) {  // wave-uniform
+      if (!ok)  // (0 x inf is NaN)
+#pragma unroll
+        for (int w = 0; w < NCH; ++w) rowg[wave][tile_slot(n, 4 * w + g)] = u32x4{0, 0, 0, 0};
     }
     __syncthreads();
     // the wave's dS patch (and dz columns) over the step's tiles: tiles
