@@ -423,9 +423,9 @@ __global__ __launch_bounds__(64 * SplitCfg<D>::NW) __attribute__((amdgpu_waves_p
       float a[QI], b[QJ];
 #pragma unroll
       for (int i = 0; i < QI; ++i) {
-        const float x = *(const float*)(kh + at + 64 * (i0 + i));
-        a[i] = ok ? phi<DT_FP32>(x) : 0.f;
-        if constexpr (MODE == MODE_BWD) a[i] *= tstash[min(t, t_end - 1)].x;
+        float x = phi<DT_FP32>(*(const float*)(kh + at + 64 * (i0 + i)));
+        if constexpr (MODE == MODE_BWD) x *= tstash[min(t, t_end - 1)].x;
+        a[i] = ok ? x : 0.f;  // (masked last: 1/den may be infinite)
       }
 #pragma unroll
       for (int j = 0; j < QJ; ++j) {
