@@ -332,7 +332,7 @@ __global__ __launch_bounds__(64 * SplitCfg<D>::NW) __attribute__((amdgpu_waves_p
   float z[4] = {0.f, 0.f, 0.f, 0.f};
   // phi, split, LDS
   auto stage = [&](int64_t t0, Regs& x, int step) {
-    SplitRange kr, vr;
+    SplitRange<4> kr, vr;  // by feature: a row and a column of S each
     if (t0 + TPS > t_end) {  // uniform: rows past the end add nothing
 #pragma unroll
       for (int i = 0; i < NP; ++i)
@@ -358,10 +358,11 @@ __global__ __launch_bounds__(64 * SplitCfg<D>::NW) __attribute__((amdgpu_waves_p
         if constexpr (MODE == MODE_BWD) z[c] = fmaf(x.st[i].y, a[c], z[c]);
         else z[c] += a[c];
       }
-      kr.see(a[0], a[1]);
-      kr.see(a[2], a[3]);
-      vr.see(b[0], b[1]);
-      vr.see(b[2], b[3]);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        kr.see(c, a[c]);
+        vr.see(c, b[c]);
+      }
       const int at = row * (2 * D) + (((c4 >> 1) ^ swz(row)) * 16) + (c4 & 1) * 8;
       const Split2 a0 = split2(a[0], a[1]), a1 = split2(a[2], a[3]);
       const Split2 b0 = split2(b[0], b[1]), b1 = split2(b[2], b[3]);

@@ -65,23 +65,35 @@ __device__ __forceinline__ Split2 split2(double a, double b) {
 }
 
 // Stage M [D][D] and v [D]; barriers are the caller's (one before, so that
-// out_of_range is cleared, is here).
-template <int D>
+// out_of_range is cleared, is here).  COLS, ROWS: whether M's columns, its
+// rows are results of the kernel's products, whose ranges count one by one
+// (a thread meets 2 (d = 128: 4) elements of each of its columns and eight of
+// a row at a time); VEC: whether v is an operand too.
+template <int D, bool COLS, bool ROWS, bool VEC>
 __device__ __forceinline__ void stage_matrix(MatLds<D>& L, const double* __restrict__ M,
                                              const double* __restrict__ v) {
   using C = Rows32<D>;
   if (threadIdx.x == 0) L.out_of_range = 0;
   __syncthreads();
-  SplitRange r;
+  const double vx = threadIdx.x < D ? v[threadIdx.x] : 0.0;  // in flight with the matrix's loads
+  SplitRange<8> cols;
+  bool bad = false;
+  static_assert(C::NTH % (D / 8) == 0, "a thread's elements lie in the same columns");
   for (int u = threadIdx.x; u < D * D / 8; u += C::NTH) {
     const int row = u / (D / 8), ch = u % (D / 8);
+    SplitRange<> r;
     double x[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) x[j] = M[row * D + 8 * ch + j];
     u32x4 h, m, l;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      r.see((float)x[2 * j], (float)x[2 * j + 1]);
+      const float a = (float)x[2 * j], b = (float)x[2 * j + 1];
+      if (ROWS) r.see(0, a, b);
+      if (COLS) {
+        cols.see(2 * j, a);
+        cols.see(2 * j + 1, b);
+      }
       const Split2 s = split2(x[2 * j], x[2 * j + 1]);
       h[j] = s.h;
       m[j] = s.m;
@@ -91,17 +103,19 @@ __device__ __forceinline__ void stage_matrix(MatLds<D>& L, const double* __restr
     *(u32x4*)at = h;
     *(u32x4*)(at + C::PART) = m;
     *(u32x4*)(at + 2 * C::PART) = l;
+    bad |= r.bad();
   }
+  bad |= cols.bad();
   if (threadIdx.x < D) {
-    const double x = v[threadIdx.x];
-    r.see((float)x, 0.f);
-    const Split2 s = split2(x, 0.0);
+    const float mag = fabsf((float)vx);  // the vector's elements are summed: judged 64 at a time
+    if (VEC) bad |= !(mag < 0x1p63f) || (mag > 0.f && !__any(mag >= 0x1p-90f));
+    const Split2 s = split2(vx, 0.0);
     L.v[0][threadIdx.x] = (uint16_t)s.h;
     L.v[1][threadIdx.x] = (uint16_t)s.m;
     L.v[2][threadIdx.x] = (uint16_t)s.l;
-    L.vd[threadIdx.x] = x;
+    L.vd[threadIdx.x] = vx;
   }
-  if (r.bad()) L.out_of_range = 1;  // every writer stores the same
+  if (bad) L.out_of_range = 1;  // every writer stores the same
 }
 
 __device__ __forceinline__ bf16x8 join(const u32x2& lo, const u32x2& hi) {
@@ -279,7 +293,7 @@ __global__ __launch_bounds__(Rows32<D>::NTH) __attribute__((amdgpu_waves_per_eu(
     rl = (float)(rden - (double)rh);
   };
   if (sw.nk > 0) load(0);
-  stage_matrix(L, M, v);
+  stage_matrix<D, true, false, true>(L, M, v);
   __syncthreads();
   const bool all_bad = __builtin_amdgcn_readfirstlane(L.out_of_range);  // uniform over the workgroup
   const int cbase = column_base<D>(g, n);
@@ -287,7 +301,7 @@ __global__ __launch_bounds__(Rows32<D>::NTH) __attribute__((amdgpu_waves_per_eu(
   Bf16x3 p[TT][NS];
   // phi of the loaded rows as operands; whether all lie in the range
   auto convert = [&]() {
-    SplitRange range;
+    SplitRange<TT> range;
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt)
 #pragma unroll
@@ -296,7 +310,7 @@ __global__ __launch_bounds__(Rows32<D>::NTH) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
         for (int j = 0; j < 8; ++j) x[j] = phi<DT_FP32>(__uint_as_float(raw[tt][8 * s + j]));
 #pragma unroll
-        for (int j = 0; j < 8; j += 2) range.see(x[j], x[j + 1]);
+        for (int j = 0; j < 8; j += 2) range.see(tt, x[j], x[j + 1]);
         p[tt][s] = split_run(x);
       }
     return !all_bad && !__any(range.bad());
@@ -416,7 +430,7 @@ __global__ __launch_bounds__(Rows32<D>::NTH) __attribute__((amdgpu_waves_per_eu(
   float ph[Q4];  // phi(q)
   Bf16x3 bg[NS];
   auto convert = [&](bool all_bad) {
-    SplitRange rp, rx;
+    SplitRange<> rp, rx;
 #pragma unroll
     for (int c = 0; c < Q4; ++c) ph[c] = phi<DT_FP32>(__uint_as_float(rq[c]));
 #pragma unroll
@@ -426,8 +440,8 @@ __global__ __launch_bounds__(Rows32<D>::NTH) __attribute__((amdgpu_waves_per_eu(
       for (int j = 0; j < 8; ++j) x[j] = __uint_as_float(rg[8 * s + j]);
 #pragma unroll
       for (int j = 0; j < 8; j += 2) {
-        rx.see(x[j], x[j + 1]);
-        rp.see(ph[8 * s + j], ph[8 * s + j + 1]);
+        rx.see(0, x[j], x[j + 1]);
+        rp.see(0, ph[8 * s + j], ph[8 * s + j + 1]);
       }
       bg[s] = split_run(x);
     }
@@ -453,7 +467,7 @@ __global__ __launch_bounds__(Rows32<D>::NTH) __attribute__((amdgpu_waves_per_eu(
     if (g == 0) stash[(int64_t)bh * N + t] = float2{(float)rden, (float)(-go)};
   };
   if (sw.nk > 0) load(0);
-  stage_matrix(L, M, v);
+  stage_matrix<D, false, true, true>(L, M, v);
   __syncthreads();
   const bool all_bad = __builtin_amdgcn_readfirstlane(L.out_of_range);
   const int rbase = row_base<D>(g, n);
@@ -533,7 +547,7 @@ __global__ __launch_bounds__(Rows32<D>::NTH) __attribute__((amdgpu_waves_per_eu(
   float ph[Q4];  // phi(k)
   Bf16x3 bk[NS], bv[NS];
   auto convert = [&](bool all_bad) {
-    SplitRange rp, rx;
+    SplitRange<> rp, rx;
 #pragma unroll
     for (int c = 0; c < Q4; ++c) ph[c] = phi<DT_FP32>(__uint_as_float(rk[c]));
 #pragma unroll
@@ -543,8 +557,8 @@ __global__ __launch_bounds__(Rows32<D>::NTH) __attribute__((amdgpu_waves_per_eu(
       for (int j = 0; j < 8; ++j) x[j] = __uint_as_float(rv[8 * s + j]);
 #pragma unroll
       for (int j = 0; j < 8; j += 2) {
-        rx.see(x[j], x[j + 1]);
-        rp.see(ph[8 * s + j], ph[8 * s + j + 1]);
+        rx.see(0, x[j], x[j + 1]);
+        rp.see(0, ph[8 * s + j], ph[8 * s + j + 1]);
       }
       bv[s] = split_run(x);
       bk[s] = split_run(ph + 8 * s);
@@ -563,7 +577,7 @@ __global__ __launch_bounds__(Rows32<D>::NTH) __attribute__((amdgpu_waves_per_eu(
     store4<OT>(okh + at, ok);
   };
   if (sw.nk > 0) load(0);
-  stage_matrix(L, M, dz64 + (int64_t)bh * D);
+  stage_matrix<D, true, true, false>(L, M, dz64 + (int64_t)bh * D);
   __syncthreads();
   const bool all_bad = __builtin_amdgcn_readfirstlane(L.out_of_range);
   const int cbase = column_base<D>(g, n), rbase = row_base<D>(g, n);

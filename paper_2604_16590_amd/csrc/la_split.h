@@ -18,9 +18,11 @@
 //
 // The split is exact for |x| in [2^-100, 2^127): below, l (and m) leave the
 // bf16 range, above, h rounds to infinity, and an infinity's rest is NaN.
-// Kernels test each operand run (`SplitRange`) and take the fp32 matrix
-// instructions for a step whose operands leave the range, so infinities and
-// extreme scales give what they gave there.
+// Two values within it may still have a product h h = inf beside h m = -inf,
+// so operands are held below 2^63: then no product and no sum of small
+// products overflows.  Kernels test their operands (`SplitRange`) and take
+// the fp32 matrix instructions for a step whose operands leave the range, so
+// infinities and extreme scales give what they gave there.
 #pragma once
 #include "la_device.h"
 
@@ -39,17 +41,31 @@ __device__ __forceinline__ Split2 split2(float a, float b) {
   return s;
 }
 
-// Largest magnitude of the values seen by a lane; `bad` when some value is
-// too large for the split or all of them (not all zero) are too small for
-// it.  A small value beside a larger one of its lane is split to less than
-// 2^-27 of the larger.  NaN passes: its parts are NaN.
+// Largest magnitudes of the values a lane has seen, in C classes; `bad` when
+// some value is too large, or all of a class (not all zero) are too small for
+// the split.  A small value beside a larger one of its class is split to less
+// than 2^-27 of the larger, so a class holds only values that are summed into
+// the same results: a column of a contraction's operand (its rows are what is
+// summed over), or one token's run.  NaN passes: its parts are NaN.
+template <int C = 1>
 struct SplitRange {
-  float mx = 0.f;
-  __device__ __forceinline__ void see(float a, float b) {
-    mx = fmaxf(fmaxf(mx, fabsf(a)), fabsf(b));
+  float mx[C] = {};
+  __device__ __forceinline__ void see(int c, float a) { mx[c] = fmaxf(mx[c], fabsf(a)); }
+  __device__ __forceinline__ void see(int c, float a, float b) {
+    mx[c] = fmaxf(fmaxf(mx[c], fabsf(a)), fabsf(b));
   }
   __device__ __forceinline__ bool bad() const {
-    return !(mx < 0x1p127f) || (mx > 0.f && mx < 0x1p-90f);
+    float hi = mx[0], lo = mx[0];
+#pragma unroll
+    for (int c = 1; c < C; ++c) {
+      hi = fmaxf(hi, mx[c]);
+      lo = fminf(lo, mx[c]);
+    }
+    bool b = !(hi < 0x1p63f);
+    if (lo < 0x1p-90f)  // a class of zeros, or a bad one
+#pragma unroll
+      for (int c = 0; c < C; ++c) b |= mx[c] > 0.f && mx[c] < 0x1p-90f;
+    return b;
   }
 };
 
