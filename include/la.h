@@ -31,7 +31,8 @@
  *    mutable global state; calls may come from several host threads.
  *  - Results are bitwise reproducible: tile sizes and the number of
  *    partial sums depend only on (N, d, dtype), and every cross-tile sum
- *    runs in a fixed order (no floating-point atomics).
+ *    runs in a fixed order (no floating-point atomics).  (A workspace too
+ *    small for one head's partials takes fewer; see la_workspace_size.)
  */
 #ifndef LA_H
 #define LA_H
@@ -113,7 +114,10 @@ la_status la_version(int32_t* major, int32_t* minor);
  * (1/den, dden) passed between them; bf16 at d >= 32 runs them as one pass
  * and needs no such buffer.  With a somewhat smaller workspace, down to one
  * partial for 2,048 (d = 128) or 512 tokens, a pass runs in parts of its
- * heads, with the same results; below, LA_ERR_OOM.
+ * heads, with the same results; where not even one head's workspace fits, in
+ * one part with those fewer partials, whose sums over tokens round
+ * differently (no FP32 sum covers more than the bound above); below,
+ * LA_ERR_OOM.
  */
 la_status la_workspace_size(const la_attn_desc* desc, int32_t pass, size_t* bytes);
 

@@ -113,8 +113,16 @@ int64_t summary_partials(int64_t N, int d, int dt) {
 
 bool fused_backward(int d, int dt) { return dt == LA_BF16 && d >= 32; }
 
-Tiling choose_tiling(int64_t N, int d, int dt, bool backward) {
-  int64_t P = backward && fused_backward(d, dt) ? fused_partials(N, d) : summary_partials(N, d, dt);
+// The fewest partials a pass takes: one for 2,048 (d = 128) or 512 tokens,
+// for workspaces without room for one head's finer ones.
+int64_t coarse_partials(int64_t N, int d) {
+  return std::min(max_partials(d), ceil_div(N, d >= 128 ? 2048 : 512));
+}
+
+Tiling choose_tiling(int64_t N, int d, int dt, bool backward, bool coarse) {
+  int64_t P = coarse                                 ? coarse_partials(N, d)
+              : backward && fused_backward(d, dt) ? fused_partials(N, d)
+                                                  : summary_partials(N, d, dt);
   P = std::max<int64_t>(P, ceil_div(N, max_fp32_run(dt)));
   // a multiple of 64: the summary steps over 32 tokens, the fused
   // backward over 64 (four waves x 16); max_fp32_run is one too, so
@@ -131,7 +139,7 @@ Tiling choose_tiling(int64_t N, int d, int dt, bool backward) {
 // 512 (d = 128: 2048) tokens each would make, which keeps the size the
 // same from 64 (128) of them up to max_fp32_run tokens each.
 int64_t partial_room(int64_t N, int d, int P) {
-  return std::max<int64_t>(P, std::min(max_partials(d), ceil_div(N, d >= 128 ? 2048 : 512)));
+  return std::max<int64_t>(P, coarse_partials(N, d));
 }
 
 // Apply workgroups per head: at most one per token block.  Per-token work, so
@@ -179,11 +187,11 @@ struct Layout {
 // per query token (1/den, -(dO . O)) between the query kernel and the dS
 // reduction, the only part of any workspace that grows with N.  bf16 at
 // d >= 32 fuses the two passes and needs no stash.
-Layout layout_for(const la_attn_desc* d, int pass) {
+Layout layout_for(const la_attn_desc* d, int pass, bool coarse = false) {
   const int64_t BH = d->B * d->H, D = d->d;
-  const Tiling t = choose_tiling(d->N, (int)D, d->in_dtype, pass == 1);
-  const size_t part =
-      align_up((size_t)BH * partial_room(d->N, (int)D, t.P) * (D * D + D) * sizeof(float));
+  const Tiling t = choose_tiling(d->N, (int)D, d->in_dtype, pass == 1, coarse);
+  const int64_t room = coarse ? t.P : partial_room(d->N, (int)D, t.P);
+  const size_t part = align_up((size_t)BH * room * (D * D + D) * sizeof(float));
   const size_t mat = align_up((size_t)BH * D * D * sizeof(double));
   const size_t vec = align_up((size_t)BH * D * sizeof(double));
   const size_t img = align_up((size_t)BH * head_image_bytes((int)D, d->in_dtype));
@@ -211,15 +219,14 @@ Layout layout_for(const la_attn_desc* d, int pass) {
 }  // namespace
 
 // The workspace that a pass has always taken: two operand images of S (and dS)
-// and a partial for 2,048 (d = 128) or 512 tokens.  Short sequences are cut
-// finer now, up to 3.3 times this (fp32, d = 128); with less than they want,
-// but this much, a problem runs in parts of its heads.
+// and the coarse partials.  Short sequences are cut finer now, up to 3.3
+// times this (fp32, d = 128); with less than they want, but this much, a
+// problem runs in parts of its heads, and where not even one head's finer
+// partials fit, with the coarse ones.
 namespace la {
 size_t least_workspace(const la_attn_desc* d, int pass) {
   const int64_t BH = d->B * d->H, D = d->d;
-  int64_t P = std::max(std::min(max_partials((int)D), ceil_div(d->N, D >= 128 ? 2048 : 512)),
-                       ceil_div(d->N, max_fp32_run(d->in_dtype)));
-  P = ceil_div(d->N, ceil_div(ceil_div(d->N, P), 64) * 64);
+  const int64_t P = choose_tiling(d->N, (int)D, d->in_dtype, pass == 1, true).P;
   const size_t part = align_up((size_t)BH * P * (D * D + D) * sizeof(float));
   const size_t sums = align_up((size_t)BH * D * D * sizeof(double)) + align_up((size_t)BH * D * sizeof(double));
   const size_t img = align_up((size_t)BH * head_image_bytes((int)D, d->in_dtype));
@@ -253,19 +260,22 @@ Part part_for(const la_attn_desc* d, int pass, size_t ws_bytes) {
   return {1, most(p.H)};
 }
 
-// Calls f(part's descriptor, its first b, its first h) for parts of the
+// Calls f(part's descriptor, its first b, its first h, coarse) for parts of the
 // problem that fit ws_bytes, one after the other.  A head's result does not
-// depend on the others in a call, so the bits are those of one call.
+// depend on the others in a call, so the bits are those of one call.  With
+// less than one head's layout, one call in coarse partials, which fit the
+// least workspace: its sums over tokens round differently.
 template <class F>
 la_status in_parts(const la_attn_desc* desc, int pass, size_t ws_bytes, F&& f) {
+  if (ws_bytes < la::least_workspace(desc, pass)) return LA_ERR_OOM;
   const Part most = part_for(desc, pass, ws_bytes);
-  if (ws_bytes < la::least_workspace(desc, pass) || !most.H) return LA_ERR_OOM;
+  if (!most.H) return f(desc, 0, 0, true);
   for (int64_t b = 0; b < desc->B; b += most.B)
     for (int64_t h = 0; h < desc->H; h += most.H) {
       la_attn_desc p = *desc;
       p.B = std::min(most.B, desc->B - b);
       p.H = std::min(most.H, desc->H - h);
-      const la_status st = f(&p, b, h);
+      const la_status st = f(&p, b, h, false);
       if (st != LA_OK) return st;
     }
   return LA_OK;
@@ -317,24 +327,24 @@ la_status check_gate(const void* other, const double* sigma, double sigma_data) 
 la_status forward_impl(const la_attn_desc* desc, const void* q, const void* k, const void* v,
                        void* o, double* s_out, double* z_out, void* ws, size_t ws_bytes,
                        la_stream stream, const void* other, const double* sigma,
-                       double sigma_data) {
+                       double sigma_data, bool coarse = false) {
   la_status st = check_desc(desc);
   if (st != LA_OK) return st;
   if (!q || !k || !v || !o || !ws) return LA_ERR_INVALID_ARG;
   if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(o)) return LA_ERR_INVALID_ARG;
   if (((uintptr_t)ws % kAlign) != 0) return LA_ERR_INVALID_ARG;
   if (((uintptr_t)s_out & 7u) || ((uintptr_t)z_out & 7u)) return LA_ERR_INVALID_ARG;
-  const Layout L = layout_for(desc, 0);
+  const Layout L = layout_for(desc, 0, coarse);
   if (ws_bytes < L.total)
-    return in_parts(desc, 0, ws_bytes, [&](const la_attn_desc* p, int64_t b, int64_t h) {
+    return in_parts(desc, 0, ws_bytes, [&](const la_attn_desc* p, int64_t b, int64_t h, bool c) {
       const int64_t i = in_offset(desc, b, h), j = out_offset(desc, b, h);
       const int64_t bh = b * desc->H + h, d = desc->d;
       return forward_impl(p, (const char*)q + i, (const char*)k + i, (const char*)v + i, (char*)o + j,
                           s_out ? s_out + bh * d * d : nullptr, z_out ? z_out + bh * d : nullptr, ws,
                           ws_bytes, stream, other ? (const char*)other + j : nullptr,
-                          sigma ? sigma + b : nullptr, sigma_data);
+                          sigma ? sigma + b : nullptr, sigma_data, c);
     });
-  const Tiling t = choose_tiling(desc->N, (int)desc->d, desc->in_dtype, false);
+  const Tiling t = choose_tiling(desc->N, (int)desc->d, desc->in_dtype, false, coarse);
   char* w = (char*)ws;
   la::FwdArgs a{};
   a.B = desc->B; a.H = desc->H; a.N = desc->N; a.D = (int)desc->d;
@@ -381,6 +391,48 @@ la_status apply_impl(const la_attn_desc* desc, const void* q, const double* s, c
   a.other = other; a.sigma = sigma; a.sigma_data = sigma_data;
   a.stream = (hipStream_t)stream;
   hipError_t e = la::launch_apply(a);
+  if (e != hipSuccess) return hip_fail(e);
+  return LA_OK;
+}
+
+la_status backward_impl(const la_attn_desc* desc, const void* q, const void* k, const void* v,
+                        const double* s, const double* z, const void* dout, void* dq, void* dk,
+                        void* dv, void* ws, size_t ws_bytes, la_stream stream, bool coarse = false) {
+  la_status st = check_desc(desc);
+  if (st != LA_OK) return st;
+  if (!q || !k || !v || !s || !z || !dout || !dq || !dk || !dv || !ws) return LA_ERR_INVALID_ARG;
+  for (const void* p : {q, k, v, dout, (const void*)dq, (const void*)dk, (const void*)dv})
+    if (!aligned16(p)) return LA_ERR_INVALID_ARG;
+  if (((uintptr_t)s & 7u) || ((uintptr_t)z & 7u)) return LA_ERR_INVALID_ARG;
+  if (((uintptr_t)ws % kAlign) != 0) return LA_ERR_INVALID_ARG;
+  const Layout L = layout_for(desc, 1, coarse);
+  if (ws_bytes < L.total)
+    return in_parts(desc, 1, ws_bytes, [&](const la_attn_desc* p, int64_t b, int64_t h, bool c) {
+      const int64_t i = in_offset(desc, b, h), j = out_offset(desc, b, h);
+      const int64_t bh = b * desc->H + h, d = desc->d;
+      return backward_impl(p, (const char*)q + i, (const char*)k + i, (const char*)v + i, s + bh * d * d,
+                           z + bh * d, (const char*)dout + i, (char*)dq + j, (char*)dk + j, (char*)dv + j,
+                           ws, ws_bytes, stream, c);
+    });
+  const Tiling t = choose_tiling(desc->N, (int)desc->d, desc->in_dtype, true, coarse);
+  char* w = (char*)ws;
+  la::BwdArgs a{};
+  a.B = desc->B; a.H = desc->H; a.N = desc->N; a.D = (int)desc->d;
+  a.in_dt = desc->in_dtype; a.out_dt = desc->out_dtype;
+  a.sb = desc->in_sb; a.sh = desc->in_sh; a.sn = desc->in_sn;
+  a.osb = desc->out_sb; a.osh = desc->out_sh; a.osn = desc->out_sn;
+  a.q = q; a.k = k; a.v = v; a.dout = dout;
+  a.dq = dq; a.dk = dk; a.dv = dv;
+  a.S64 = s; a.z64 = z;
+  a.P = t.P; a.Tw = t.Tw; a.Ta = query_tokens(desc->N, desc->B * desc->H, desc->in_dtype);
+  a.Gk = key_groups(desc->N, desc->B * desc->H, (int)desc->d, desc->in_dtype);
+  a.part = (float*)(w + L.part);
+  a.stash = (float2*)(w + L.stash);
+  a.dS64 = (double*)(w + L.dS64);
+  a.dz64 = (double*)(w + L.dz64);
+  a.dimg = w + L.dimg;
+  a.stream = (hipStream_t)stream;
+  hipError_t e = la::launch_backward(a);
   if (e != hipSuccess) return hip_fail(e);
   return LA_OK;
 }
@@ -462,43 +514,7 @@ la_status la_backward(const la_attn_desc* desc, const void* q, const void* k,
                       const void* v, const double* s, const double* z,
                       const void* dout, void* dq, void* dk, void* dv, void* ws,
                       size_t ws_bytes, la_stream stream) {
-  la_status st = check_desc(desc);
-  if (st != LA_OK) return st;
-  if (!q || !k || !v || !s || !z || !dout || !dq || !dk || !dv || !ws) return LA_ERR_INVALID_ARG;
-  for (const void* p : {q, k, v, dout, (const void*)dq, (const void*)dk, (const void*)dv})
-    if (!aligned16(p)) return LA_ERR_INVALID_ARG;
-  if (((uintptr_t)s & 7u) || ((uintptr_t)z & 7u)) return LA_ERR_INVALID_ARG;
-  if (((uintptr_t)ws % kAlign) != 0) return LA_ERR_INVALID_ARG;
-  const Layout L = layout_for(desc, 1);
-  if (ws_bytes < L.total)
-    return in_parts(desc, 1, ws_bytes, [&](const la_attn_desc* p, int64_t b, int64_t h) {
-      const int64_t i = in_offset(desc, b, h), j = out_offset(desc, b, h);
-      const int64_t bh = b * desc->H + h, d = desc->d;
-      return la_backward(p, (const char*)q + i, (const char*)k + i, (const char*)v + i, s + bh * d * d,
-                         z + bh * d, (const char*)dout + i, (char*)dq + j, (char*)dk + j, (char*)dv + j,
-                         ws, ws_bytes, stream);
-    });
-  const Tiling t = choose_tiling(desc->N, (int)desc->d, desc->in_dtype, true);
-  char* w = (char*)ws;
-  la::BwdArgs a{};
-  a.B = desc->B; a.H = desc->H; a.N = desc->N; a.D = (int)desc->d;
-  a.in_dt = desc->in_dtype; a.out_dt = desc->out_dtype;
-  a.sb = desc->in_sb; a.sh = desc->in_sh; a.sn = desc->in_sn;
-  a.osb = desc->out_sb; a.osh = desc->out_sh; a.osn = desc->out_sn;
-  a.q = q; a.k = k; a.v = v; a.dout = dout;
-  a.dq = dq; a.dk = dk; a.dv = dv;
-  a.S64 = s; a.z64 = z;
-  a.P = t.P; a.Tw = t.Tw; a.Ta = query_tokens(desc->N, desc->B * desc->H, desc->in_dtype);
-  a.Gk = key_groups(desc->N, desc->B * desc->H, (int)desc->d, desc->in_dtype);
-  a.part = (float*)(w + L.part);
-  a.stash = (float2*)(w + L.stash);
-  a.dS64 = (double*)(w + L.dS64);
-  a.dz64 = (double*)(w + L.dz64);
-  a.dimg = w + L.dimg;
-  a.stream = (hipStream_t)stream;
-  hipError_t e = la::launch_backward(a);
-  if (e != hipSuccess) return hip_fail(e);
-  return LA_OK;
+  return backward_impl(desc, q, k, v, s, z, dout, dq, dk, dv, ws, ws_bytes, stream);
 }
 
 }  // extern "C"
