@@ -313,7 +313,9 @@ la_status la_tiled_forward(const la_tile_desc* desc, int64_t heads, const void* 
  *    releases the request.
  * Member results do not depend on how a request is sliced or what else
  * runs: tiling depends only on (N, d, dtype), so a request computes the
- * same bits alone and in a mix.
+ * same bits alone and in a mix. A member whose workspace of
+ * la_workspace_size does not fit runs in parts of its heads, down to the
+ * least workspace of la_workspace_size's comment.
  * ------------------------------------------------------------------------ */
 typedef struct la_server la_server;
 

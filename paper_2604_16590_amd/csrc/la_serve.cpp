@@ -38,6 +38,10 @@
 #include "../../include/la.h"
 #include "../../include/la_gen.h"
 
+namespace la {
+size_t least_workspace(const la_attn_desc* d, int pass);  // la_api.cpp
+}
+
 namespace {
 
 constexpr size_t kAlign = 256;
@@ -109,6 +113,7 @@ struct Slice {
   int index;
   int64_t b0, m;       // members [b0, b0 + m)
   size_t off, bytes;   // transient block: generated inputs + workspace
+  size_t ws;           // the workspace's part of it
   int stream;
   hipEvent_t start, gen, done;  // timed events: slice start, inputs ready, done
   uint64_t t_fake_done;
@@ -167,24 +172,42 @@ struct la_server {
 
 namespace {
 
-// Transient bytes of a slice of m members: generated inputs (Q, K, V; Q
+// The transient block of a slice of m members: generated inputs (Q, K, V; Q
 // only when reusing a summary) plus the workspace of the forward (apply).
-// Kept bytes of a request: S, z (not when reusing) and a generated O.
-size_t slice_bytes(const la_request& r, int64_t m) {
+struct Block {
+  size_t inputs, ws;
+  size_t bytes() const { return inputs + align_up(ws); }
+};
+
+Block slice_block(const la_request& r, int64_t m) {
   la_attn_desc d = r.desc;
   d.B = m;
-  if (r.generate) {
-    d.in_sh = d.N * d.d; d.in_sb = d.H * d.in_sh; d.in_sn = d.d;
-    d.out_sh = d.N * d.d; d.out_sb = d.H * d.out_sh; d.out_sn = d.d;
-  }
-  size_t ws = 0;
-  la_workspace_size(&d, reuses(r) ? 2 : 0, &ws);
-  size_t b = align_up(ws);
+  Block b{};
+  la_workspace_size(&d, reuses(r) ? 2 : 0, &b.ws);
   const size_t n_gen = reuses(r) ? 1 : 3;
-  if (r.generate) b += n_gen * align_up(member_tensor_bytes(d, d.in_dtype) * (size_t)m);
+  if (r.generate) b.inputs = n_gen * align_up(member_tensor_bytes(d, d.in_dtype) * (size_t)m);
   return b;
 }
 
+size_t keep_bytes(const la_request& r);
+
+// The least block a one-member slice runs in: with the workspace of one head
+// (the others follow in it, with the same results), or, where the budget
+// could not hold that either, the least one that the pass accepts.
+Block lean_block(const la_request& r, size_t budget) {
+  Block b = slice_block(r, 1);
+  la_attn_desc d = r.desc;
+  d.B = 1;
+  const int pass = reuses(r) ? 2 : 0;
+  const size_t full = b.ws, least = la::least_workspace(&d, pass);
+  d.H = 1;
+  la_workspace_size(&d, pass, &b.ws);
+  b.ws = std::min(full, std::max(b.ws, least));
+  if (keep_bytes(r) + b.bytes() > budget) b.ws = std::min(full, least);
+  return b;
+}
+
+// Kept bytes of a request: S, z (not when reusing) and a generated O.
 size_t keep_bytes(const la_request& r) {
   const la_attn_desc& d = r.desc;
   size_t b = 0;
@@ -275,8 +298,7 @@ la_status launch_slice(la_server* s, Request& rq, Slice& sl, bool* enqueued) {
   }
   if (sl.fail_late) return LA_ERR_HIP;  // injected failure after the inputs
   if (hipEventRecord(sl.gen, st) != hipSuccess) return LA_ERR_HIP;
-  size_t ws = 0;
-  la_workspace_size(&d, reuses(r) ? 2 : 0, &ws);
+  const size_t ws = sl.ws;
   double* S = rq.s + (size_t)sl.b0 * d.H * d.d * d.d;
   double* z = rq.z + (size_t)sl.b0 * d.H * d.d;
   const la_status st2 = reuses(r) ? la_apply(&d, q, S, z, o, blk, ws, st)
@@ -395,18 +417,24 @@ int admit(la_server* s) {
     int64_t m = left;
     if (s->cfg.max_members_per_slice > 0) m = std::min<int64_t>(m, s->cfg.max_members_per_slice);
     size_t room = s->arena.largest_free();
+    const Block lean = lean_block(r, s->arena.size());
     if (cap > 0) {
-      const size_t share = std::max<size_t>(s->cfg.hbm_budget_bytes / s->cfg.max_slots, slice_bytes(r, 1));
-      room = std::min(room, share);
+      size_t one = slice_block(r, 1).bytes();
+      if (keep_bytes(r) + one > s->arena.size()) one = lean.bytes();
+      room = std::min(room, std::max<size_t>(s->cfg.hbm_budget_bytes / s->cfg.max_slots, one));
     }
-    while (m > 0 && slice_bytes(r, m) > room) m = m > 8 ? m * 3 / 4 : m - 1;
-    if (m <= 0) break;
+    while (m > 0 && slice_block(r, m).bytes() > room) m = m > 8 ? m * 3 / 4 : m - 1;
+    Block block = lean;
+    if (m > 0) block = slice_block(r, m);
+    else if (lean.bytes() <= room) m = 1;
+    else break;
     Slice sl{};
     sl.req = id;
     sl.index = rq.slices_started;
     sl.b0 = rq.next_member;
     sl.m = m;
-    sl.bytes = slice_bytes(r, m);
+    sl.bytes = block.bytes();
+    sl.ws = block.ws;
     if (!s->arena.alloc(sl.bytes, &sl.off)) break;
     sl.stream = s->next_stream;
     s->next_stream = (s->next_stream + 1) % std::max(1, (int)s->streams.size());
@@ -573,7 +601,7 @@ la_status la_serve_submit(la_server* s, const la_request* r, uint64_t* id) {
         od.d != d.d || od.in_dtype != d.in_dtype)
       return LA_ERR_INVALID_ARG;
   }
-  if (keep_bytes(req) + slice_bytes(req, 1) > s->arena.size()) {
+  if (keep_bytes(req) + lean_block(req, s->arena.size()).bytes() > s->arena.size()) {
     s->n_rejected += 1;
     return LA_ERR_OOM;
   }

@@ -54,3 +54,26 @@ def test_least_workspace_of_few_heads(H, N, d, dtype):
     assert normwise(z.cpu().numpy()[..., None], z_ref[..., None]) < (4e-3 if dtype == "bf16" else 1e-6)
     for x, r in zip((dq, dk, dv), oracle.backward(*host)):
         assert normwise(as64(x), r) < TOL[dtype]
+
+
+@pytest.mark.parametrize("H", [1, 8])
+def test_served_member_of_the_least_size(H):
+    # a budget with no room for the usual workspace: parts of the heads (the
+    # same bits), or for one head fewer partials
+    import paper_2604_16590_amd as la
+    from paper_2604_16590_amd import serve
+    dev = require_gpu()
+    N, d = 4096, 128
+    host = make_inputs((1, H, N, d), "fp32", seed=H)
+    q, k, v = (to_device(x, dev) for x in host)
+    o = torch.full_like(q, float("nan"))
+    desc = BB.make_desc(q, o)
+    keep = up(H * d * d * 8) + up(H * d * 8)
+    least = up(H * 2 * (d * d + d) * 4) + keep + BB.workspace_size(desc, 2)
+    assert least < BB.workspace_size(desc, 0)
+    torch.cuda.synchronize()
+    with serve.Server(keep + least, max_slots=1, n_streams=1) as srv:
+        assert srv.wait(srv.submit(desc, q, k, v, o)).state == serve.DONE
+    if H > 1:
+        assert torch.equal(o, la.forward(q, k, v))
+    assert normwise(as64(o), oracle.forward(*host)) < TOL["fp32"]
