@@ -151,11 +151,20 @@ int apply_groups(int64_t N, int64_t BH, int d) {
     // 270 tokens, and two share a compute unit: one round of 512 workgroups
     // (4 x 16 heads of 4,096: 44 us, 81 with 2,048; 16 of 43,237: 92, 126),
     // more where each still has 8,192 tokens (8 heads of 2,097,152 as views of
-    // [B, N, H, d]: 1.72 ms, 1.95 in one round); beyond 128 heads up to 2,048
-    // of at least 2,048 tokens, so that the last round is not half empty.
-    const int64_t ga = BH <= 128 ? std::max(512 / BH, std::min(ceil_div(4096, BH), N / 8192))
-                                 : std::min(ceil_div(2048, BH), N / 2048);
-    return (int)std::max<int64_t>(1, std::min(ceil_div(N, blk), ga));
+    // [B, N, H, d]: 1.72 ms, 1.95 in one round).  Beyond 128 heads a round does
+    // not divide evenly: the count, up to sixteen, whose rounds of (tokens each
+    // + the operands' 300) are fewest (4,095 tokens: 129 heads, 3 each, 85 us,
+    // 125 with 1 and 100 with 2; 256, 2, 127, 145 with 1 and 160 with 3; 300, 3,
+    // 165, 197 and 175; 384, 4, 199, 215 and 199; 500, 1, 236, 243 with 2).
+    if (BH <= 128)
+      return (int)std::max<int64_t>(
+          1, std::min(ceil_div(N, blk), std::max(512 / BH, std::min(ceil_div(4096, BH), N / 8192))));
+    int64_t ga = 1, least = INT64_MAX;
+    for (int64_t g = 1; g <= std::min<int64_t>(16, ceil_div(N, blk)); ++g) {
+      const int64_t cost = ceil_div(BH * g, 512) * (ceil_div(ceil_div(N, blk), g) * blk + 300);
+      if (cost < least) { least = cost; ga = g; }
+    }
+    return (int)ga;
   }
   const int64_t grid = 4096;
   int64_t ga = std::min(ceil_div(N, blk), ceil_div(grid, BH));
