@@ -100,7 +100,9 @@ bool team_summary(int64_t N, int d, int dt) {
 // not below 4 d (2 d) tokens, so that a few heads still fill compute units:
 // one head of 4,096 fp32 tokens (d = 64) takes 14 us in sixteen partials and
 // 21 in eight, while 1,024 heads of 8,192 bf16 tokens take 396 + 94 us
-// (summary + combine) in four and 430 + 110 in eight.  A single wave's
+// (summary + combine) in four and 430 + 110 in eight.  (fp32 at d = 64: up to
+// 1,024 tokens are one FP32 sum, but 32 to an accumulation; S is 1.8e-7 off
+// where 512 tokens, four to an accumulation, left 4.0e-7.)  A single wave's
 // partials: 2048 (512) tokens, at d <= 32 up to sixteen of at least 4 d.
 int64_t summary_partials(int64_t N, int d, int dt) {
   const int64_t unit = dt == LA_BF16 ? 4 * d : 2 * d;

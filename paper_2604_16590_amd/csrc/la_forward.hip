@@ -72,8 +72,9 @@ __device__ __forceinline__ void summary_load(const char* kh, const char* vh, uin
 }
 
 // A partial's tokens are summed in runs of Tq (summary_run), from zero each,
-// and the runs' sums added in order in FP32, so the same bits come of two
-// forms:
+// and the runs' sums added in order in FP32, so that the same bits come of
+// two forms (teams always take the second, and join longer partials' runs in
+// FP64, join64):
 // NW = 1: a wave to a partial takes its runs one after the other and keeps
 // the sum so far in LDS.  One dimension of waves in (partial, (b, h)) order,
 // (b, h) fastest: wave w takes partial w / BH of (b, h) = w % BH, so a
@@ -91,7 +92,7 @@ template <int DT, int D, int MODE, int NW>
 __global__ __launch_bounds__(NW == 1 ? 256 : 64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 16 ? 4 : SummaryCfg<DT, D, MODE>::WAVES_PER_SIMD))) void summary_kernel(
     const void* __restrict__ k, const void* __restrict__ v, int64_t sb,
     int64_t sh, int64_t sn, int H, int64_t N, int P, int Tw, int Tq,
-    const float2* __restrict__ stash, float* __restrict__ part, int BH) {
+    const float2* __restrict__ stash, float* __restrict__ part, int BH, bool join64) {
   using C = SummaryCfg<DT, D, MODE>;
   constexpr int F = C::F;
   constexpr int E = D * D + D;
@@ -191,6 +192,34 @@ __global__ __launch_bounds__(NW == 1 ? 256 : 64 * NW) __attribute__((amdgpu_wave
     __shared__ f32x4 red[NW][RT][64];
     __shared__ float zred[NW][D];
     const int runs = (int)((min(N - (int64_t)p * Tw, (int64_t)Tw) + Tq - 1) / Tq);
+    // K neighbouring sums, the runs' sums in order.  Only teams of four join
+    // in FP64, with all loads in flight (no branch divides them)
+    constexpr bool J64 = NW == 4 && D >= 64;
+    auto join = [&](auto kc, auto at, float* x) {
+      constexpr int K = decltype(kc)::value;
+#pragma unroll
+      for (int j = 0; j < K; ++j) x[j] = at(0, j);
+      if (J64 && join64) {
+        float y[NW][K];
+#pragma unroll
+        for (int w = 1; w < NW; ++w)
+#pragma unroll
+          for (int j = 0; j < K; ++j) y[w][j] = at(w, j);
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+          double s = x[j];
+#pragma unroll
+          for (int w = 1; w < NW; ++w) {
+            if (w < runs) s += (double)y[w][j];
+          }
+          x[j] = (float)s;
+        }
+      } else {
+        for (int w = 1; w < runs; ++w)
+#pragma unroll
+          for (int j = 0; j < K; ++j) x[j] += at(w, j);
+      }
+    };
 #pragma unroll
     for (int i = 0; i < F; ++i) {
       const float zs = sum_groups(zacc[i]);
@@ -206,22 +235,16 @@ __global__ __launch_bounds__(NW == 1 ? 256 : 64 * NW) __attribute__((amdgpu_wave
       for (int u = wave; u < RT / F * 4; u += NW) {
         const int t = u / 4 * F, r = u % 4;
         float x[F];
-#pragma unroll
-        for (int j = 0; j < F; ++j) x[j] = red[0][t + j][lane][r];
-        for (int w = 1; w < runs; ++w)
-#pragma unroll
-          for (int j = 0; j < F; ++j) x[j] += red[w][t + j][lane][r];
+        join(std::integral_constant<int, F>{}, [&](int w, int j) { return red[w][t + j][lane][r]; }, x);
         uint32_t w[F];
 #pragma unroll
         for (int j = 0; j < F; ++j) w[j] = __float_as_uint(x[j]);
         store_words<4 * F>(out + (F * (4 * g + r) + (r0 + t) / F) * D + F * m, w);
       }
     }
-    if (threadIdx.x < D) {
-      float x = zred[0][threadIdx.x];
-      for (int w = 1; w < runs; ++w) x += zred[w][threadIdx.x];
-      out[D * D + threadIdx.x] = x;
-    }
+    if (threadIdx.x < D)
+      join(std::integral_constant<int, 1>{}, [&](int w, int) { return zred[w][threadIdx.x]; },
+           out + D * D + threadIdx.x);
     return;
   }
 
@@ -855,8 +878,12 @@ static void launch_summary_t(const void* k, const void* v, int64_t sb, int64_t s
   } else {
 #define LA_SUM(NW, GRID)                                                             \
   summary_kernel<DT, D, MODE, NW><<<GRID, NW == 1 ? 256 : 64 * NW, 0, stream>>>(      \
-      k, v, sb, sh, sn, (int)H, N, P, Tw, Tq, stash, part, (int)BH)
+      k, v, sb, sh, sn, (int)H, N, P, Tw, Tq, stash, part, (int)BH, join64)
     const int Tq = summary_run(D, Tw, team);
+    // an FP32 sum covers at most 2,048 (d = 128) or 512 tokens of a team's
+    // (the join in FP64 takes conversions: 2 us of the 20 of two heads of
+    // 1,000 tokens at d = 128, whose partials are shorter)
+    const bool join64 = team && Tw > (D >= 128 ? 2048 : 512);
     const int runs = (Tw + Tq - 1) / Tq;
     // A wave to a whole partial where those fill the chip, d = 64: from 832
     // partials (12 heads of 50,000 tokens in 64 each: 40 us by teams, 44; 14:
