@@ -82,15 +82,19 @@ int64_t fused_partials(int64_t N, int d) {
                   std::min<int64_t>(4, ceil_div(N, 4 * d)));
 }
 
-// bf16 summaries with four waves to a partial: sequences too short for
-// max_partials of a single wave's 2048 (d = 128) or 512 tokens.  Longer ones
+// bf16 summaries with four waves to a partial: sequences too short for 64
+// partials of a single wave's 2048 (d = 128) or 512 tokens.  Longer ones
 // keep the SIMDs streaming with a wave to a partial, whose four waves of a
 // workgroup, four heads of a token range, read a BNHD view best (8 x 8 heads
-// of 63,607 tokens at d = 64, BNHD: 200 us, 224 with teams).  At d <= 32
-// heads of a BNHD view share cache lines, and it is the better form for all
-// (d = 32, 8 heads of 30,001 tokens: 34 us, 38).
+// of 63,607 tokens at d = 64, BNHD: 200 us, 224 with teams).  A team is one
+// workgroup a compute unit at d = 128, so eight heads of more than 131,072
+// tokens would take a second round of them: the forward of 8 x 262,144 takes
+// 417 us, 441 with teams, gated on BNHD views 545, 574 (one head of 200,001
+// would take 121 instead of 181, but the bits may not follow the head count).
+// At d <= 32 heads of a BNHD view share cache lines, and a single wave is the
+// better form for all (d = 32, 8 heads of 30,001 tokens: 34 us, 38).
 bool team_summary(int64_t N, int d, int dt) {
-  return dt == LA_BF16 && d >= 64 && N <= max_partials(d) * (d >= 128 ? 2048 : 512);
+  return dt == LA_BF16 && d >= 64 && N <= 64 * (d >= 128 ? 2048 : 512);
 }
 
 // The summary's partials.  A partial's write and read cost 2 (d + 1) * 4
