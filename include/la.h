@@ -101,13 +101,14 @@ la_status la_version(int32_t* major, int32_t* minor);
 /*
  * Device workspace the caller must provide for a pass (0 = forward,
  * 1 = backward, 2 = apply), in bytes, 256-byte aligned.  It holds O(d^2)
- * per head (the FP64 summary and its matrix-core operand images) plus the
+ * per head (the FP64 summary and its matrix-core operand images; for the
+ * apply, room for the images that is no longer used) plus the
  * per-tile partial sums of the token reduction.  Each partial sums at most
  * 16,384 tokens (bf16 inputs; 4,096 for fp32) in FP32 before the partials
  * are added in FP64, so the FP32 part of every sum over tokens is bounded
  * whatever N is; there are at most 128 partials (d = 128) or 64 (d < 128) until
- * that bound is reached (2,097,152 or 1,048,576 bf16 tokens per head) and
- * grows with N beyond it, by (d*d + d) * 4 bytes per 16,384 tokens per
+ * that bound is reached (2,097,152 or 1,048,576 bf16 tokens per head); beyond
+ * it the size grows with N, by (d*d + d) * 4 bytes per 16,384 tokens per
  * head (0.8 % of the bytes of K and V at d = 128).  Where the backward runs
  * its query pass and its dS reduction separately (fp32 inputs, and
  * d = 16) it adds 8 bytes per (b, h, token) for the per-query pair

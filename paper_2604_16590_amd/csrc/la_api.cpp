@@ -197,11 +197,12 @@ struct Layout {
   size_t part, S64, z64, img, stash, dS64, dz64, dimg, total;
 };
 
-// Forward: [part][S64][z64][img].  Apply: [img].
-// Backward: [part][stash][dS64][dz64][dimg]; the stash holds two floats
-// per query token (1/den, -(dO . O)) between the query kernel and the dS
-// reduction, the only part of any workspace that grows with N.  bf16 at
-// d >= 32 fuses the two passes and needs no stash.
+// Forward: [part][S64][z64][img].  Backward: [part][stash][dS64][dz64][dimg];
+// the stash holds two floats per query token (1/den, -(dO . O)) between the
+// query kernel and the dS reduction, the only part of any workspace that
+// grows with N.  bf16 at d >= 32 fuses the two passes and needs no stash;
+// fp32 at d >= 64 has no images.  The apply makes its operands in LDS; its
+// workspace stays the two images that callers have always brought.
 Layout layout_for(const la_attn_desc* d, int pass, bool coarse = false) {
   const int64_t BH = d->B * d->H, D = d->d;
   const Tiling t = choose_tiling(d->N, (int)D, d->in_dtype, pass == 1, coarse);
@@ -209,11 +210,13 @@ Layout layout_for(const la_attn_desc* d, int pass, bool coarse = false) {
   const size_t part = align_up((size_t)BH * room * (D * D + D) * sizeof(float));
   const size_t mat = align_up((size_t)BH * D * D * sizeof(double));
   const size_t vec = align_up((size_t)BH * D * sizeof(double));
-  const size_t img = align_up((size_t)BH * head_image_bytes((int)D, d->in_dtype));
+  const size_t img = pass != 2 && la::fp32_rows(d->in_dtype, (int)D)
+                         ? 0
+                         : align_up((size_t)BH * head_image_bytes((int)D, d->in_dtype));
   Layout L{};
   size_t off = 0;
   if (pass == 2) {
-    L.img = off; off += img;
+    off += img;
   } else if (pass == 0) {
     L.part = off; off += part;
     L.S64 = off; off += mat;
@@ -392,7 +395,7 @@ la_status apply_impl(const la_attn_desc* desc, const void* q, const double* s, c
   if (((uintptr_t)s & 7u) || ((uintptr_t)z & 7u)) return LA_ERR_INVALID_ARG;
   if (((uintptr_t)ws % kAlign) != 0) return LA_ERR_INVALID_ARG;
   const Layout L = layout_for(desc, 2);
-  if (ws_bytes < L.total) return LA_ERR_OOM;
+  if (ws_bytes < L.total) return LA_ERR_OOM;  // (it is not used)
   la::FwdArgs a{};
   a.B = desc->B; a.H = desc->H; a.N = desc->N; a.D = (int)desc->d;
   a.in_dt = desc->in_dtype; a.out_dt = desc->out_dtype;
@@ -402,7 +405,6 @@ la_status apply_impl(const la_attn_desc* desc, const void* q, const double* s, c
   a.Ga = apply_groups(desc->N, desc->B * desc->H, (int)desc->d);
   a.S64 = const_cast<double*>(s);
   a.z64 = const_cast<double*>(z);
-  a.img = (char*)ws + L.img;
   a.other = other; a.sigma = sigma; a.sigma_data = sigma_data;
   a.stream = (hipStream_t)stream;
   hipError_t e = la::launch_apply(a);

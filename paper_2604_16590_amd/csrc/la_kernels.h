@@ -328,7 +328,7 @@ struct FwdArgs {
   double* S64;         // [BH][D][D]
   double* z64;         // [BH][D]
   bool want_summary;   // S64, z64 are results
-  void* img;           // [BH][2 images]
+  void* img;           // [BH][2 images] (forward, but not fp32_rows)
   // noise-gated mix (null `other`: plain output): o = g_b A + (1 - g_b) other,
   // g_b = sigma_data / (sigma_data + sigma[b])
   const void* other;   // output dtype and strides
@@ -350,7 +350,7 @@ struct BwdArgs {
   float2* stash;       // [BH][N] per query token: (1/den, -(dO . O))
   double* dS64;
   double* dz64;
-  void* dimg;          // images of dS
+  void* dimg;          // images of dS (not fp32_rows)
   hipStream_t stream;
 };
 
