@@ -11,12 +11,12 @@
 // phi(Q) and phi(K) are recomputed from the inputs here, never stored by
 // the forward (the paper trains with activation recomputation, Sec. III-D).
 //
-// Passes: (1) images of S; (2) the query pass: dQ and each wave's partial
-// sums of dS, dz in one kernel for bf16 at d >= 32 (bwd_qds_kernel,
-// bwd_qds4_kernel), otherwise the query kernel (dQ and per-token
-// (1/den, dden)) followed by the token reduction for dS, dz (the forward's
-// summary kernel in its backward mode); (3) FP64 combine of dS, dz;
-// (4) key kernel: dK, dV.
+// Passes: (1) the query pass: dQ and each workgroup's partial sums of dS, dz in
+// one kernel for bf16 at d >= 32 (bwd_qds_kernel, bwd_qds4_kernel), otherwise
+// the query kernel (dQ and per-token (1/den, dden)) followed by the token
+// reduction for dS, dz (the forward's summary kernel in its backward mode);
+// (2) FP64 combine of dS, dz, unless the key pass adds up their partials
+// itself; (3) key kernel: dK, dV.  fp32 at d = 64 and 128: la_fp32.hip.
 #include <type_traits>
 
 #include "la_kernels.h"
@@ -252,30 +252,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void b
       for (int w = 0; w < C::RWD; ++w) { qw[w] = 0; gw[w] = 0; }
     }
   };
-  constexpr int PT = C::PF ? TT : 1;  // tiles held ahead of their step
-  typedef uint32_t Regs[PT][2][C::RWD];
+  static_assert(C::PF, "a step's tiles are held ahead of it");
+  typedef uint32_t Regs[TT][2][C::RWD];
   auto load = [&](int64_t t0, Regs& x) {
 #pragma unroll
-    for (int tt = 0; tt < PT; ++tt) load_one(t0 + 16 * tt, x[tt][0], x[tt][1]);
+    for (int tt = 0; tt < TT; ++tt) load_one(t0 + 16 * tt, x[tt][0], x[tt][1]);
   };
 
   auto compute = [&](int64_t t0, const Regs& x) {
     uint32_t pq[TT][C::PW], pg[TT][C::PW];
-    if constexpr (C::PF) {
 #pragma unroll
-      for (int tt = 0; tt < TT; ++tt) {
-        phi_words<DT, D>(x[tt][0], pq[tt]);
-        raw_words<DT, D>(x[tt][1], pg[tt]);
-      }
-    } else {
-      // load and convert one tile at a time (fewer live registers)
-#pragma unroll
-      for (int tt = 0; tt < TT; ++tt) {
-        uint32_t one[2][C::RWD];
-        load_one(t0 + 16 * tt, one[0], one[1]);
-        phi_words<DT, D>(one[0], pq[tt]);
-        raw_words<DT, D>(one[1], pg[tt]);
-      }
+    for (int tt = 0; tt < TT; ++tt) {
+      phi_words<DT, D>(x[tt][0], pq[tt]);
+      raw_words<DT, D>(x[tt][1], pg[tt]);
     }
     f32x4 acc[TT][NT];
 #pragma unroll
@@ -317,18 +306,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void b
     }
   };
 
-  // two register sets in turn where the registers allow a step ahead
+  // two register sets in turn
   constexpr int STRIDE = 16 * TT * 4;
   Regs ra, rb;
   int64_t t0 = wg_begin + 16 * TT * wave;
-  if (C::PF && t0 < wg_end) load(t0, ra);
+  if (t0 < wg_end) load(t0, ra);
   while (t0 < wg_end) {
     const int64_t t1 = t0 + STRIDE;
-    if (C::PF && t1 < wg_end) load(t1, rb);
+    if (t1 < wg_end) load(t1, rb);
     compute(t0, ra);
     if (t1 >= wg_end) break;
     const int64_t t2 = t1 + STRIDE;
-    if (C::PF && t2 < wg_end) load(t2, ra);
+    if (t2 < wg_end) load(t2, ra);
     compute(t1, rb);
     t0 = t2;
   }
@@ -393,8 +382,8 @@ void bwd_qds_kernel(const void* __restrict__ q, const void* __restrict__ dout, i
   const int lane = threadIdx.x & 63, wave = wave_index();
   const int g = lane >> 4, n = lane & 15;
   // wave w of partial p takes the head's 32-token blocks 4p + w, 4p + w +
-  // 4P, ... (a partial at most Tw tokens), so the grid's waves move through
-  // Q, G and dQ together
+  // 4P, ... (a partial 128 ceil(ceil(N / 32) / 4P) tokens at most, a wave a
+  // quarter of them), so the grid's waves move through Q, G and dQ together
   const int p = hp.g;
   const int64_t nb = (N + 16 * TT - 1) / (16 * TT), b0 = 4 * (int64_t)p + wave;
   const int nsteps = b0 < nb ? (int)((nb - 1 - b0) / (4 * (int64_t)P) + 1) : 0;
@@ -579,7 +568,7 @@ void bwd_qds_kernel(const void* __restrict__ q, const void* __restrict__ dout, i
 
 // ---------------------------------------------------------------------------
 // Fused query backward at d = 128 (bf16): the four waves of a workgroup
-// share one partial (64-token blocks p, p + P, ..., at most Tw tokens),
+// share one partial (64-token blocks p, p + P, ...),
 // taking 16-token tiles in turn (one block per step); two workgroups fit a compute unit, so one
 // waiting at a barrier leaves the SIMDs to the other.  Each wave does the
 // query pass for its tile and puts its tile's rows into LDS; after a barrier, wave w
@@ -636,11 +625,11 @@ void bwd_qds4_kernel(const void* __restrict__ q, const void* __restrict__ dout, 
   const int lane = threadIdx.x & 63, wave = wave_index();
   const int g = lane >> 4, n = lane & 15;
   // partial p (this workgroup) takes the head's 64-token blocks p, p + P,
-  // p + 2P, ... (at most Tw tokens), so the grid moves through Q, G and dQ
-  // together; the step count is the same for all waves
+  // p + 2P, ..., so the grid moves through Q, G and dQ together; the step
+  // count is the same for all waves
   const int p = blockIdx.x;
   const int64_t nb = (N + 16 * NW - 1) / (16 * NW);
-  const int nsteps = (int)((nb - 1 - p) / P + 1);  // >= 1: P <= N / 64 <= nb
+  const int nsteps = (int)((nb - 1 - p) / P + 1);  // >= 1: P <= ceil(N / 64) = nb
   auto block_token = [&](int k) { return ((int64_t)p + (int64_t)k * P) * (16 * NW); };
 
   const int64_t row_bytes = sn * 2, orow_bytes = osn * OES;
@@ -1073,7 +1062,7 @@ static hipError_t launch_rows(const BwdArgs& a) {
           a.z64, a.stash, (int)G, BH, shared);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    e = launch_summary(MODE_BWD, DT, D, a.q, a.dout, a.sb, a.sh, a.sn, a.B, a.H, a.N, a.P, a.Tw,
+    e = launch_summary_bwd(DT, D, a.q, a.dout, a.sb, a.sh, a.sn, a.B, a.H, a.N, a.P, a.Tw,
                        a.stash, a.part, a.stream);
     if (e != hipSuccess) return e;
     if (!fold) e = launch_combine(a.part, a.P, a.dS64, a.dz64, a.dimg, DT, BH, D, IMG_T | IMG_N, a.stream);

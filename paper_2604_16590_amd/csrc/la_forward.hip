@@ -926,16 +926,20 @@ static void launch_summary_d(int mode, int dt, const void* k, const void* v, int
 #undef LA_SUM
 }
 
-hipError_t launch_summary(int mode, int dt, int D, const void* k, const void* v, int64_t sb,
-                          int64_t sh, int64_t sn, int64_t B, int64_t H, int64_t N, int P,
-                          int Tw, const float2* stash, float* part, hipStream_t stream) {
+hipError_t launch_summary_bwd(int dt, int D, const void* q, const void* g, int64_t sb, int64_t sh,
+                              int64_t sn, int64_t B, int64_t H, int64_t N, int P, int Tw,
+                              const float2* stash, float* part, hipStream_t stream) {
+  if (dt == DT_BF16 && D != 16) return hipErrorInvalidValue;  // la_backward.hip's fused pass
+#define LA_SUM(D) \
+  launch_summary_d<D>(MODE_BWD, dt, q, g, sb, sh, sn, B, H, N, P, Tw, false, stash, part, stream)
   switch (D) {
-    case 16: launch_summary_d<16>(mode, dt, k, v, sb, sh, sn, B, H, N, P, Tw, false, stash, part, stream); break;
-    case 32: launch_summary_d<32>(mode, dt, k, v, sb, sh, sn, B, H, N, P, Tw, false, stash, part, stream); break;
-    case 64: launch_summary_d<64>(mode, dt, k, v, sb, sh, sn, B, H, N, P, Tw, false, stash, part, stream); break;
-    case 128: launch_summary_d<128>(mode, dt, k, v, sb, sh, sn, B, H, N, P, Tw, false, stash, part, stream); break;
+    case 16: LA_SUM(16); break;
+    case 32: LA_SUM(32); break;
+    case 64: LA_SUM(64); break;
+    case 128: LA_SUM(128); break;
     default: return hipErrorInvalidValue;
   }
+#undef LA_SUM
   return hipGetLastError();
 }
 
@@ -943,7 +947,6 @@ template <int D>
 static void launch_combine_d(const float* part, int P, double* M64, double* v64, void* img,
                              int img_dt, int64_t BH, int what, hipStream_t stream) {
   const dim3 grid(D / 8 + 1, (unsigned)BH);
-  constexpr int E = D * D + D;
   if (img_dt == DT_BF16)
     combine_kernel<D, DT_BF16><<<grid, 8 * D, 0, stream>>>(part, P, M64, v64, img, what);
   else

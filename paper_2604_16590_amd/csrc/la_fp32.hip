@@ -662,7 +662,7 @@ hipError_t backward_d(const BwdArgs& a) {
         a.stash);
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  e = launch_summary(MODE_BWD, DT_FP32, D, a.q, a.dout, a.sb, a.sh, a.sn, a.B, a.H, a.N, a.P, a.Tw,
+  e = launch_summary_bwd(DT_FP32, D, a.q, a.dout, a.sb, a.sh, a.sn, a.B, a.H, a.N, a.P, a.Tw,
                      a.stash, a.part, a.stream);
   if (e != hipSuccess) return e;
   e = launch_combine(a.part, a.P, a.dS64, a.dz64, nullptr, DT_FP32, BH, D, 0, a.stream);

@@ -176,7 +176,7 @@ inline dim3 row_grid(int64_t G, int64_t BH, bool shared) {
 
 // A head's d x d matrix and d vector where a workgroup makes its operands
 // itself: in FP64, or (part) as P <= 4 partial sums [d][d], [d] still to be
-// added, in the combine's order.
+// added, in the combine's order (more, at d <= 32: sum_partials first).
 template <int D>
 struct MatrixSrc {
   const double* M;
@@ -362,11 +362,11 @@ int32_t record_hip_error(int32_t e);
 hipError_t launch_forward(const FwdArgs& a);
 // Apply only, of a given S and z.
 hipError_t launch_apply(const FwdArgs& a);
-// Token-reduction kernel: forward summary (MODE_FWD) or the dS/dz sums of
-// the backward (MODE_BWD, k = Q, v = dO, stash = per-token (1/den, -(dO . O))).
-hipError_t launch_summary(int mode, int dt, int D, const void* k, const void* v, int64_t sb,
-                          int64_t sh, int64_t sn, int64_t B, int64_t H, int64_t N, int P,
-                          int Tw, const float2* stash, float* part, hipStream_t stream);
+// The dS/dz sums of the two-pass backward (fp32 and d = 16; g = dO, stash =
+// per-token (1/den, -(dO . O))).
+hipError_t launch_summary_bwd(int dt, int D, const void* q, const void* g, int64_t sb, int64_t sh,
+                              int64_t sn, int64_t B, int64_t H, int64_t N, int P, int Tw,
+                              const float2* stash, float* part, hipStream_t stream);
 // FP64 sum of the P partials [D][D], [D] of each head, and the operands
 // `what` (IMG_*) of the result.
 hipError_t launch_combine(const float* part, int P, double* M64, double* v64, void* img,
