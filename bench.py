@@ -473,10 +473,9 @@ def cpu_baseline_other_workloads():
 
 # attention kernels of the long-context step, by the demangled name's start
 PROFILE_KERNELS = (("la::summary_kernel<0, 128, 0", "summary_fwd"),
-                   ("la::combine_kernel<128, 0>", "combine"),
+                   ("la::combine_kernel<128, 0>", "combine"),  # both passes' (of S, z and of dS, dz)
                    ("la::apply_kernel<0, 0, 128, false>", "apply"),
                    ("la::bwd_qds4_kernel<0>", "bwd_query_ds"),
-                   ("la::combine_kernel<128, 1>", "combine_bwd"),
                    ("la::bwd_key_kernel<0, 0, 128", "bwd_key"))
 COPY_KERNEL = "stream_copy_swept_kernel"
 
@@ -564,7 +563,7 @@ def summarize_profiles(top, prof=None):
         events = {k: v["avg_ms"] * 1e6 for k, v in last_json_line(trace_out)["kernels"].items()}
     for r in sorted(rows, key=lambda r: -float(r["TotalDurationNs"])):
         pname = profile_name(r["Name"])
-        ev = events.get(pname if pname != "combine_bwd" else "", None)
+        ev = events.get(pname, None)
         med = median(durs.get(r["Name"], []))
         lines.append("%-14s %-60s %6s %14s %12.0f %7.2f %12s %13s" % (
             pname or "-", r["Name"][:60], r["Calls"], r["TotalDurationNs"],
@@ -592,10 +591,9 @@ def summarize_profiles(top, prof=None):
             continue
         fk = fetch.get(name, (0.0, 0))[0]
         wk = write.get(name, (0.0, 0))[0]
-        base = pname if pname != "combine_bwd" else "combine"
         kern[pname] = {"fetch_kib": fk, "write_kib": wk,
                        "hbm_bytes_per_launch": (fk * f_fac + wk * w_fac) * 1024.0,
-                       "alg_bytes_per_launch": KERNEL_PASSES.get(base, 0) * elems * 2,
+                       "alg_bytes_per_launch": KERNEL_PASSES.get(pname, 0) * elems * 2,
                        "dispatches": fetch.get(name, (0.0, 0))[1]}
     # the digest of the sources the counted runs used (their bench lines
     # carry it), so that counters taken on other sources never pass for
