@@ -143,11 +143,14 @@ def make_desc(q: torch.Tensor, out: torch.Tensor) -> AttnDesc:
 # engine's thread and the caller's wake each other): two heads of 1,000 tokens
 # at d = 128 take 126 us a pass on the host, 146 without these.  Hence the raw stream handle (0.1
 # us; a torch Stream object 2.0) and one comparison of whole stride tuples.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # private: may go
+
+
 def _stream(device) -> int:
     index = device.index
-    if device.type != "cuda" or index is None:
+    if _raw_stream is None or device.type != "cuda" or index is None:
         return torch.cuda.current_stream(device).cuda_stream
-    return torch._C._cuda_getCurrentRawStream(index)
+    return _raw_stream(index)
 
 
 def workspace_size(desc: AttnDesc, pass_: int) -> int:
