@@ -417,17 +417,15 @@ int admit(la_server* s) {
     int64_t m = left;
     if (s->cfg.max_members_per_slice > 0) m = std::min<int64_t>(m, s->cfg.max_members_per_slice);
     size_t room = s->arena.largest_free();
-    const Block lean = lean_block(r, s->arena.size());
     if (cap > 0) {
       size_t one = slice_block(r, 1).bytes();
-      if (keep_bytes(r) + one > s->arena.size()) one = lean.bytes();
+      if (keep_bytes(r) + one > s->arena.size()) one = lean_block(r, s->arena.size()).bytes();
       room = std::min(room, std::max<size_t>(s->cfg.hbm_budget_bytes / s->cfg.max_slots, one));
     }
     while (m > 0 && slice_block(r, m).bytes() > room) m = m > 8 ? m * 3 / 4 : m - 1;
-    Block block = lean;
-    if (m > 0) block = slice_block(r, m);
-    else if (lean.bytes() <= room) m = 1;
-    else break;
+    const Block block = m > 0 ? slice_block(r, m) : lean_block(r, s->arena.size());
+    if (block.bytes() > room) break;
+    m = std::max<int64_t>(m, 1);
     Slice sl{};
     sl.req = id;
     sl.index = rq.slices_started;
@@ -601,7 +599,8 @@ la_status la_serve_submit(la_server* s, const la_request* r, uint64_t* id) {
         od.d != d.d || od.in_dtype != d.in_dtype)
       return LA_ERR_INVALID_ARG;
   }
-  if (keep_bytes(req) + lean_block(req, s->arena.size()).bytes() > s->arena.size()) {
+  if (keep_bytes(req) + slice_block(req, 1).bytes() > s->arena.size() &&
+      keep_bytes(req) + lean_block(req, s->arena.size()).bytes() > s->arena.size()) {
     s->n_rejected += 1;
     return LA_ERR_OOM;
   }
