@@ -481,7 +481,7 @@ void bwd_qds_kernel(const void* __restrict__ q, const void* __restrict__ dout, i
       const double rden = 1.0 / (double)dacc[tt][0][0];
       const bool ok = t0 + 16 * tt + n < N;
       const float rd = ok ? (float)rden : 0.f;  // zero past the end: no dS, dz share
-      const float go = ok ? gn * rd : 0.f;      // G . O
+      const float go = (ok ? gn : 0.f) * rd;    // G . O
       const float dd = -go * rd;
       // dQ chunk by chunk (few live registers): run positions [CH*w, +CH);
       // phi(q)/den rows into LDS
@@ -722,7 +722,7 @@ void bwd_qds4_kernel(const void* __restrict__ q, const void* __restrict__ dout, 
 #pragma unroll
       for (int r = 0; r < 4; ++r) gn += run_val<DT_BF16>(pq, 4 * i + r) * acc[i][r];
     gn = sum_groups(gn);
-    const float go = ok ? gn * rd : 0.f;
+    const float go = (ok ? gn : 0.f) * rd;
     // dz = sum_i dden_i phi(q_i) = sum_i (phi(q_i)/den_i)(-G_i . O_i): one
     // more column block of the dS product, whose B operand holds -G.O of
     // each token as a bf16 pair hi + lo in columns 0 and 1 (made
