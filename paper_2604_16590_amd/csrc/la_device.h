@@ -37,6 +37,28 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, r);
 }
 
+// N doubles -> N / 2 packed bfloat16 pairs, each rounded once: a double that
+// rounds to an fp32 midpoint of two bfloat16 values without being it goes to
+// its own side first (one value in 2^16 is a midpoint).
+template <int N>
+__device__ __forceinline__ void pack_bf16_once(const double* x, uint32_t* w) {
+  uint32_t f[N], off = 1;
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    f[j] = __float_as_uint((float)x[j]);
+    off = j ? min(off, (f[j] ^ 0x8000u) & 0xffffu) : (f[j] ^ 0x8000u) & 0xffffu;
+  }
+  if (off == 0)
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+      if ((f[j] & 0xffffu) == 0x8000u) {
+        const double m = (double)__uint_as_float(f[j]);
+        if (x[j] != m) f[j] += fabs(x[j]) > fabs(m) ? 1 : -1;
+      }
+#pragma unroll
+  for (int j = 0; j < N; j += 2) w[j >> 1] = pack_bf16(__uint_as_float(f[j]), __uint_as_float(f[j + 1]));
+}
+
 // x + (sum of the two bfloat16 halves of w), exact products, FP32 sums.
 __device__ __forceinline__ float add_bf16_pair(float x, uint32_t w) {
   return x + (bf16lo(w) + bf16hi(w));
